@@ -515,8 +515,9 @@ __device__ __forceinline__ int32_t key_tri(unsigned long long k) {
 constexpr double T_ERR_MAX = 9.5e-6;
 
 // Pair test of the link from X (centre frame) along c against a staged
-// candidate: 0 miss, 1 hit (t), -1 undecided (left to the exact pass).
-template <typename R>
+// candidate: 0 miss, 1 hit (t), 2 hit whose t needs the vertices themselves
+// (VERTEX_T: by vertex_t), -1 undecided (left to the exact pass).
+template <typename R, bool VERTEX_T>
 __device__ __forceinline__ int pair_test(const CandSoA<R>& CS, int ci, const R Xp[3], const R cv[3], double& t, QStats& st) {
 #define CF(k) CS.f[(k)][ci]
     constexpr R u = Unit<R>::u;
@@ -555,10 +556,14 @@ __device__ __forceinline__ int pair_test(const CandSoA<R>& CS, int ci, const R X
             t = (double)tf;
             return 1;
         }
-        if (!((CS.tri[ci] >> 29) & C_EXACT)) return -1;
+        if (!((CS.tri[ci] >> 29) & C_EXACT)) {
+            if constexpr (!VERTEX_T) return -1;
+            st.t64++;
+            return 2;
+        }
+        st.t64++;
         // t from the staged vertices in float64: V0 = v0, V1 - V0 = -E_0,
         // V2 - V0 = E_2, all exact
-        st.t64++;
         const double a1[3] = {-(double)CF(F_E + 3 * 0 + 0), -(double)CF(F_E + 3 * 0 + 1), -(double)CF(F_E + 3 * 0 + 2)};
         const double a2[3] = {(double)CF(F_E + 3 * 2 + 0), (double)CF(F_E + 3 * 2 + 1), (double)CF(F_E + 3 * 2 + 2)};
         const double nn[3] = {a1[1] * a2[2] - a1[2] * a2[1], a1[2] * a2[0] - a1[0] * a2[2],
@@ -644,6 +649,41 @@ __device__ __forceinline__ double o3_value(const double* a, const double* b, con
     return adz * (bdx * cdy - cdx * bdy) + bdz * (cdx * ady - adx * cdy) + cdz * (adx * bdy - bdx * ady);
 }
 
+// scaled global coordinate v 2^L - 1/2 (exact), the frame of the exact pass
+__device__ __forceinline__ void vert_scaled(const DevMesh& m, int vid, double s, double g[3]) {
+    for (int a = 0; a < 3; a++) g[a] = load_coord(m, vid, a) * s - 0.5;
+}
+
+// hit parameter of X->Y on the plane of A, B, C, which its ends lie strictly on
+// either side of
+__device__ __forceinline__ double plane_t(const double* A, const double* B, const double* C, const double* X,
+                                          const double* Y) {
+    const double px = o3_value(A, B, C, X), py = o3_value(A, B, C, Y);
+    return fmin(fmax(px / (px - py), 0.0), 1.0);
+}
+
+// Hit parameter, from the vertices in float64, of a pair whose signs are
+// certain but whose float32 t is not near enough (float64 vertices whose local
+// coordinates are not float32 values: 1% of the pairs of a 112,000-triangle
+// star): the value that the exact pass gives.  Queued for that pass instead,
+// such pairs cost two atomics each on one address, a key and a second walk:
+// k_cl_q_f32 2.65 ms and the exact pass 0.25 ms there, 0.60 and 0.05 ms now.
+__device__ __forceinline__ double vertex_t(const DevMesh& m, int L, int tri, const int b0[3], const float Xp[3],
+                                           const float cv[3]) {
+    const double s = ldexp(1.0, L);
+    double A[3], B[3], C[3];
+    vert_scaled(m, m.tris[3 * (int64_t)tri], s, A);
+    vert_scaled(m, m.tris[3 * (int64_t)tri + 1], s, B);
+    vert_scaled(m, m.tris[3 * (int64_t)tri + 2], s, C);
+    double X[3], Y[3];
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        X[a] = (double)b0[a] + ((double)Xp[a] + 1.5);
+        Y[a] = X[a] + (double)cv[a];
+    }
+    return plane_t(A, B, C, X, Y);
+}
+
 // segment X->Y in the plane of T: entry parameter into the closed triangle
 template <int K>
 __device__ __forceinline__ int clip_axis(const double* A, const double* B, const double* C, const double* X,
@@ -701,9 +741,7 @@ __device__ __noinline__ int exact_seg_hit(const double* A, const double* B, cons
     const int v0 = o3_sign64(X, Y, A, B, st), v1 = o3_sign64(X, Y, B, C, st), v2 = o3_sign64(X, Y, C, A, st);
     const bool pos = v0 > 0 || v1 > 0 || v2 > 0, neg = v0 < 0 || v1 < 0 || v2 < 0;
     if (pos && neg) return 0;
-    const double px = o3_value(A, B, C, X), py = o3_value(A, B, C, Y);
-    t = px / (px - py);
-    t = fmin(fmax(t, 0.0), 1.0);
+    t = plane_t(A, B, C, X, Y);
     return 1;
 }
 
@@ -853,8 +891,9 @@ __device__ __forceinline__ void enqueue_fix(int32_t* fixq, int32_t* fixn, int64_
     m, d, wmask, loff, lval, lcap, blk_off, task_off, cap, link_cell, link_dir, link_q, link_tri, keys, mark, fixq, fixn, \
         pairq, pairn, pcap, sl
 
-// the q kernel's body, one wave per workgroup (both forms)
-template <typename R>
+// the q kernel's body, one wave per workgroup (both forms); F32V: the
+// vertices are float32 (float32 form only)
+template <typename R, bool F32V>
 __device__ __forceinline__ void cl_q_body(CL_Q_PARAMS) {
     __shared__ CandSoA<R> cand;
     // box test as bit masks over the staged candidates: for axis a and lattice
@@ -934,12 +973,8 @@ __device__ __forceinline__ void cl_q_body(CL_Q_PARAMS) {
 #pragma unroll
                     for (int i = 0; i < 3; i++) vid[i] = m.tris[3 * (int64_t)tri + i];
                 }
-                if constexpr (std::is_same<R, float>::value) {
-                    if (m.vdtype == GEO_F32) stage_cand_f32in(m, L, tri, vid, b0, cand, lane, blo, bhi, st);
-                    else stage_cand<R>(m, L, tri, vid, b0, cand, lane, blo, bhi, st);
-                } else {
-                    stage_cand<R>(m, L, tri, vid, b0, cand, lane, blo, bhi, st);
-                }
+                if constexpr (F32V) stage_cand_f32in(m, L, tri, vid, b0, cand, lane, blo, bhi, st);
+                else stage_cand<R>(m, L, tri, vid, b0, cand, lane, blo, bhi, st);
             }
             // first task of the next staging unit, and its candidates
             pf_task = -1;
@@ -1036,7 +1071,13 @@ __device__ __forceinline__ void cl_q_body(CL_Q_PARAMS) {
                 const R Xp[3] = {(R)xf.x, (R)xf.y, (R)xf.z};
                 const R cv[3] = {(R)((cw & 3) - 1), (R)(((cw >> 8) & 3) - 1), (R)(((cw >> 16) & 3) - 1)};
                 double tq;
-                const int res = pair_test<R>(cand, cidx, Xp, cv, tq, st);
+                int res = pair_test<R, !F32V>(cand, cidx, Xp, cv, tq, st);
+                if constexpr (std::is_same<R, float>::value && !F32V) {
+                    if (res == 2) {
+                        tq = vertex_t(m, L, cand.tri[cidx] & TRI_MASK, b0, Xp, cv);
+                        res = 1;
+                    }
+                }
                 if (res == 1) {
                     atomicMin(&lbest[ow], hit_key(tq, cand.tri[cidx] & TRI_MASK));  // each link keeps its nearest hit
                 } else if (res < 0) {
@@ -1095,18 +1136,18 @@ __device__ __forceinline__ void cl_q_body(CL_Q_PARAMS) {
     }
 }
 
-// float32 form: 4 waves per SIMD (128 VGPRs, under 10 KB of LDS per wave)
+// float32 form: 4 waves per SIMD (128 VGPRs, under 10 KB of LDS per wave); one
+// kernel per vertex type, since float32 vertices hardly ever need vertex_t and
+// its registers cost them 4% (2.95 -> 3.07 ms on the 7.2M-triangle star)
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) k_cl_q_f32(CL_Q_PARAMS) {
-    cl_q_body<float>(CL_Q_ARGS);
+    cl_q_body<float, true>(CL_Q_ARGS);
+}
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) k_cl_q_f32_v64(CL_Q_PARAMS) {
+    cl_q_body<float, false>(CL_Q_ARGS);
 }
 
 // float64 form
-__global__ void __launch_bounds__(64) k_cl_q_f64(CL_Q_PARAMS) { cl_q_body<double>(CL_Q_ARGS); }
-
-// scaled global coordinate v 2^L - 1/2 (exact), the frame of the exact pass
-__device__ __forceinline__ void vert_scaled(const DevMesh& m, int vid, double s, double g[3]) {
-    for (int a = 0; a < 3; a++) g[a] = load_coord(m, vid, a) * s - 0.5;
-}
+__global__ void __launch_bounds__(64) k_cl_q_f64(CL_Q_PARAMS) { cl_q_body<double, false>(CL_Q_ARGS); }
 
 // Exact pass, pairs: each queued (link, triangle) pair the filters left
 // undecided is tested with exact predicates (one thread per pair) and folded
@@ -1313,14 +1354,9 @@ int launch_cutlinks(const DevMesh& m, const DevLevel& d, const geo_bins* rows, c
     // balance better; empty ranges exit at once
     const unsigned gq = 65536;
     kt_record(GEO_KT_CUTLINKS_Q, s, false);
-    if (precision == GEO_PREC_F32_FALLBACK)
-        k_cl_q_f32<<<gq, 64, 0, s>>>(m, d, wmask, links->off, links->val, links->cap, blk_off, task_off, cap,
-                                        link_cell, link_dir, link_q, link_tri, keys, mark, fixq, fixn, pairq, pairn, pcap,
-                                    sl);
-    else
-        k_cl_q_f64<<<gq, 64, 0, s>>>(m, d, wmask, links->off, links->val, links->cap, blk_off, task_off, cap,
-                                         link_cell, link_dir, link_q, link_tri, keys, mark, fixq, fixn, pairq, pairn, pcap,
-                                    sl);
+    auto q_kernel = precision != GEO_PREC_F32_FALLBACK ? k_cl_q_f64 : m.vdtype == GEO_F32 ? k_cl_q_f32 : k_cl_q_f32_v64;
+    q_kernel<<<gq, 64, 0, s>>>(m, d, wmask, links->off, links->val, links->cap, blk_off, task_off, cap, link_cell, link_dir,
+                               link_q, link_tri, keys, mark, fixq, fixn, pairq, pairn, pcap, sl);
     kt_record(GEO_KT_CUTLINKS_Q, s, true);
     GEO_LAUNCH_CHECK();
     if (cap > 0) {
