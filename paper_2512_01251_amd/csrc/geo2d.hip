@@ -187,10 +187,6 @@ __global__ void __launch_bounds__(256) k2_bins(Dev2Mesh m, Dev2Level d, int kind
     }
 }
 
-__global__ void k2_copy_count(const int32_t* off, int64_t nkeys, int64_t* d_count) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *d_count = off[nkeys];
-}
-
 __global__ void k2_level0(int nbx, int nby, int32_t* bcoord) {
     const int64_t n = (int64_t)nbx * nby;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
@@ -526,7 +522,7 @@ int geo2_build_bins(const geo2_mesh* mesh, const geo2_level* lv, int32_t kind, g
     p += al256(sizeof(int32_t) * (size_t)(nkeys + 1));
     int32_t* cursor = reinterpret_cast<int32_t*>(p);
     p += al256(sizeof(int32_t) * (size_t)(nkeys + 1));
-    int32_t* partials = reinterpret_cast<int32_t*>(p);
+    int64_t* partials = reinterpret_cast<int64_t*>(p);
     int rc = geo_fill_i32(cnt, 0, nkeys + 1, s);
     if (rc == GEO_OK) rc = geo_fill_i32(cursor, 0, nkeys + 1, s);
     if (rc != GEO_OK) return rc;
@@ -537,9 +533,8 @@ int geo2_build_bins(const geo2_mesh* mesh, const geo2_level* lv, int32_t kind, g
     const unsigned g = grid1((int64_t)mesh->ne * 64, 256, 8192);  // one wave per edge
     if (mesh->ne > 0) k2_bins<false><<<g, 256, 0, s>>>(m, d, kk, scale, cnt, nullptr, nullptr, nullptr, 0);
     GEO_LAUNCH_CHECK();
-    rc = geo_scan_exclusive(cnt, bins->off, nkeys, partials, s);
+    rc = geo_scan_exclusive(cnt, bins->off, nkeys, partials, s, bins->d_count);
     if (rc != GEO_OK) return rc;
-    k2_copy_count<<<1, 64, 0, s>>>(bins->off, nkeys, bins->d_count);
     if (mesh->ne > 0)
         k2_bins<true><<<g, 256, 0, s>>>(m, d, kk, scale, nullptr, bins->off, cursor, bins->val, bins->cap);
     GEO_LAUNCH_CHECK();
@@ -584,7 +579,7 @@ int geo2_refine_flags(const geo2_level* lv, const uint16_t* solid, int32_t n_pro
     p += al256(sizeof(int32_t) * (size_t)(nb + 1));
     int32_t* off = reinterpret_cast<int32_t*>(p);
     p += al256(sizeof(int32_t) * (size_t)(nb + 1));
-    int32_t* partials = reinterpret_cast<int32_t*>(p);
+    int64_t* partials = reinterpret_cast<int64_t*>(p);
     const Dev2Level d = dev2_level(lv);
     const unsigned g = grid1(nb, 256, 16384);
     if (nb > 0) {
@@ -623,16 +618,15 @@ int geo2_cutlinks(const geo2_mesh* mesh, const geo2_level* lv, const geo_bins* r
     p += al256(sizeof(int32_t) * (size_t)(nb + 1));
     int32_t* off = reinterpret_cast<int32_t*>(p);
     p += al256(sizeof(int32_t) * (size_t)(nb + 1));
-    int32_t* partials = reinterpret_cast<int32_t*>(p);
+    int64_t* partials = reinterpret_cast<int64_t*>(p);
     const Dev2Mesh m = dev2_mesh(mesh);
     const Dev2Level d = dev2_level(lv);
     const double scale = ldexp(1.0, lv->level);
     const unsigned g = grid1(nb, 1, 65536);
     if (nb > 0) k2_cl_count<<<g, 64, 0, s>>>(m, d, rows->off, rows->val, rows->cap, scale, mask, cnt);
     GEO_LAUNCH_CHECK();
-    const int rc = geo_scan_exclusive(cnt, off, nb, partials, s);
+    const int rc = geo_scan_exclusive(cnt, off, nb, partials, s, d_nlinks);
     if (rc != GEO_OK) return rc;
-    k2_copy_count<<<1, 64, 0, s>>>(off, nb, d_nlinks);
     if (nb > 0)
         k2_cl_fill<<<g, 64, 0, s>>>(m, d, links->off, links->val, links->cap, scale, mask, off, cap, link_cell,
                                     link_dir, link_q, link_edge);

@@ -17,7 +17,12 @@ size_t bins_ws_bytes(int64_t nkeys, int64_t cap) {
            al(geo_scan_partials_bytes(nkeys));
 }
 
-size_t rows_levels_ws_bytes(int64_t nkeys, int64_t cap) { return bins_ws_bytes(nkeys, cap) + al(sizeof(int64_t)); }
+// each level's scan may end in a tile of its own
+size_t rows_partials_bytes(int64_t nkeys) { return geo_scan_partials_bytes(nkeys) + sizeof(int64_t) * GEO_MAX_LEVELS; }
+
+size_t rows_levels_ws_bytes(int64_t nkeys, int64_t cap) {
+    return bins_ws_bytes(nkeys, cap) + al(rows_partials_bytes(nkeys)) + al(sizeof(int64_t));
+}
 
 bool check_level(const geo_level* lv) {
     if (!lv) return false;
@@ -116,7 +121,7 @@ int geo_build_bins(const geo_mesh* mesh, const geo_level* lv, int32_t kind, int3
     p += al(sizeof(int32_t) * (size_t)out->cap);
     int32_t* cnt = reinterpret_cast<int32_t*>(p);
     p += al(sizeof(int32_t) * ((size_t)nkeys + 1));
-    int32_t* partials = reinterpret_cast<int32_t*>(p);
+    int64_t* partials = reinterpret_cast<int64_t*>(p);
     const DevMesh m = dev_mesh(mesh);
     const DevLevel d = dev_level(lv);
     int rc;
@@ -170,8 +175,8 @@ int geo_build_row_bins_levels(const geo_mesh* mesh, const int32_t n0[3], int32_t
     p += al(sizeof(int32_t) * (size_t)cap);
     int32_t* cnt = reinterpret_cast<int32_t*>(p);
     p += al(sizeof(int32_t) * ((size_t)nkeys + 1));
-    int32_t* partials = reinterpret_cast<int32_t*>(p);
-    p += al(geo_scan_partials_bytes(nkeys));
+    int64_t* partials = reinterpret_cast<int64_t*>(p);
+    p += al(rows_partials_bytes(nkeys));
     int64_t* d_pairs = reinterpret_cast<int64_t*>(p);
     lv.level = lmin;
     const DevMesh m = dev_mesh(mesh);
@@ -181,8 +186,9 @@ int geo_build_row_bins_levels(const geo_mesh* mesh, const int32_t n0[3], int32_t
     if ((rc = launch_check_mesh(m, d, d_stats, s)) != GEO_OK) return rc;
     if ((rc = launch_rows_levels(m, d, precision, rl, cnt, pairs, rank, cap, d_pairs, d_stats, s)) != GEO_OK)
         return rc;
-    for (int l = 0; l < nlev; l++)
-        if ((rc = geo_scan_exclusive(cnt + rl.base[l], out[l].off, out[l].nkeys, partials, s)) != GEO_OK) return rc;
+    ScanJobs jobs{};
+    for (int l = 0; l < nlev; l++) jobs.add(cnt + rl.base[l], out[l].off, out[l].nkeys, nullptr);
+    if ((rc = geo_scan_jobs(jobs, partials, s)) != GEO_OK) return rc;
     return launch_rows_levels_scatter(pairs, rank, cap, d_pairs, rl, s);
 }
 

@@ -1305,7 +1305,7 @@ int launch_cutlinks(const DevMesh& m, const DevLevel& d, const geo_bins* rows, c
     p += al(sizeof(int32_t) * (size_t)nb);
     int32_t* task_off = reinterpret_cast<int32_t*>(p);
     p += al(sizeof(int32_t) * ((size_t)nb + 1));
-    int32_t* partials = reinterpret_cast<int32_t*>(p);
+    int64_t* partials = reinterpret_cast<int64_t*>(p);
     p += al(geo_scan_partials_bytes(nb));
     uint32_t* ws_mask = reinterpret_cast<uint32_t*>(p);
     p += al(sizeof(uint32_t) * 64 * (size_t)nb);
@@ -1331,10 +1331,9 @@ int launch_cutlinks(const DevMesh& m, const DevLevel& d, const geo_bins* rows, c
     k_cl_mask<<<g, 64, 0, s>>>(d, rows->off, rows->val, rows->cap, links->off, lattice, wmask, link_mask ? 1 : 0,
                                blk_cnt, fixn);
     GEO_LAUNCH_CHECK();
-    // exact link count (the table's offsets are int32)
-    int rc = geo_sum_i32(blk_cnt, nb, d_nlinks, s);
+    // the link count is exact in 64 bits (the table's offsets are int32)
+    int rc = geo_scan_exclusive(blk_cnt, blk_off, nb, partials, s, d_nlinks);
     if (rc != GEO_OK) return rc;
-    if ((rc = geo_scan_exclusive(blk_cnt, blk_off, nb, partials, s)) != GEO_OK) return rc;
     // the block counts are free once scanned: their array holds the slots
     QSlots sl{nullptr, 0};
     if (d_stats) {

@@ -6,8 +6,8 @@
 // contiguous), -1 where a (cell, direction) has no link.
 //
 //   k_dn_flag    one thread per link: marks the block of each run of links
-//   scan         boundary-block index of every block
-//   k_dn_map     block map (-1 for blocks without links) and the count
+//   scan         boundary-block index of every block, and their count
+//   k_dn_map     block map (-1 for blocks without links)
 //   k_dn_starts  first link of every boundary block (the table is sorted by block)
 //   k_dn_write   one workgroup per boundary block: entries built in LDS, written once
 #include "geo_internal.h"
@@ -34,10 +34,9 @@ __global__ void k_dn_flag(int64_t n_links, const int32_t* link_cell, int64_t nb,
     }
 }
 
-__global__ void k_dn_map(int64_t nb, const int32_t* flag, const int32_t* pre, int32_t* block_map, int64_t* d_nbnd) {
+__global__ void k_dn_map(int64_t nb, const int32_t* flag, const int32_t* pre, int32_t* block_map) {
     for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += (int64_t)gridDim.x * blockDim.x)
         block_map[b] = flag[b] ? pre[b] : -1;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *d_nbnd = pre[nb];
 }
 
 // first link of each boundary block (the table is sorted by block), and
@@ -123,7 +122,7 @@ int launch_links_dense(int64_t nb, int64_t n_links, const int32_t* link_cell, co
     int32_t* flag = reinterpret_cast<int32_t*>(p);
     int32_t* pre = reinterpret_cast<int32_t*>(p + a);
     int32_t* start = reinterpret_cast<int32_t*>(p + 2 * a);
-    int32_t* partials = reinterpret_cast<int32_t*>(p + 3 * a);
+    int64_t* partials = reinterpret_cast<int64_t*>(p + 3 * a);
     int rc;
     if (nb == 0) return geo_fill_u64(reinterpret_cast<uint64_t*>(d_nbnd), 0, 1, s);
     if ((rc = geo_fill_i32(flag, 0, nb, s)) != GEO_OK) return rc;
@@ -132,8 +131,8 @@ int launch_links_dense(int64_t nb, int64_t n_links, const int32_t* link_cell, co
         k_dn_flag<<<grid_for(n_links, 256), 256, 0, s>>>(n_links, link_cell, nb, flag);
         GEO_LAUNCH_CHECK();
     }
-    if ((rc = geo_scan_exclusive(flag, pre, nb, partials, s)) != GEO_OK) return rc;
-    k_dn_map<<<grid_for(nb, 256), 256, 0, s>>>(nb, flag, pre, block_map, d_nbnd);
+    if ((rc = geo_scan_exclusive(flag, pre, nb, partials, s, d_nbnd)) != GEO_OK) return rc;
+    k_dn_map<<<grid_for(nb, 256), 256, 0, s>>>(nb, flag, pre, block_map);
     GEO_LAUNCH_CHECK();
     // start[] has nb + 1 entries, enough for any count of boundary blocks
     k_dn_starts<<<grid_for(n_links > 0 ? n_links : 1, 256), 256, 0, s>>>(n_links, link_cell, nb, block_map, d_nbnd,

@@ -283,12 +283,30 @@ void kt_record(int kernel, hipStream_t s, bool stop);
 
 // zero *one and p[0..n-1] (one launch)
 int geo_zero_counts(uint64_t* one, int32_t* p, int64_t n, hipStream_t s);
-int geo_scan_exclusive(const int32_t* in, int32_t* out, int64_t n, int32_t* partials,
-                       hipStream_t s);
+// exclusive scans of up to GEO_MAX_LEVELS arrays together: out[0..len-1] =
+// prefix sums of in, out[len] = total, *total (if given) = the total in 64
+// bits.  in and out must not overlap.  partials: geo_scan_partials_bytes of
+// each array's len, together.
+struct ScanJobs {
+    int n;
+    int tile0[GEO_MAX_LEVELS];
+    const int32_t* in[GEO_MAX_LEVELS];
+    int32_t* out[GEO_MAX_LEVELS];
+    int64_t len[GEO_MAX_LEVELS];
+    int64_t* total[GEO_MAX_LEVELS];
+    void add(const int32_t* i, int32_t* o, int64_t l, int64_t* t) {
+        in[n] = i;
+        out[n] = o;
+        len[n] = l;
+        total[n++] = t;
+    }
+};
+int geo_scan_jobs(ScanJobs& jobs, int64_t* partials, hipStream_t s);
+int geo_scan_exclusive(const int32_t* in, int32_t* out, int64_t n, int64_t* partials, hipStream_t s,
+                       int64_t* total = nullptr);
 size_t geo_scan_partials_bytes(int64_t n);
 int geo_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 int geo_fill_u64(uint64_t* p, uint64_t v, int64_t n, hipStream_t s);
-int geo_sum_i32(const int32_t* in, int64_t n, int64_t* out, hipStream_t s);
 
 // ROWS bins of several levels built together (levels lmin .. lmin+nlev-1):
 // keys of level lmin+l start at base[l] in the joint key space; count, off,

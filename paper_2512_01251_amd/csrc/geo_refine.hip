@@ -209,7 +209,7 @@ int launch_refine(const DevLevel& d, const uint64_t* solid, int n_prop, uint8_t*
     p += al(sizeof(int32_t) * (size_t)nb);
     int32_t* offs = reinterpret_cast<int32_t*>(p);
     p += al(sizeof(int32_t) * ((size_t)nb + 1));
-    int32_t* partials = reinterpret_cast<int32_t*>(p);
+    int64_t* partials = reinterpret_cast<int64_t*>(p);
 
     if (nb == 0) {
         int rc = geo_fill_u64(reinterpret_cast<uint64_t*>(d_nchild), 0, 1, s);

@@ -1,11 +1,38 @@
-// Device-wide exclusive scan of int32 counts and small fill kernels.
+// Device-wide exclusive scans of int32 counts and small fill kernels.
+//
+// Tiles of 4,096 values.  Two launches: the sums of all tiles, then the tiles
+// themselves, each adding up the sums of the tiles before it (at most a few
+// thousand words from L2) instead of waiting for a scan of the sums by one
+// workgroup.  Several arrays go through the same two launches, and where no
+// array has more than SCAN_DIRECT tiles one launch does: a tile then reads the
+// values before it again (at most 48 loads per thread, less than a launch).
+// Bound by launches below about 10^6 values and by HBM above (4 bytes read
+// twice, 4 written).  The scans of a step with
+// three launches of 2,048-value tiles per array, and now: 228 and 135 us on the
+// 7.2M-triangle star (22.3M row lines, four refinements, 5.8M blocks twice),
+// 99 and 43 us with 1,792 triangles, 39 and 18 us in one level of 64^3 cells.
 #include "geo_internal.h"
 
 namespace {
 
 constexpr int SCAN_THREADS = 256;
-constexpr int SCAN_ITEMS = 8;
+constexpr int SCAN_ITEMS = 16;
 constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
+constexpr int SCAN_DIRECT = 4;
+
+// sum of v over the workgroup (every thread calls it)
+__device__ __forceinline__ int64_t block_sum(int64_t v) {
+    __shared__ int64_t wsum[SCAN_THREADS / 64];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
+    __syncthreads();
+    int64_t t = 0;
+#pragma unroll
+    for (int i = 0; i < SCAN_THREADS / 64; i++) t += wsum[i];
+    __syncthreads();
+    return t;
+}
 
 // exclusive scan across the block (every thread calls it; the wave scan is
 // the shared data-parallel one); returns the block total in *total
@@ -26,62 +53,86 @@ __device__ __forceinline__ int block_excl_scan(int v, int* total) {
     return base + incl - v;
 }
 
-__global__ void __launch_bounds__(SCAN_THREADS) k_tile_sums(const int32_t* in, int64_t n, int32_t* partials) {
-    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
-    int s = 0;
-#pragma unroll
-    for (int i = 0; i < SCAN_ITEMS; i++) {
-        int64_t k = base + (int64_t)i * SCAN_THREADS + threadIdx.x;
-        if (k < n) s += in[k];
-    }
-    int tot;
-    block_excl_scan(s, &tot);
-    if (threadIdx.x == 0) partials[blockIdx.x] = tot;
+// job of a tile (uniform)
+__device__ __forceinline__ int tile_job(const ScanJobs& j, int tile) {
+    int q = 0;
+    for (int i = 1; i < j.n; i++) q += tile >= j.tile0[i] ? 1 : 0;
+    return q;
 }
 
-// single workgroup: exclusive scan of the tile sums, total at partials[ntiles]
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_partials(int32_t* partials, int64_t ntiles) {
-    int carry = 0;
-    for (int64_t c0 = 0; c0 < ntiles; c0 += SCAN_TILE) {
-        int v[SCAN_ITEMS];
-        int s = 0;
+// This thread's values of the tile in[0..n-1] (n may exceed the tile; zero
+// past n): value 4 i + c is that of position 1024 i + 4 t + c.  All loads are
+// in flight together: 16 bytes each where the tile is whole and aligned, else
+// single words with the index clamped instead of a branch per load.
+__device__ __forceinline__ void tile_load(const int32_t* in, int64_t n, int v[SCAN_ITEMS]) {
+    const int t = threadIdx.x;
+    if (n >= SCAN_TILE && (reinterpret_cast<uintptr_t>(in) & 15) == 0) {  // uniform
 #pragma unroll
-        for (int i = 0; i < SCAN_ITEMS; i++) {
-            int64_t k = c0 + (int64_t)threadIdx.x * SCAN_ITEMS + i;
-            v[i] = k < ntiles ? partials[k] : 0;
-            s += v[i];
+        for (int i = 0; i < SCAN_ITEMS / 4; i++) {
+            const int4 x = reinterpret_cast<const int4*>(in)[i * SCAN_THREADS + t];
+            v[4 * i] = x.x;
+            v[4 * i + 1] = x.y;
+            v[4 * i + 2] = x.z;
+            v[4 * i + 3] = x.w;
         }
-        int tot;
-        int ex = block_excl_scan(s, &tot) + carry;
-#pragma unroll
-        for (int i = 0; i < SCAN_ITEMS; i++) {
-            int64_t k = c0 + (int64_t)threadIdx.x * SCAN_ITEMS + i;
-            if (k < ntiles) partials[k] = ex;
-            ex += v[i];
-        }
-        carry += tot;
-        __syncthreads();
+        return;
     }
-    if (threadIdx.x == 0) partials[ntiles] = carry;
+    if (n <= 0) {  // uniform
+#pragma unroll
+        for (int k = 0; k < SCAN_ITEMS; k++) v[k] = 0;
+        return;
+    }
+    const int last = n < SCAN_TILE ? (int)n - 1 : SCAN_TILE - 1;
+#pragma unroll
+    for (int k = 0; k < SCAN_ITEMS; k++) {
+        const int j = 1024 * (k / 4) + 4 * t + (k & 3);
+        v[k] = in[j < last ? j : last];
+    }
+#pragma unroll
+    for (int k = 0; k < SCAN_ITEMS; k++)
+        if (1024 * (k / 4) + 4 * t + (k & 3) > last) v[k] = 0;
+}
+
+__device__ __forceinline__ int64_t tile_share(const int32_t* in, int64_t n) {
+    int v[SCAN_ITEMS];
+    tile_load(in, n, v);
+    int64_t s = 0;
+#pragma unroll
+    for (int k = 0; k < SCAN_ITEMS; k++) s += v[k];
+    return s;
+}
+
+__global__ void __launch_bounds__(SCAN_THREADS) k_tile_sums(ScanJobs jobs, int64_t* partials) {
+    const int q = tile_job(jobs, blockIdx.x);
+    const int64_t base = (int64_t)((int)blockIdx.x - jobs.tile0[q]) * SCAN_TILE;
+    const int64_t t = block_sum(tile_share(jobs.in[q] + base, jobs.len[q] - base));
+    if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
 // The tile passes through LDS so that global reads and writes are coalesced
 // (lane-consecutive), while each thread scans SCAN_ITEMS consecutive values.
 // The LDS rows are padded by one word per SCAN_ITEMS, so a thread's
-// consecutive items fall in distinct banks.
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_tiles(const int32_t* in, int32_t* out, int64_t n,
-                                                            const int32_t* partials, int64_t ntiles) {
+// consecutive items fall in distinct banks.  partials == nullptr: the values
+// of the tiles before are read themselves.
+__global__ void __launch_bounds__(SCAN_THREADS) k_scan_tiles(ScanJobs jobs, const int64_t* partials) {
     __shared__ int tile[SCAN_TILE + SCAN_TILE / SCAN_ITEMS];
-    const int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
+    const int q = tile_job(jobs, blockIdx.x);
+    const int first = jobs.tile0[q], ti = (int)blockIdx.x - first;
+    const int32_t* in = jobs.in[q];
+    int32_t* out = jobs.out[q];
+    const int64_t n = jobs.len[q], base = (int64_t)ti * SCAN_TILE;
     const int t = threadIdx.x;
     auto slot = [](int j) { return j + j / SCAN_ITEMS; };
-#pragma unroll
-    for (int i = 0; i < SCAN_ITEMS; i++) {
-        const int j = i * SCAN_THREADS + t;
-        tile[slot(j)] = base + j < n ? in[base + j] : 0;
-    }
-    __syncthreads();
     int v[SCAN_ITEMS];
+    tile_load(in + base, n - base, v);
+#pragma unroll
+    for (int k = 0; k < SCAN_ITEMS; k++) tile[slot(1024 * (k / 4) + 4 * t + (k & 3))] = v[k];
+    int64_t before = 0;
+    if (partials)
+        for (int i = t; i < ti; i += SCAN_THREADS) before += partials[first + i];
+    else
+        for (int i = 0; i < ti; i++) before += tile_share(in + (int64_t)i * SCAN_TILE, SCAN_TILE);
+    before = block_sum(before);  // (its barrier also covers the LDS tile)
     int s = 0;
 #pragma unroll
     for (int i = 0; i < SCAN_ITEMS; i++) {
@@ -89,19 +140,38 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_tiles(const int32_t* in, 
         s += v[i];
     }
     int tot;
-    int ex = block_excl_scan(s, &tot) + partials[blockIdx.x];
+    int ex = block_excl_scan(s, &tot) + (int)before;
 #pragma unroll
     for (int i = 0; i < SCAN_ITEMS; i++) {
         tile[slot(t * SCAN_ITEMS + i)] = ex;
         ex += v[i];
     }
     __syncthreads();
+    if (base + SCAN_TILE <= n && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {  // uniform
 #pragma unroll
-    for (int i = 0; i < SCAN_ITEMS; i++) {
-        const int j = i * SCAN_THREADS + t;
-        if (base + j < n) out[base + j] = tile[slot(j)];
+        for (int i = 0; i < SCAN_ITEMS / 4; i++) {
+            const int j = slot(1024 * i + 4 * t);  // four positions of one group
+            reinterpret_cast<int4*>(out + base)[i * SCAN_THREADS + t] =
+                make_int4(tile[j], tile[j + 1], tile[j + 2], tile[j + 3]);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < SCAN_ITEMS; i++) {
+            const int j = i * SCAN_THREADS + t;
+            if (base + j < n) out[base + j] = tile[slot(j)];
+        }
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = partials[ntiles];
+    if (base + SCAN_TILE >= n) {  // the array's last tile: totals, exact in 64 bits
+        // the tile's own values summed in 64 bits (their int32 sum may wrap)
+        int64_t own = 0;
+#pragma unroll
+        for (int i = 0; i < SCAN_ITEMS; i++) own += v[i];
+        own = block_sum(own);
+        if (t == 0) {
+            out[n] = (int32_t)(before + own);
+            if (jobs.total[q]) *jobs.total[q] = before + own;
+        }
+    }
 }
 
 __global__ void k_fill_i32(int32_t* p, int32_t v, int64_t n) {
@@ -121,22 +191,6 @@ __global__ void k_fill_u64(uint64_t* p, uint64_t v, int64_t n) {
         p[i] = v;
 }
 
-// *out += sum of in[0..n-1] in 64-bit (one atomic per workgroup of 256)
-__global__ void __launch_bounds__(256) k_sum_i32(const int32_t* in, int64_t n, unsigned long long* out) {
-    __shared__ unsigned long long part[4];
-    unsigned long long acc = 0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        acc += (unsigned long long)(uint32_t)in[i];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned long long t = part[0] + part[1] + part[2] + part[3];
-        if (t) atomicAdd(out, t);
-    }
-}
-
 inline unsigned grid_for(int64_t n, int threads) {
     int64_t g = (n + threads - 1) / threads;
     if (g > 65536) g = 65536;
@@ -147,24 +201,30 @@ inline unsigned grid_for(int64_t n, int threads) {
 }  // namespace
 
 size_t geo_scan_partials_bytes(int64_t n) {
-    int64_t ntiles = (n + SCAN_TILE - 1) / SCAN_TILE;
-    return sizeof(int32_t) * (size_t)(ntiles + 1);
+    const int64_t ntiles = (n + SCAN_TILE - 1) / SCAN_TILE;
+    return sizeof(int64_t) * (size_t)(ntiles > 0 ? ntiles : 1);
 }
 
-// out[0..n-1] = exclusive prefix sums of in, out[n] = total.  in and out must
-// not overlap.  partials: geo_scan_partials_bytes(n) bytes.
-int geo_scan_exclusive(const int32_t* in, int32_t* out, int64_t n, int32_t* partials, hipStream_t s) {
-    int64_t ntiles = (n + SCAN_TILE - 1) / SCAN_TILE;
-    if (ntiles == 0) {
-        k_fill_i32<<<1, 64, 0, s>>>(out, 0, 1);
-        GEO_LAUNCH_CHECK();
-        return GEO_OK;
+int geo_scan_jobs(ScanJobs& j, int64_t* partials, hipStream_t s) {
+    int64_t tiles = 0, most = 0;
+    for (int q = 0; q < j.n; q++) {
+        const int64_t nt = j.len[q] > 0 ? (j.len[q] + SCAN_TILE - 1) / SCAN_TILE : 1;
+        j.tile0[q] = (int)tiles;
+        tiles += nt;
+        most = nt > most ? nt : most;
     }
-    k_tile_sums<<<(unsigned)ntiles, SCAN_THREADS, 0, s>>>(in, n, partials);
-    k_scan_partials<<<1, SCAN_THREADS, 0, s>>>(partials, ntiles);
-    k_scan_tiles<<<(unsigned)ntiles, SCAN_THREADS, 0, s>>>(in, out, n, partials, ntiles);
+    if (tiles == 0) return GEO_OK;
+    const bool direct = most <= SCAN_DIRECT;
+    if (!direct) k_tile_sums<<<(unsigned)tiles, SCAN_THREADS, 0, s>>>(j, partials);
+    k_scan_tiles<<<(unsigned)tiles, SCAN_THREADS, 0, s>>>(j, direct ? nullptr : partials);
     GEO_LAUNCH_CHECK();
     return GEO_OK;
+}
+
+int geo_scan_exclusive(const int32_t* in, int32_t* out, int64_t n, int64_t* partials, hipStream_t s, int64_t* total) {
+    ScanJobs j{};
+    j.add(in, out, n, total);
+    return geo_scan_jobs(j, partials, s);
 }
 
 int geo_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s) {
@@ -183,17 +243,6 @@ int geo_zero_counts(uint64_t* one, int32_t* p, int64_t n, hipStream_t s) {
 int geo_fill_u64(uint64_t* p, uint64_t v, int64_t n, hipStream_t s) {
     if (n <= 0) return GEO_OK;
     k_fill_u64<<<grid_for(n, 256), 256, 0, s>>>(p, v, n);
-    GEO_LAUNCH_CHECK();
-    return GEO_OK;
-}
-
-// *out = sum of the non-negative in[0..n-1], exact in 64 bits
-int geo_sum_i32(const int32_t* in, int64_t n, int64_t* out, hipStream_t s) {
-    int rc = geo_fill_u64(reinterpret_cast<uint64_t*>(out), 0, 1, s);
-    if (rc != GEO_OK || n <= 0) return rc;
-    int64_t g = (n + 255) / 256;
-    if (g > 256) g = 256;
-    k_sum_i32<<<(unsigned)g, 256, 0, s>>>(in, n, reinterpret_cast<unsigned long long*>(out));
     GEO_LAUNCH_CHECK();
     return GEO_OK;
 }
