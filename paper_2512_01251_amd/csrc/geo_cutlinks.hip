@@ -6,10 +6,11 @@
 //              bins of 36 row lines, so a neighbour centre is classified even
 //              where its block does not exist; lane t forms the link mask of
 //              cell t.  The masks are kept (the caller's link_mask, else the
-//              workspace) and the block's link count is reduced.
-//  scans       block counts -> table offsets, so the table is laid out in
+//              workspace); the block's link count and its number of tasks
+//              are formed with them.
+//  scan        block counts -> table offsets, so the table is laid out in
 //              the order (block, t, k) without atomics; tasks per block ->
-//              task offsets.
+//              task offsets, in the same launches.
 //  k_cl_multi  blocks whose candidates span several chunks of 64: the 64-bit
 //              nearest-hit keys of their links are set to "no hit" before
 //              k_cl_q and turned into q and triangle after it.
@@ -168,12 +169,25 @@ __device__ __forceinline__ void block_link_mask2(const DevLevel& d, const int32_
     mb = ((nb >> 13) & 1u) ? 0u : (nb & dirs);
 }
 
+// candidates of block b that lie within the LINKS bins' capacity
+__device__ __forceinline__ int candidates(const int32_t* loff, int64_t lcap, int64_t b) {
+    int64_t c0 = loff[b], c1 = loff[b + 1];
+    if (c1 > lcap) c1 = lcap;
+    if (c0 < 0) c0 = 0;
+    return c1 > c0 ? (int)(c1 - c0) : 0;
+}
+
+// q-kernel tasks of a block with n links and nc candidates
+__device__ __forceinline__ int block_tasks(int n, int nc) {
+    return n > 0 ? ((n + 63) / 64) * (nc > CL_CAND ? (nc + CL_CAND - 1) / CL_CAND : 1) : 0;
+}
+
 __global__ void __launch_bounds__(64) k_cl_mask(DevLevel d, const int32_t* off, const int32_t* val, int64_t cap,
-                                                const int32_t* loff, int lattice, uint32_t* wmask, int zero_fill,
-                                                int32_t* blk_cnt, int32_t* fixn) {
+                                                const int32_t* loff, int64_t lcap, int lattice, uint32_t* wmask,
+                                                int zero_fill, int32_t* blk_cnt, int32_t* ntask, int32_t* fixn) {
     __shared__ unsigned halo[72];
     // the exact pass's queue counters start at zero (read from the next launch on)
-    if (blockIdx.x == 0 && threadIdx.x < 3) fixn[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 2) fixn[threadIdx.x] = 0;
     const uint32_t dirs = lattice_dirs(lattice);
     const int lane = threadIdx.x;
     const int64_t nchunks = (d.nblocks + 63) / 64;
@@ -186,7 +200,8 @@ __global__ void __launch_bounds__(64) k_cl_mask(DevLevel d, const int32_t* off, 
         // a cut link crosses the surface inside the block's reach, so a block
         // without candidate triangles has none
         const bool has = inb && loff[bl] != loff[bl + 1];
-        if (inb && !has) blk_cnt[bl] = 0;
+        const int nc = has ? candidates(loff, lcap, bl) : 0;
+        int nlinks = 0;  // links of this lane's block
         unsigned long long todo = __ballot(has);
         while (todo) {  // uniform
             const int i = __ffsll(todo) - 1;
@@ -207,10 +222,12 @@ __global__ void __launch_bounds__(64) k_cl_mask(DevLevel d, const int32_t* off, 
                 ca += __shfl_xor(ca, o, 64);
                 cb += __shfl_xor(cb, o, 64);
             }
-            if (lane == 0) {
-                blk_cnt[ba] = ca;
-                if (bb >= 0) blk_cnt[bb] = cb;
-            }
+            if (lane == i) nlinks = ca;
+            if (lane == j) nlinks = cb;
+        }
+        if (inb) {  // counts and tasks of the chunk's blocks, written together
+            blk_cnt[bl] = nlinks;
+            ntask[bl] = block_tasks(nlinks, nc);
         }
         if (zero_fill) {  // the caller's mask: every block is written
             unsigned long long empty = __ballot(inb && !has);
@@ -777,65 +794,43 @@ __global__ void __launch_bounds__(64) k_cl_stats(QSlots sl, const int32_t* ntask
     fold_slots(sl, *ntasks, stats);
 }
 
-// tasks per block: ceil(links / 64) x ceil(candidates / 64); blocks with
-// links and more than one chunk of candidates are listed (in no particular
-// order) for k_cl_multi
-__global__ void __launch_bounds__(256) k_cl_ntask(int64_t nb, const int32_t* blk_off, const int32_t* loff,
-                                                  int64_t lcap, int32_t* ntask, int32_t* mlist, int32_t* mcount,
-                                                  QSlots sl) {
-    __shared__ int wg_count, wg_base;
-    const int lane = threadIdx.x & 63;
-    if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < sl.n * QSLOT_WORDS; i += blockDim.x) sl.p[i] = 0ull;
-    for (int64_t b0 = (int64_t)blockIdx.x * blockDim.x; b0 < nb; b0 += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t b = b0 + threadIdx.x;
-        bool multi = false;
-        if (b < nb) {
-            const int n = blk_off[b + 1] - blk_off[b];
-            int64_t c0 = loff[b], c1 = loff[b + 1];
-            if (c1 > lcap) c1 = lcap;
-            if (c0 < 0) c0 = 0;
-            const int nc = c1 > c0 ? (int)(c1 - c0) : 0;
-            ntask[b] = n > 0 ? ((n + 63) / 64) * (nc > 0 ? (nc + CL_CAND - 1) / CL_CAND : 1) : 0;
-            multi = n > 0 && nc > CL_CAND;
+// Blocks whose candidates span several chunks (their tasks merge into keys):
+// mode 0 sets the keys of their links to "no hit" and clears the queue marks,
+// mode 1 turns the keys into q and triangle.  Chunks of 64 blocks, one
+// coalesced read of their offsets per wave; then one wave step per such block,
+// lanes over its links (28 and 74 us on the 7.2M-triangle star; a list of
+// those blocks, made by a pass of its own, took 44 + 13 + 35 us; numbering the
+// links of a chunk's blocks through took 47 and 69 us).  Mode 0 also clears
+// the statistics slots.
+__global__ void __launch_bounds__(64) k_cl_multi(int64_t nb, const int32_t* blk_off, const int32_t* loff, int64_t lcap,
+                                                 int64_t cap, int mode, unsigned long long* keys, int32_t* mark,
+                                                 float* link_q, int32_t* link_tri, QSlots sl) {
+    const int lane = threadIdx.x;
+    if (mode == 0 && blockIdx.x == 0)
+        for (int i = lane; i < sl.n * QSLOT_WORDS; i += 64) sl.p[i] = 0ull;
+    for (int64_t b0 = (int64_t)blockIdx.x * 64; b0 < nb; b0 += (int64_t)gridDim.x * 64) {
+        const int64_t b = b0 + lane;
+        int p0 = 0, p1 = 0;
+        if (b < nb && candidates(loff, lcap, b) > CL_CAND) {
+            p0 = blk_off[b];
+            p1 = blk_off[b + 1];
         }
-        // list slots: one LDS reservation per wave, one global one per
-        // workgroup (same-address atomics serialise)
-        if (threadIdx.x == 0) wg_count = 0;
-        __syncthreads();
-        const unsigned long long bal = __ballot(multi);
-        int wofs = 0;
-        if (bal && lane == 0) wofs = atomicAdd(&wg_count, __popcll(bal));
-        wofs = __shfl(wofs, 0, 64);
-        __syncthreads();
-        if (threadIdx.x == 0) wg_base = wg_count ? atomicAdd(mcount, wg_count) : 0;
-        __syncthreads();
-        if (multi) mlist[wg_base + wofs + __popcll(bal & ((1ull << lane) - 1ull))] = (int32_t)b;
-        __syncthreads();
-    }
-}
-
-// Blocks whose candidates span several chunks (their tasks merge into keys),
-// from the list of k_cl_ntask: mode 0 sets the keys of their links to "no
-// hit" and clears the queue marks, mode 1 turns the keys into q and triangle.
-// One wave per listed block, lanes over its links.
-__global__ void k_cl_multi(const int32_t* mlist, const int32_t* mcount, const int32_t* blk_off, int64_t cap,
-                           int mode, unsigned long long* keys, int32_t* mark, float* link_q, int32_t* link_tri) {
-    const int lane = threadIdx.x & 63;
-    const int64_t nw = ((int64_t)gridDim.x * blockDim.x) >> 6;
-    const int64_t nm = *mcount;
-    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; i < nm; i += nw) {
-        const int64_t b = mlist[i];
-        int64_t p1 = blk_off[b + 1];
-        if (p1 > cap) p1 = cap;
-        for (int64_t p = blk_off[b] + lane; p < p1; p += 64) {
-            if (mode == 0) {
-                keys[p] = KEY_MISS;
-                mark[p] = 0;
-            } else {
-                const unsigned long long k = keys[p];
-                link_q[p] = key_q(k);
-                link_tri[p] = key_tri(k);
+        unsigned long long todo = __ballot(p1 > p0);
+        while (todo) {  // uniform
+            const int i = __ffsll(todo) - 1;
+            todo &= todo - 1;
+            const int64_t q0 = __shfl(p0, i, 64);
+            int64_t q1 = __shfl(p1, i, 64);
+            if (q1 > cap) q1 = cap;
+            for (int64_t p = q0 + lane; p < q1; p += 64) {
+                if (mode == 0) {
+                    keys[p] = KEY_MISS;
+                    mark[p] = 0;
+                } else {
+                    const unsigned long long k = keys[p];
+                    link_q[p] = key_q(k);
+                    link_tri[p] = key_tri(k);
+                }
             }
         }
     }
@@ -1284,9 +1279,9 @@ inline int64_t pair_cap(int64_t cap) { return cap < 1 ? 1 : (cap < (1 << 22) ? c
 size_t geo_cutlinks_ws_bytes(int64_t nb, int64_t cap) {
     const size_t c = (size_t)(cap > 0 ? cap : 1);
     return 2 * al(sizeof(int32_t) * (size_t)nb) + 2 * al(sizeof(int32_t) * ((size_t)nb + 1)) +
-           al(geo_scan_partials_bytes(nb)) + al(sizeof(uint32_t) * 64 * (size_t)nb) +
-           al(sizeof(unsigned long long) * c) + 2 * al(sizeof(int32_t) * c) + al(3 * sizeof(int32_t)) +
-           al(sizeof(int2) * (size_t)pair_cap(cap)) + al(sizeof(int32_t) * (size_t)nb);
+           al(2 * geo_scan_partials_bytes(nb)) + al(sizeof(uint32_t) * 64 * (size_t)nb) +
+           al(sizeof(unsigned long long) * c) + 2 * al(sizeof(int32_t) * c) + al(2 * sizeof(int32_t)) +
+           al(sizeof(int2) * (size_t)pair_cap(cap));
 }
 
 int launch_cutlinks(const DevMesh& m, const DevLevel& d, const geo_bins* rows, const geo_bins* links, int lattice,
@@ -1306,7 +1301,7 @@ int launch_cutlinks(const DevMesh& m, const DevLevel& d, const geo_bins* rows, c
     int32_t* task_off = reinterpret_cast<int32_t*>(p);
     p += al(sizeof(int32_t) * ((size_t)nb + 1));
     int64_t* partials = reinterpret_cast<int64_t*>(p);
-    p += al(geo_scan_partials_bytes(nb));
+    p += al(2 * geo_scan_partials_bytes(nb));
     uint32_t* ws_mask = reinterpret_cast<uint32_t*>(p);
     p += al(sizeof(uint32_t) * 64 * (size_t)nb);
     unsigned long long* keys = reinterpret_cast<unsigned long long*>(p);
@@ -1315,24 +1310,24 @@ int launch_cutlinks(const DevMesh& m, const DevLevel& d, const geo_bins* rows, c
     p += al(sizeof(int32_t) * c);
     int32_t* fixq = reinterpret_cast<int32_t*>(p);
     p += al(sizeof(int32_t) * c);
-    // fixn[0]: queued links, fixn[1]: queued pairs, fixn[2]: listed multi-chunk blocks
+    // fixn[0]: queued links, fixn[1]: queued pairs
     int32_t* fixn = reinterpret_cast<int32_t*>(p);
     int32_t* pairn = fixn + 1;
-    int32_t* mcount = fixn + 2;
-    p += al(3 * sizeof(int32_t));
+    p += al(2 * sizeof(int32_t));
     const int64_t pcap = pair_cap(cap);
     int2* pairq = reinterpret_cast<int2*>(p);
-    p += al(sizeof(int2) * (size_t)pcap);
-    int32_t* mlist = reinterpret_cast<int32_t*>(p);
     if (nb == 0) return geo_fill_u64(reinterpret_cast<uint64_t*>(d_nlinks), 0, 1, s);
     uint32_t* wmask = link_mask ? link_mask : ws_mask;
     const int64_t nchunk = (nb + 63) / 64;
     const unsigned g = (unsigned)(nchunk < 32768 ? nchunk : 32768);
-    k_cl_mask<<<g, 64, 0, s>>>(d, rows->off, rows->val, rows->cap, links->off, lattice, wmask, link_mask ? 1 : 0,
-                               blk_cnt, fixn);
+    k_cl_mask<<<g, 64, 0, s>>>(d, rows->off, rows->val, rows->cap, links->off, links->cap, lattice, wmask,
+                               link_mask ? 1 : 0, blk_cnt, ntask, fixn);
     GEO_LAUNCH_CHECK();
     // the link count is exact in 64 bits (the table's offsets are int32)
-    int rc = geo_scan_exclusive(blk_cnt, blk_off, nb, partials, s, d_nlinks);
+    ScanJobs jobs{};
+    jobs.add(blk_cnt, blk_off, nb, d_nlinks);
+    jobs.add(ntask, task_off, nb, nullptr);
+    int rc = geo_scan_jobs(jobs, partials, s);
     if (rc != GEO_OK) return rc;
     // the block counts are free once scanned: their array holds the slots
     QSlots sl{nullptr, 0};
@@ -1341,14 +1336,8 @@ int launch_cutlinks(const DevMesh& m, const DevLevel& d, const geo_bins* rows, c
         sl.p = reinterpret_cast<unsigned long long*>(blk_cnt);
         sl.n = fit < QSLOT_MAX ? (int)fit : QSLOT_MAX;
     }
-    const unsigned gb = (unsigned)((nb + 255) / 256 < 65536 ? (nb + 255) / 256 : 65536);
-    k_cl_ntask<<<gb, 256, 0, s>>>(nb, blk_off, links->off, links->cap, ntask, mlist, mcount, sl);
+    k_cl_multi<<<g, 64, 0, s>>>(nb, blk_off, links->off, links->cap, cap, 0, keys, mark, link_q, link_tri, sl);
     GEO_LAUNCH_CHECK();
-    if ((rc = geo_scan_exclusive(ntask, task_off, nb, partials, s)) != GEO_OK) return rc;
-    if (cap > 0) {
-        k_cl_multi<<<4096, 256, 0, s>>>(mlist, mcount, blk_off, cap, 0, keys, mark, link_q, link_tri);
-        GEO_LAUNCH_CHECK();
-    }
     // tasks are split into one contiguous range per workgroup; finer ranges
     // balance better; empty ranges exit at once
     const unsigned gq = 65536;
@@ -1359,7 +1348,7 @@ int launch_cutlinks(const DevMesh& m, const DevLevel& d, const geo_bins* rows, c
     kt_record(GEO_KT_CUTLINKS_Q, s, true);
     GEO_LAUNCH_CHECK();
     if (cap > 0) {
-        k_cl_multi<<<4096, 256, 0, s>>>(mlist, mcount, blk_off, cap, 1, keys, mark, link_q, link_tri);
+        k_cl_multi<<<g, 64, 0, s>>>(nb, blk_off, links->off, links->cap, cap, 1, keys, mark, link_q, link_tri, sl);
         k_cl_fix_pairs<<<256, 256, 0, s>>>(m, d, link_cell, link_dir, pairq, pairn, pcap, cap, keys, d_stats);
         k_cl_fix<<<4096, 64, 0, s>>>(m, d, links->off, links->val, links->cap, link_cell, link_dir, fixq, fixn, mark,
                                      cap, keys, link_q, link_tri, sl, task_off + nb, d_stats);
