@@ -20,8 +20,14 @@ size_t bins_ws_bytes(int64_t nkeys, int64_t cap) {
 // each level's scan may end in a tile of its own
 size_t rows_partials_bytes(int64_t nkeys) { return geo_scan_partials_bytes(nkeys) + sizeof(int64_t) * GEO_MAX_LEVELS; }
 
-size_t rows_levels_ws_bytes(int64_t nkeys, int64_t cap) {
-    return bins_ws_bytes(nkeys, cap) + al(rows_partials_bytes(nkeys)) + al(sizeof(int64_t));
+// the ROWS builds: staged pairs, ranks, key counts and scan partials as for
+// the LINKS bins, the list of large items' pieces, the statistics slots, the
+// two counters
+size_t rows_ws_bytes(int64_t nkeys, int64_t cap) {
+    const size_t c = (size_t)(cap > 0 ? cap : 0);
+    return al(sizeof(int2) * c) + al(sizeof(int32_t) * c) + al(sizeof(int32_t) * ((size_t)nkeys + 1)) +
+           al(rows_partials_bytes(nkeys)) + al(sizeof(int4) * ROW_LIST_CAP) +
+           al(sizeof(unsigned long long) * ROW_SLOTS * ROW_SLOT_WORDS) + al(2 * sizeof(int64_t));
 }
 
 bool check_level(const geo_level* lv) {
@@ -69,8 +75,8 @@ size_t geo_workspace_size(int32_t call, int64_t nkeys, int64_t cap) {
     if (nkeys < 0) return 0;
     switch (call) {
         case GEO_CALL_BINS_ROWS:
+        case GEO_CALL_BINS_ROWS_LEVELS: return rows_ws_bytes(nkeys, cap);
         case GEO_CALL_BINS_LINKS: return bins_ws_bytes(nkeys, cap);
-        case GEO_CALL_BINS_ROWS_LEVELS: return rows_levels_ws_bytes(nkeys, cap);
         case GEO_CALL_REFINE: return geo_refine_ws_bytes(nkeys);
         case GEO_CALL_CUTLINKS: return geo_cutlinks_ws_bytes(nkeys, cap);
         case GEO_CALL_LINKS_DENSE: return geo_dense_ws_bytes(nkeys);
@@ -112,6 +118,8 @@ int geo_build_bins(const geo_mesh* mesh, const geo_level* lv, int32_t kind, int3
     const int64_t nkeys = kind == GEO_BINS_ROWS ? row_keys(lv) : (int64_t)lv->nblocks;
     if (!check_bins(out, kind, nkeys)) return GEO_ERR_ARG;
     if (nkeys + 1 > INT32_MAX) return GEO_ERR_ARG;
+    if (kind == GEO_BINS_ROWS)  // the joint build of one level
+        return geo_build_row_bins_levels(mesh, lv->n0, lv->level, 1, precision, out, d_stats, ws, ws_bytes, stream);
     if (ws_bytes < bins_ws_bytes(nkeys, out->cap) || (!ws && ws_bytes)) return GEO_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     char* p = static_cast<char*>(ws);
@@ -127,11 +135,7 @@ int geo_build_bins(const geo_mesh* mesh, const geo_level* lv, int32_t kind, int3
     int rc;
     if ((rc = geo_zero_counts(reinterpret_cast<uint64_t*>(out->d_count), cnt, nkeys, s)) != GEO_OK) return rc;
     if ((rc = launch_check_mesh(m, d, d_stats, s)) != GEO_OK) return rc;
-    if (kind == GEO_BINS_ROWS)
-        rc = launch_rows_pass1(m, d, precision, cnt, pairs, rank, out->cap, out->d_count, d_stats, s);
-    else
-        rc = launch_links_pass1(m, d, cnt, pairs, rank, out->cap, out->d_count, s);
-    if (rc != GEO_OK) return rc;
+    if ((rc = launch_links_pass1(m, d, cnt, pairs, rank, out->cap, out->d_count, s)) != GEO_OK) return rc;
     if ((rc = geo_scan_exclusive(cnt, out->off, nkeys, partials, s)) != GEO_OK) return rc;
     return launch_bins_scatter(pairs, rank, out->cap, out->d_count, out->off, out->val, s);
 }
@@ -159,37 +163,44 @@ int geo_build_row_bins_levels(const geo_mesh* mesh, const int32_t n0[3], int32_t
         rl.base[l] = (int)nkeys;
         nkeys += nk;
         if (nkeys + 1 > INT32_MAX) return GEO_ERR_ARG;
-        rl.count[l] = reinterpret_cast<unsigned long long*>(out[l].d_count);
         rl.off[l] = out[l].off;
         rl.val[l] = out[l].val;
         rl.cap[l] = out[l].cap;
         cap += out[l].cap;
     }
     for (int l = nlev; l <= GEO_MAX_LEVELS; l++) rl.base[l] = (int)nkeys;
-    if (ws_bytes < rows_levels_ws_bytes(nkeys, cap) || (!ws && ws_bytes)) return GEO_ERR_WORKSPACE;
+    if (ws_bytes < rows_ws_bytes(nkeys, cap) || (!ws && ws_bytes)) return GEO_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
+    RowWork w{};
     char* p = static_cast<char*>(ws);
-    int2* pairs = reinterpret_cast<int2*>(p);
+    w.pairs = reinterpret_cast<int2*>(p);
     p += al(sizeof(int2) * (size_t)cap);
-    int32_t* rank = reinterpret_cast<int32_t*>(p);
+    w.rank = reinterpret_cast<int32_t*>(p);
     p += al(sizeof(int32_t) * (size_t)cap);
-    int32_t* cnt = reinterpret_cast<int32_t*>(p);
+    w.cnt = reinterpret_cast<int32_t*>(p);
     p += al(sizeof(int32_t) * ((size_t)nkeys + 1));
     int64_t* partials = reinterpret_cast<int64_t*>(p);
     p += al(rows_partials_bytes(nkeys));
-    int64_t* d_pairs = reinterpret_cast<int64_t*>(p);
+    w.list = reinterpret_cast<int4*>(p);
+    p += al(sizeof(int4) * ROW_LIST_CAP);
+    w.slots = d_stats ? reinterpret_cast<unsigned long long*>(p) : nullptr;
+    p += al(sizeof(unsigned long long) * ROW_SLOTS * ROW_SLOT_WORDS);
+    w.d_pairs = reinterpret_cast<int64_t*>(p);
+    w.list_n = reinterpret_cast<int*>(w.d_pairs + 1);
+    w.cap = cap;
     lv.level = lmin;
     const DevMesh m = dev_mesh(mesh);
     const DevLevel d = dev_level(&lv);
     int rc;
-    if ((rc = launch_rows_levels_zero(rl, d_pairs, cnt, nkeys, s)) != GEO_OK) return rc;
+    if ((rc = launch_rows_levels_zero(w, nkeys, s)) != GEO_OK) return rc;
     if ((rc = launch_check_mesh(m, d, d_stats, s)) != GEO_OK) return rc;
-    if ((rc = launch_rows_levels(m, d, precision, rl, cnt, pairs, rank, cap, d_pairs, d_stats, s)) != GEO_OK)
-        return rc;
+    if ((rc = launch_rows_levels(m, d, precision, rl, w, s)) != GEO_OK) return rc;
+    // the counts of every key are complete whatever fits the pair array, so
+    // the scans' totals are the entries needed
     ScanJobs jobs{};
-    for (int l = 0; l < nlev; l++) jobs.add(cnt + rl.base[l], out[l].off, out[l].nkeys, nullptr);
+    for (int l = 0; l < nlev; l++) jobs.add(w.cnt + rl.base[l], out[l].off, out[l].nkeys, out[l].d_count);
     if ((rc = geo_scan_jobs(jobs, partials, s)) != GEO_OK) return rc;
-    return launch_rows_levels_scatter(pairs, rank, cap, d_pairs, rl, s);
+    return launch_rows_levels_scatter(rl, w, d_stats, s);
 }
 
 int geo_voxelize(const geo_level* lv, const geo_bins* rows, uint64_t* solid, geo_stream_t stream) {

@@ -1,10 +1,9 @@
 // Spatial binning on gfx950 (Methodology, "Spatial Binning").
 //
 // ROWS bins hold, per x-row line of a level, the exact surface events along
-// the line (parity crossings and on-surface intervals); they are built
-// triangle-parallel: each triangle visits the row lines inside its yz
-// bounding box, decides exactly whether the line meets it, and where along
-// the line.  LINKS bins hold, per block, the triangles overlapping the block
+// the line (parity crossings and on-surface intervals); they are built from
+// the triangles: for each row line inside a triangle's yz bounding box it is
+// decided exactly whether the line meets it, and where along the line.  LINKS bins hold, per block, the triangles overlapping the block
 // box widened by one cell (the widened bin cover of Algorithm 2).
 //
 // Both are counting sorts without a global sort: pass 1 appends (key, value)
@@ -137,7 +136,7 @@ struct RowTri {
     R v[3][3];    // local coordinates (level-L cell units, centres at integers)
     R delta;      // bound on |v - exact| (0 when exact)
     int o[3];     // integer origin of the local frame
-    int idx[3];   // vertex ids in local order (b and c swapped when the yz area is negative)
+    int tri;      // triangle id; bit 31: b and c swapped (the yz area is negative)
 };
 
 // exact scaled coordinate X = v 2^L - 1/2 of vertex vid, axis a, in float64
@@ -148,13 +147,29 @@ __device__ __forceinline__ double scaled64(const DevMesh& m, int vid, int a, dou
 // exact float64 local coordinates of T (reloaded from memory)
 template <typename R>
 __device__ __forceinline__ void local64(const DevMesh& m, const RowTri<R>& T, double s, double v[3][3]) {
-    for (int i = 0; i < 3; i++)
-        for (int a = 0; a < 3; a++) v[i][a] = scaled64(m, T.idx[i], a, s) - (double)T.o[a];
+    const int64_t t = 3 * (int64_t)(T.tri & 0x7fffffff);
+    const int sw = T.tri < 0 ? 1 : 0;
+    for (int i = 0; i < 3; i++) {
+        const int vid = m.tris[t + (i == 0 ? 0 : (i - 1) ^ sw) + (i == 0 ? 0 : 1)];
+        for (int a = 0; a < 3; a++) v[i][a] = scaled64(m, vid, a, s) - (double)T.o[a];
+    }
 }
 
 struct Stats {
     unsigned fb = 0, ex = 0;
 };
+
+// the rows pass counts into slots of 128 bytes, like the q kernel: atomics of
+// all its workgroups on the caller's counters complete one every 8.7 ns
+template <typename R>
+__device__ __forceinline__ void row_stats(unsigned long long* slots, const Stats& st) {
+    if (!slots) return;
+    unsigned long long* s = slots + (blockIdx.x % ROW_SLOTS) * ROW_SLOT_WORDS;
+    const unsigned fb = (unsigned)wave_incl_scan((int)st.fb), ex = (unsigned)wave_incl_scan((int)st.ex);
+    if (threadIdx.x != 63) return;
+    if (std::is_same<R, float>::value && fb) atomicAdd(&s[0], (unsigned long long)fb);
+    if (ex) atomicAdd(&s[1], (unsigned long long)ex);
+}
 
 // exact sign of orient2d in the (y,z) plane of local points p, q and (py, pz)
 template <typename R>
@@ -256,27 +271,35 @@ __device__ __forceinline__ void tri_load(const DevMesh& m, int64_t t, TriLoad& t
         for (int a = 0; a < 3; a++) tl.x[i][a] = load_coord(m, tl.id[i], a);
 }
 
-// Set up the local frame of level L.  Returns false for triangles with no line.
+// Row lines of level L inside the triangle's yz box: [jlo, jhi] x [klo, khi]
+// (empty when the low end is above the high one).  X: scaled coordinates.
+struct RowBox {
+    int jlo, jhi, klo, khi;
+    __device__ __forceinline__ bool any() const { return jlo <= jhi && klo <= khi; }
+};
+__device__ __forceinline__ RowBox row_box(const TriLoad& tl, double s, int ny, int nz) {
+    double y[3], z[3];  // the same float64 operations as scaled64
+    for (int i = 0; i < 3; i++) {
+        y[i] = tl.x[i][1] * s - 0.5;
+        z[i] = tl.x[i][2] * s - 0.5;
+    }
+    const double ymin = fmin(y[0], fmin(y[1], y[2])), ymax = fmax(y[0], fmax(y[1], y[2]));
+    const double zmin = fmin(z[0], fmin(z[1], z[2])), zmax = fmax(z[0], fmax(z[1], z[2]));
+    return {(int)fmax(ceil(ymin), 0.0), (int)fmin(floor(ymax), (double)(ny - 1)), (int)fmax(ceil(zmin), 0.0),
+            (int)fmin(floor(zmax), (double)(nz - 1))};
+}
+
+// The local frame of a level (s = 2^L) of a triangle with lines in box b
 template <typename R>
-__device__ bool row_setup(const TriLoad& tl, int L, int ny, int nz, bool f32_verts, RowTri<R>& T, int& jlo,
-                          int& jhi, int& klo, int& khi) {
-    const double s = ldexp(1.0, L);
-    const int(&id)[3] = tl.id;
+__device__ void row_frame(const TriLoad& tl, int tri, double s, const RowBox& b, bool f32_verts, RowTri<R>& T) {
     double X[3][3];  // the same float64 operations as scaled64
     for (int i = 0; i < 3; i++)
         for (int a = 0; a < 3; a++) X[i][a] = tl.x[i][a] * s - 0.5;
-    const double ymin = fmin(X[0][1], fmin(X[1][1], X[2][1])), ymax = fmax(X[0][1], fmax(X[1][1], X[2][1]));
-    const double zmin = fmin(X[0][2], fmin(X[1][2], X[2][2])), zmax = fmax(X[0][2], fmax(X[1][2], X[2][2]));
-    jlo = (int)fmax(ceil(ymin), 0.0);
-    jhi = (int)fmin(floor(ymax), (double)(ny - 1));
-    klo = (int)fmax(ceil(zmin), 0.0);
-    khi = (int)fmin(floor(zmax), (double)(nz - 1));
-    if (jlo > jhi || klo > khi) return false;
     // origin: x from vertex 0, y/z from the first line; fall back to 0 on an
     // axis where the translation would not be exact in float64.  Float32
     // vertices within the coordinate contract (0 or [1/4, n0], n0 2^L <=
     // 2^15) need no check: X and X - o span at most 2^14 .. 2^-25, 40 bits.
-    int o[3] = {(int)floor(X[0][0]), jlo, klo};
+    int o[3] = {(int)floor(X[0][0]), b.jlo, b.klo};
     for (int a = 0; a < 3 && !f32_verts; a++) {
         bool exact = true;
         for (int i = 0; i < 3; i++) {
@@ -290,7 +313,6 @@ __device__ bool row_setup(const TriLoad& tl, int L, int ny, int nz, bool f32_ver
     }
     R delta = 0;
     for (int i = 0; i < 3; i++) {
-        T.idx[i] = id[i];
         for (int a = 0; a < 3; a++) {
             const double x = X[i][a] - (double)o[a];
             T.v[i][a] = (R)x;
@@ -301,8 +323,8 @@ __device__ bool row_setup(const TriLoad& tl, int L, int ny, int nz, bool f32_ver
         }
     }
     T.delta = delta;
+    T.tri = tri;
     for (int a = 0; a < 3; a++) T.o[a] = o[a];
-    return true;
 }
 
 template <typename R>
@@ -312,9 +334,25 @@ __device__ __forceinline__ void swap_bc(RowTri<R>& T) {
         T.v[1][a] = T.v[2][a];
         T.v[2][a] = tmp;
     }
-    int ti = T.idx[1];
-    T.idx[1] = T.idx[2];
-    T.idx[2] = ti;
+    T.tri ^= (int)0x80000000u;
+}
+
+// how the lines meet the triangle: mode 1, proper yz projection (made
+// counter-clockwise here); mode 2, edge-on (drop = the axis besides x of a
+// plane with non-zero area, areaSign its sign); mode 0, zero area
+struct RowMode {
+    int mode, drop, areaSign;
+};
+template <typename R>
+__device__ __forceinline__ RowMode row_mode(const DevMesh& m, RowTri<R>& T, double s, Stats& st) {
+    const int ayz = chain_area<R>(m, T, s, 1, 2, st);
+    if (ayz < 0) swap_bc<R>(T);
+    if (ayz != 0) return {1, 0, 0};
+    // edge-on or degenerate: find a plane (x,y) or (x,z) with non-zero area
+    const int axy = chain_area<R>(m, T, s, 0, 1, st);
+    if (axy != 0) return {2, 1, axy};
+    const int axz = chain_area<R>(m, T, s, 0, 2, st);
+    return {axz != 0 ? 2 : 0, 2, axz};
 }
 
 // events of one (triangle, line) pair; e0: parity event or none, e1: surface interval or none
@@ -414,131 +452,249 @@ __device__ void row_events(const DevMesh& m, const RowTri<R>& T, double s, int m
     }
 }
 
-// The row-line events of one level for the wave's triangles (live lanes hold
-// one loaded triangle each), appended under keys key_base + j + ny k.  Called
-// by the whole wave; returns the number of pairs appended.
+// ------------------------------------------------------------------------
+// ROWS pass: the levels' keys are consecutive ranges of one key space.
+//
+// A wave takes a batch of up to 64 triangles.  First every lane finds, for its
+// triangle and each level, whether it has row lines there at all; the
+// (triangle, level) items that have are set up 64 at a time, one per lane (a
+// fine triangle has lines on one level or two of five), and kept in LDS; then
+// their (item, line) pairs are numbered through and every lane takes one pair,
+// whatever triangle it is of.  Bound by VALU work and its latency: the lines
+// per item vary from one to hundreds, and a lane that walked the lines of its
+// own triangle left the others idle.  An item with more than ROW_BIG lines is
+// cut into pieces that a second launch spreads over the chip (a CAD mesh has a
+// dozen triangles of 10^5 lines; overflow of that list is done in place).
+// Before (one lane per triangle, its lines in turn) and now, float32 form:
+// 0.61 and 0.42 ms on 7.2M triangles over levels 0..4, 0.16 and 0.10 ms on 112k
+// over 0..3, 127 and 22 us on 1,792 over 0..2, 6.4 and 0.08 ms on a 1,024-
+// triangle cylinder over 0..3; float64 form 0.28 and 0.19 ms on 1.02M.
+// ------------------------------------------------------------------------
+constexpr int ROW_BIG = 128;          // lines of an item done by its own wave
+constexpr int ROW_PIECES = 64;        // most pieces of an item
+constexpr int ROW_LIST = ROW_LIST_CAP;
+
 template <typename R>
-__device__ __forceinline__ int rows_level(const DevMesh& m, bool live, const TriLoad& tl, int L, int key_base,
-                                          Appender<false>& app, Stats& st, const int n0[3]) {
-    const int nx = n0[0] << L, ny = n0[1] << L, nz = n0[2] << L;
-    const double s = ldexp(1.0, L);
-    RowTri<R> T;
-    int jlo = 0, jhi = -1, klo = 0, khi = -1;
-    int mode = 0, drop = 0, areaSign = 0;
-    if (live && row_setup<R>(tl, L, ny, nz, m.vdtype == GEO_F32, T, jlo, jhi, klo, khi)) {
-        const int ayz = chain_area<R>(m, T, s, 1, 2, st);
-        if (ayz < 0) swap_bc<R>(T);
-        if (ayz != 0) {
-            mode = 1;
-        } else {
-            // edge-on or degenerate: find a plane (x,y) or (x,z) with non-zero area
-            const int axy = chain_area<R>(m, T, s, 0, 1, st);
-            if (axy != 0) { mode = 2; drop = 1; areaSign = axy; }
-            else {
-                const int axz = chain_area<R>(m, T, s, 0, 2, st);
-                if (axz != 0) { mode = 2; drop = 2; areaSign = axz; }
+struct RowItems {  // field-major: lane i writes item i, any lane reads any item
+    R v[9][64], delta[64];
+    int o[3][64], tri[64];
+    int jlo[64], klo[64], nj[64];
+    int base[64];  // first key of the item's level
+    int meta[64];  // level | mode << 4 | drop << 6 | (areaSign + 1) << 8
+    int pre[64];   // number of the item's first pair
+};
+
+template <typename R>
+__device__ __forceinline__ void item_store(RowItems<R>& I, int i, const RowTri<R>& T, const RowBox& b, int base, int L,
+                                           const RowMode& md, int pre) {
+    for (int k = 0; k < 9; k++) I.v[k][i] = T.v[k / 3][k % 3];
+    I.delta[i] = T.delta;
+    for (int a = 0; a < 3; a++) I.o[a][i] = T.o[a];
+    I.tri[i] = T.tri;
+    I.jlo[i] = b.jlo;
+    I.klo[i] = b.klo;
+    I.nj[i] = b.jhi - b.jlo + 1;
+    I.base[i] = base;
+    I.meta[i] = L | md.mode << 4 | md.drop << 6 | (md.areaSign + 1) << 8;
+    I.pre[i] = pre;
+}
+
+// events of line `line` (j fastest) of the item, appended by the whole wave
+template <typename R>
+__device__ __forceinline__ void line_events(const DevMesh& m, const int n0[3], bool on, const RowTri<R>& T, int L,
+                                            const RowMode& md, int jlo, int klo, int nj, int base, int line,
+                                            Appender<false>& app, Stats& st) {
+    bool h0 = false, h1 = false;
+    int32_t e0 = 0, e1 = 0;
+    int key = 0;
+    if (on) {
+        const unsigned q = (unsigned)line / (unsigned)nj;
+        const int j = jlo + (line - (int)q * nj), k = klo + (int)q;
+        key = base + j + (n0[1] << L) * k;
+        row_events<R>(m, T, ldexp(1.0, L), md.mode, md.drop, md.areaSign, j, k, n0[0] << L, st, h0, e0, h1, e1);
+    }
+    app.add(h0, key, e0);
+    app.add(h1, key, e1);
+}
+
+template <typename R>
+__device__ __forceinline__ void item_events(const DevMesh& m, const int n0[3], bool on, const RowItems<R>& I, int i,
+                                            int line, Appender<false>& app, Stats& st) {
+    RowTri<R> P;
+    for (int k = 0; k < 9; k++) P.v[k / 3][k % 3] = I.v[k][i];
+    P.delta = I.delta[i];
+    for (int a = 0; a < 3; a++) P.o[a] = I.o[a][i];
+    P.tri = I.tri[i];
+    const int meta = I.meta[i];
+    line_events<R>(m, n0, on, P, meta & 15, {meta >> 4 & 3, meta >> 6 & 3, (meta >> 8) - 1}, I.jlo[i], I.klo[i], I.nj[i],
+                   I.base[i], line, app, st);
+}
+
+// Pieces of an item with n lines: written to the list (triangle, level index,
+// first line, lines) by its lane.  Returns whether the list took them.
+__device__ __forceinline__ bool list_item(int4* list, int* list_n, bool big, int tri, int l, int n) {
+    const int want = big ? ((n + ROW_PIECES - 1) / ROW_PIECES + 63) & ~63 : 1;
+    const int piece = want < ROW_BIG ? ROW_BIG : want;
+    const int k = big ? (n + piece - 1) / piece : 0;
+    const int incl = wave_incl_scan(k), total = __shfl(incl, 63, 64);
+    // a full list is not added to any more, so that its counter cannot wrap
+    int at = ROW_LIST;
+    if (threadIdx.x == 0 && __hip_atomic_load(list_n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < ROW_LIST)
+        at = atomicAdd(list_n, total);
+    at = __shfl(at, 0, 64);
+    at += incl - k;
+    const bool taken = big && at + k <= ROW_LIST;
+    for (int i = 0; i < k; i++)  // a refused item leaves empty pieces
+        if (at + i < ROW_LIST)
+            list[at + i] = make_int4(tri, l, i * piece, !taken ? 0 : (n - i * piece < piece ? n - i * piece : piece));
+    return taken;
+}
+
+template <typename R>
+__device__ __forceinline__ void rows_levels_body(const DevMesh& m, const DevLevel& d, const RowLevels& rl, int tpw,
+                                                 int32_t* cnt, int2* pairs, int32_t* rank, int64_t cap,
+                                                 int64_t* d_pairs, int4* list, int* list_n, unsigned long long* slots) {
+    __shared__ int2 sbuf[APP_BUF];
+    __shared__ RowItems<R> I;
+    __shared__ uint16_t items[64 * GEO_MAX_LEVELS];  // lane | level index << 6
+    __shared__ int mark[64];
+    __shared__ int sbase[GEO_MAX_LEVELS];
+    const int lane = threadIdx.x;
+    if (lane < GEO_MAX_LEVELS) sbase[lane] = rl.base[lane];
+    Appender<false> app{sbuf, 0, pairs, rank, cap, d_pairs, cnt};
+    Stats st;
+    const bool f32v = m.vdtype == GEO_F32;
+    const int64_t stride = (int64_t)gridDim.x * tpw;
+    for (int64_t base = (int64_t)blockIdx.x * tpw; base < m.nt; base += stride) {
+        const int64_t t = base + lane;
+        TriLoad tl{};
+        const bool live = lane < tpw && t < m.nt;
+        if (live) tri_load(m, t, tl);
+        int nitems = 0;
+        __syncthreads();
+        for (int l = 0; l < rl.nlev; l++) {
+            const int L = rl.lmin + l;
+            const bool has = live && row_box(tl, ldexp(1.0, L), d.n0[1] << L, d.n0[2] << L).any();
+            const unsigned long long bal = __ballot(has);
+            if (has) items[nitems + __popcll(bal & ((1ull << lane) - 1ull))] = (uint16_t)(lane | l << 6);
+            nitems += __popcll(bal);
+        }
+        __syncthreads();
+        for (int c = 0; c < nitems; c += 64) {  // uniform
+            const bool valid = c + lane < nitems;
+            const int code = valid ? items[c + lane] : lane;
+            const int src = code & 63, l = code >> 6, L = rl.lmin + l;
+            TriLoad ti;
+            for (int i = 0; i < 3; i++)
+                for (int a = 0; a < 3; a++) ti.x[i][a] = __shfl(tl.x[i][a], src, 64);
+            const int tri = (int)base + src;
+            RowBox b{0, -1, 0, -1};
+            RowMode md{0, 0, 0};
+            RowTri<R> T;
+            int n = 0;
+            if (valid) {
+                const double s = ldexp(1.0, L);
+                b = row_box(ti, s, d.n0[1] << L, d.n0[2] << L);
+                row_frame<R>(ti, tri, s, b, f32v, T);
+                md = row_mode<R>(m, T, s, st);
+                if (md.mode) n = (b.jhi - b.jlo + 1) * (b.khi - b.klo + 1);
+            }
+            // large items: to the list, or (refused) below by the whole wave
+            int nbig = n > ROW_BIG ? n : 0;
+            if (__any(nbig > 0) && list_item(list, list_n, nbig > 0, tri, l, nbig)) nbig = 0;
+            if (n > ROW_BIG) n = 0;
+            const int incl = wave_incl_scan(n), total = __shfl(incl, 63, 64);
+            __syncthreads();
+            if (n > 0 || nbig > 0) item_store<R>(I, lane, T, b, sbase[l], L, md, incl - n);
+            for (int done = 0; done < total; done += 64) {  // uniform
+                // item of each pair: its number where the item's pairs start
+                // (or the chunk does), carried on by a prefix maximum
+                mark[lane] = 0;
+                __syncthreads();
+                if (n > 0 && incl > done && incl - n < done + 64)
+                    mark[incl - n > done ? incl - n - done : 0] = lane;
+                __syncthreads();
+                const int i = wave_incl_max(mark[lane]);
+                item_events<R>(m, d.n0, done + lane < total, I, i, done + lane - I.pre[i], app, st);
+            }
+            unsigned long long rest = __ballot(nbig > 0);
+            if (rest) __syncthreads();
+            while (rest) {  // uniform
+                const int i = __ffsll(rest) - 1;
+                rest &= rest - 1;
+                const int nl = __shfl(nbig, i, 64);
+                for (int q = 0; q < nl; q += 64) item_events<R>(m, d.n0, q + lane < nl, I, i, q + lane, app, st);
             }
         }
     }
-    const int nj = mode ? jhi - jlo + 1 : 0;
-    const int nlines = mode ? nj * (khi - klo + 1) : 0;
-    int added = 0;
-    for (int it = 0; __any(it < nlines); it++) {
-        bool h0 = false, h1 = false;
-        int32_t e0 = 0, e1 = 0;
-        int key = 0;
-        if (it < nlines) {
-            const int j = jlo + it % nj, k = klo + it / nj;
-            key = key_base + j + ny * k;
-            row_events<R>(m, T, s, mode, drop, areaSign, j, k, nx, st, h0, e0, h1, e1);
-        }
-        added += app.add(h0, key, e0);
-        added += app.add(h1, key, e1);
-    }
-    return added;
-}
-
-template <typename R>
-__global__ void __launch_bounds__(64) k_rows_pass1(DevMesh m, DevLevel d, int32_t* cnt, int2* pairs, int32_t* rank,
-                                                   int64_t cap, int64_t* d_count, uint64_t* stats) {
-    __shared__ int2 sbuf[APP_BUF];
-    Appender<false> app{sbuf, 0, pairs, rank, cap, d_count, cnt};
-    Stats st;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < m.nt; base += stride) {
-        const int64_t t = base + threadIdx.x;
-        TriLoad tl;
-        const bool live = t < m.nt;
-        if (live) tri_load(m, t, tl);
-        rows_level<R>(m, live, tl, d.level, 0, app, st, d.n0);
-    }
     app.flush();
-    if (stats) {
-        if constexpr (std::is_same<R, float>::value) wave_count(&stats[GEO_STAT_F32_TO_F64], st.fb);
-        wave_count(&stats[GEO_STAT_EXACT], st.ex);
-    }
+    row_stats<R>(slots, st);
 }
 
-// ROWS bins of levels lmin .. lmin+nlev-1 in one pass: each triangle is
-// loaded once and visits its lines of every level in turn; the keys of level
-// lmin+l start at rl.base[l].  Pairs share one array and one reservation
-// counter (*d_pairs); the pairs needed by each level are counted per wave in
-// LDS and added to the level's own counter once at the end.
+// float32 form: 3 waves per SIMD; the float64 form keeps its registers (a cap
+// spills it heavily)
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8)))
+k_rows_levels_f32(DevMesh m, DevLevel d, RowLevels rl, int tpw, int32_t* cnt, int2* pairs, int32_t* rank, int64_t cap,
+                  int64_t* d_pairs, int4* list, int* list_n, unsigned long long* slots) {
+    rows_levels_body<float>(m, d, rl, tpw, cnt, pairs, rank, cap, d_pairs, list, list_n, slots);
+}
+
+__global__ void __launch_bounds__(64) k_rows_levels_f64(DevMesh m, DevLevel d, RowLevels rl, int tpw, int32_t* cnt,
+                                                        int2* pairs, int32_t* rank, int64_t cap, int64_t* d_pairs,
+                                                        int4* list, int* list_n, unsigned long long* slots) {
+    rows_levels_body<double>(m, d, rl, tpw, cnt, pairs, rank, cap, d_pairs, list, list_n, slots);
+}
+
+// the listed pieces of large items, one wave per piece, lanes over its lines
 template <typename R>
-__device__ __forceinline__ void rows_levels_body(const DevMesh& m, const DevLevel& d, const RowLevels& rl, int32_t* cnt,
-                                                 int2* pairs, int32_t* rank, int64_t cap, int64_t* d_pairs,
-                                                 uint64_t* stats) {
+__global__ void __launch_bounds__(64) k_rows_pieces(DevMesh m, DevLevel d, RowLevels rl, int32_t* cnt, int2* pairs,
+                                                    int32_t* rank, int64_t cap, int64_t* d_pairs, const int4* list,
+                                                    const int* list_n, unsigned long long* slots) {
     __shared__ int2 sbuf[APP_BUF];
-    __shared__ unsigned long long slc[GEO_MAX_LEVELS];
     const int lane = threadIdx.x;
-    if (lane < GEO_MAX_LEVELS) slc[lane] = 0;
-    __syncthreads();
+    int np = *list_n;
+    if (np < 0 || np > ROW_LIST) np = ROW_LIST;
+    if ((int)blockIdx.x >= np) return;
     Appender<false> app{sbuf, 0, pairs, rank, cap, d_pairs, cnt};
     Stats st;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < m.nt; base += stride) {
-        const int64_t t = base + lane;
+    for (int e = blockIdx.x; e < np; e += gridDim.x) {
+        const int4 p = list[e];
+        if (p.w <= 0) continue;  // uniform
+        const int l = p.y, L = rl.lmin + l;
+        const double s = ldexp(1.0, L);
         TriLoad tl;
-        const bool live = t < m.nt;
-        if (live) tri_load(m, t, tl);
-        for (int l = 0; l < rl.nlev; l++) {
-            const int added = rows_level<R>(m, live, tl, rl.lmin + l, rl.base[l], app, st, d.n0);
-            if (lane == 0 && added) slc[l] += (unsigned long long)added;
-        }
+        tri_load(m, p.x, tl);
+        const RowBox b = row_box(tl, s, d.n0[1] << L, d.n0[2] << L);
+        RowTri<R> T;
+        row_frame<R>(tl, p.x, s, b, m.vdtype == GEO_F32, T);
+        Stats again;  // counted where the item was listed
+        const RowMode md = row_mode<R>(m, T, s, again);
+        for (int i = 0; i < p.w; i += 64)  // uniform
+            line_events<R>(m, d.n0, i + lane < p.w, T, L, md, b.jlo, b.klo, b.jhi - b.jlo + 1, rl.base[l],
+                           p.z + i + lane, app, st);
     }
     app.flush();
-    __syncthreads();
-    if (lane < rl.nlev && slc[lane]) atomicAdd(rl.count[lane], slc[lane]);
-    if (stats) {
-        if constexpr (std::is_same<R, float>::value) wave_count(&stats[GEO_STAT_F32_TO_F64], st.fb);
-        wave_count(&stats[GEO_STAT_EXACT], st.ex);
+    row_stats<R>(slots, st);
+}
+
+// zero the shared pair counter, the list's counter, the statistics slots and
+// the key counts
+__global__ void k_rows_levels_zero(int64_t* d_pairs, int* list_n, unsigned long long* slots, int32_t* cnt,
+                                   int64_t nkeys) {
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n = (int64_t)gridDim.x * blockDim.x;
+    if (i0 == 0) {
+        *d_pairs = 0;
+        *list_n = 0;
     }
+    if (slots && blockIdx.x == 0)
+        for (int i = threadIdx.x; i < ROW_SLOTS * ROW_SLOT_WORDS; i += blockDim.x) slots[i] = 0ull;
+    for (int64_t i = i0; i < nkeys; i += n) cnt[i] = 0;
 }
 
-// float32 form: 3 waves per SIMD (168 VGPRs; the cap spills 16 B per lane);
-// the float64 form keeps its registers (a cap spills it heavily)
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8)))
-k_rows_levels_f32(DevMesh m, DevLevel d, RowLevels rl, int32_t* cnt, int2* pairs, int32_t* rank, int64_t cap,
-                  int64_t* d_pairs, uint64_t* stats) {
-    rows_levels_body<float>(m, d, rl, cnt, pairs, rank, cap, d_pairs, stats);
-}
-
-__global__ void __launch_bounds__(64) k_rows_levels_f64(DevMesh m, DevLevel d, RowLevels rl, int32_t* cnt, int2* pairs,
-                                                        int32_t* rank, int64_t cap, int64_t* d_pairs, uint64_t* stats) {
-    rows_levels_body<double>(m, d, rl, cnt, pairs, rank, cap, d_pairs, stats);
-}
-
-// zero the per-level counters, the shared pair counter and the key counts
-__global__ void k_rows_levels_zero(RowLevels rl, int64_t* d_pairs, int32_t* cnt, int64_t nkeys) {
-    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i0 < rl.nlev) *rl.count[i0] = 0ull;
-    if (i0 == 0) *d_pairs = 0;
-    for (int64_t i = i0; i < nkeys; i += (int64_t)gridDim.x * blockDim.x) cnt[i] = 0;
-}
-
-// place the pairs of every level: the level of a pair is found from its key
+// place the pairs of every level: the level of a pair is found from its key;
+// the statistics slots are added to the caller's counters
 __global__ void k_rows_levels_scatter(const int2* pairs, const int32_t* rank, int64_t cap, const int64_t* d_pairs,
-                                      RowLevels rl) {
+                                      RowLevels rl, const unsigned long long* slots, uint64_t* stats) {
     __shared__ int sbase[GEO_MAX_LEVELS + 1];
     __shared__ const int32_t* soff[GEO_MAX_LEVELS];
     __shared__ int32_t* sval[GEO_MAX_LEVELS];
@@ -550,6 +706,11 @@ __global__ void k_rows_levels_scatter(const int2* pairs, const int32_t* rank, in
         scap[threadIdx.x] = rl.cap[threadIdx.x];
     }
     __syncthreads();
+    if (slots && blockIdx.x == 0 && threadIdx.x < ROW_SLOTS) {
+        const unsigned long long fb = slots[threadIdx.x * ROW_SLOT_WORDS], ex = slots[threadIdx.x * ROW_SLOT_WORDS + 1];
+        if (fb) atomicAdd((unsigned long long*)&stats[GEO_STAT_F32_TO_F64], fb);
+        if (ex) atomicAdd((unsigned long long*)&stats[GEO_STAT_EXACT], ex);
+    }
     const int64_t n0 = *d_pairs;
     const int64_t n = n0 < cap ? n0 : cap;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
@@ -780,48 +941,39 @@ inline unsigned grid_for(int64_t n, int threads, int64_t maxg = 1 << 16) {
 
 }  // namespace
 
-int launch_rows_pass1(const DevMesh& m, const DevLevel& d, int precision, int32_t* cnt, int2* pairs,
-                      int32_t* rank, int64_t cap, int64_t* d_count, uint64_t* d_stats, hipStream_t s) {
+int launch_rows_levels(const DevMesh& m, const DevLevel& d, int precision, const RowLevels& rl, const RowWork& w,
+                       hipStream_t s) {
     if (m.nt == 0) return GEO_OK;
-    // grid caps measured per form on 7.2M triangles: the float32 pass is
-    // fastest at 8192 workgroups, the float64 pass at 2048
-    const unsigned g = grid_for(m.nt, 64, precision == GEO_PREC_F32_FALLBACK ? 8192 : 2048);
+    const bool f32 = precision == GEO_PREC_F32_FALLBACK;
+    // triangles per wave: 64, fewer where that would leave the chip idle (below
+    // 4,096 waves; 112k triangles: 98 us, 136 with 2,048 waves, 0.16 ms with 64
+    // each), but 4 at least (1,792 triangles: 22 us, 29 with 2)
+    const int64_t per = (m.nt + 4095) / 4096;
+    const int tpw = per < 4 ? 4 : (per > 64 ? 64 : (int)per);
+    // grid caps: float32 form 16,384 (0.42 ms on 7.2M triangles over levels
+    // 0..4; 0.43 at 8,192, 0.50 at 32,768), float64 form 8,192 (0.19 ms on 1M
+    // triangles over levels 0..3, 0.22 at 2,048)
+    const unsigned g = grid_for(m.nt, tpw, f32 ? 16384 : 8192);
     kt_record(GEO_KT_ROWS, s, false);
-    if (precision == GEO_PREC_F32_FALLBACK)
-        k_rows_pass1<float><<<g, 64, 0, s>>>(m, d, cnt, pairs, rank, cap, d_count, d_stats);
-    else
-        k_rows_pass1<double><<<g, 64, 0, s>>>(m, d, cnt, pairs, rank, cap, d_count, d_stats);
+    auto pass = f32 ? k_rows_levels_f32 : k_rows_levels_f64;
+    pass<<<g, 64, 0, s>>>(m, d, rl, tpw, w.cnt, w.pairs, w.rank, w.cap, w.d_pairs, w.list, w.list_n, w.slots);
     kt_record(GEO_KT_ROWS, s, true);
+    auto pieces = f32 ? k_rows_pieces<float> : k_rows_pieces<double>;
+    pieces<<<2048, 64, 0, s>>>(m, d, rl, w.cnt, w.pairs, w.rank, w.cap, w.d_pairs, w.list, w.list_n, w.slots);
     GEO_LAUNCH_CHECK();
     return GEO_OK;
 }
 
-int launch_rows_levels(const DevMesh& m, const DevLevel& d, int precision, const RowLevels& rl, int32_t* cnt,
-                       int2* pairs, int32_t* rank, int64_t cap, int64_t* d_pairs, uint64_t* d_stats, hipStream_t s) {
-    if (m.nt == 0) return GEO_OK;
-    // grid caps measured on 7.2M triangles over levels 0..4: 16,384 workgroups
-    // for the float32 form (0.645 ms at 8,192), 2,048 for the float64 form
-    const unsigned g = grid_for(m.nt, 64, precision == GEO_PREC_F32_FALLBACK ? 16384 : 2048);
-    kt_record(GEO_KT_ROWS, s, false);
-    if (precision == GEO_PREC_F32_FALLBACK)
-        k_rows_levels_f32<<<g, 64, 0, s>>>(m, d, rl, cnt, pairs, rank, cap, d_pairs, d_stats);
-    else
-        k_rows_levels_f64<<<g, 64, 0, s>>>(m, d, rl, cnt, pairs, rank, cap, d_pairs, d_stats);
-    kt_record(GEO_KT_ROWS, s, true);
+int launch_rows_levels_zero(const RowWork& w, int64_t nkeys, hipStream_t s) {
+    k_rows_levels_zero<<<grid_for(nkeys, 256, 16384), 256, 0, s>>>(w.d_pairs, w.list_n, w.slots, w.cnt, nkeys);
     GEO_LAUNCH_CHECK();
     return GEO_OK;
 }
 
-int launch_rows_levels_zero(const RowLevels& rl, int64_t* d_pairs, int32_t* cnt, int64_t nkeys, hipStream_t s) {
-    k_rows_levels_zero<<<grid_for(nkeys, 256, 16384), 256, 0, s>>>(rl, d_pairs, cnt, nkeys);
-    GEO_LAUNCH_CHECK();
-    return GEO_OK;
-}
-
-int launch_rows_levels_scatter(const int2* pairs, const int32_t* rank, int64_t cap, const int64_t* d_pairs,
-                               const RowLevels& rl, hipStream_t s) {
-    if (cap <= 0) return GEO_OK;
-    k_rows_levels_scatter<<<grid_for(cap, 256, 8192), 256, 0, s>>>(pairs, rank, cap, d_pairs, rl);
+int launch_rows_levels_scatter(const RowLevels& rl, const RowWork& w, uint64_t* d_stats, hipStream_t s) {
+    if (w.cap <= 0 && !d_stats) return GEO_OK;
+    k_rows_levels_scatter<<<grid_for(w.cap, 256, 8192), 256, 0, s>>>(w.pairs, w.rank, w.cap, w.d_pairs, rl,
+                                                                     d_stats ? w.slots : nullptr, d_stats);
     GEO_LAUNCH_CHECK();
     return GEO_OK;
 }

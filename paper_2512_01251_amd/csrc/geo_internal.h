@@ -265,6 +265,18 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
     return v;
 }
 
+// inclusive prefix maximum of non-negative v over the wave, by the same steps
+__device__ __forceinline__ int wave_incl_max(int v) {
+    auto mx = [](int a, int b) { return a > b ? a : b; };
+    v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));
+    v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));
+    v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));
+    v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));
+    v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));
+    v = mx(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
+    return v;
+}
+
 // statistics: one atomic per wave for a per-lane count
 __device__ __forceinline__ void wave_count(uint64_t* ctr, unsigned n) {
     if (!ctr) return;
@@ -309,24 +321,33 @@ int geo_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 int geo_fill_u64(uint64_t* p, uint64_t v, int64_t n, hipStream_t s);
 
 // ROWS bins of several levels built together (levels lmin .. lmin+nlev-1):
-// keys of level lmin+l start at base[l] in the joint key space; count, off,
-// val and cap are the levels' own bins.
+// keys of level lmin+l start at base[l] in the joint key space; off, val and
+// cap are the levels' own bins.
 struct RowLevels {
     int nlev, lmin;
     int base[GEO_MAX_LEVELS + 1];
-    unsigned long long* count[GEO_MAX_LEVELS];
     const int32_t* off[GEO_MAX_LEVELS];
     int32_t* val[GEO_MAX_LEVELS];
     int64_t cap[GEO_MAX_LEVELS];
 };
-int launch_rows_levels(const DevMesh& m, const DevLevel& d, int precision, const RowLevels& rl, int32_t* cnt,
-                       int2* pairs, int32_t* rank, int64_t cap, int64_t* d_pairs, uint64_t* d_stats, hipStream_t s);
-int launch_rows_levels_zero(const RowLevels& rl, int64_t* d_pairs, int32_t* cnt, int64_t nkeys, hipStream_t s);
-int launch_rows_levels_scatter(const int2* pairs, const int32_t* rank, int64_t cap, const int64_t* d_pairs,
-                               const RowLevels& rl, hipStream_t s);
-int launch_rows_pass1(const DevMesh& m, const DevLevel& d, int precision, int32_t* cnt,
-                      int2* pairs, int32_t* rank, int64_t cap, int64_t* d_count, uint64_t* d_stats,
-                      hipStream_t s);
+// scratch of a ROWS build: counts per key, staged pairs with their ranks and
+// their number, pieces of large items, statistics slots (NULL: no statistics)
+constexpr int ROW_LIST_CAP = 65536;
+constexpr int ROW_SLOTS = 64, ROW_SLOT_WORDS = 16;
+struct RowWork {
+    int32_t* cnt;
+    int2* pairs;
+    int32_t* rank;
+    int64_t cap;
+    int64_t* d_pairs;
+    int4* list;
+    int* list_n;
+    unsigned long long* slots;
+};
+int launch_rows_levels(const DevMesh& m, const DevLevel& d, int precision, const RowLevels& rl, const RowWork& w,
+                       hipStream_t s);
+int launch_rows_levels_zero(const RowWork& w, int64_t nkeys, hipStream_t s);
+int launch_rows_levels_scatter(const RowLevels& rl, const RowWork& w, uint64_t* d_stats, hipStream_t s);
 int launch_links_pass1(const DevMesh& m, const DevLevel& d, int32_t* cnt, int2* pairs, int32_t* rank,
                        int64_t cap, int64_t* d_count, hipStream_t s);
 int launch_bins_scatter(const int2* pairs, const int32_t* rank, int64_t cap, const int64_t* d_count,
