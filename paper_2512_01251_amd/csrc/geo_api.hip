@@ -11,23 +11,37 @@ namespace {
 
 inline size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// A bin build's workspace: staged pairs, ranks, key counts, scan partials (each
+// level's scan may end in a tile of its own), the list of large triangles'
+// pieces, the statistics slots, the counters.
+size_t bin_partials_bytes(int64_t nkeys) { return geo_scan_partials_bytes(nkeys) + sizeof(int64_t) * GEO_MAX_LEVELS; }
+
 size_t bins_ws_bytes(int64_t nkeys, int64_t cap) {
     const size_t c = (size_t)(cap > 0 ? cap : 0);
     return al(sizeof(int2) * c) + al(sizeof(int32_t) * c) + al(sizeof(int32_t) * ((size_t)nkeys + 1)) +
-           al(geo_scan_partials_bytes(nkeys));
+           al(bin_partials_bytes(nkeys)) + al(sizeof(int4) * BIN_LIST_CAP) +
+           al(sizeof(unsigned long long) * ROW_SLOTS * ROW_SLOT_WORDS) + al(sizeof(BinCtl));
 }
 
-// each level's scan may end in a tile of its own
-size_t rows_partials_bytes(int64_t nkeys) { return geo_scan_partials_bytes(nkeys) + sizeof(int64_t) * GEO_MAX_LEVELS; }
-
-// the ROWS builds: staged pairs, ranks, key counts and scan partials as for
-// the LINKS bins, the list of large items' pieces, the statistics slots, the
-// two counters
-size_t rows_ws_bytes(int64_t nkeys, int64_t cap) {
-    const size_t c = (size_t)(cap > 0 ? cap : 0);
-    return al(sizeof(int2) * c) + al(sizeof(int32_t) * c) + al(sizeof(int32_t) * ((size_t)nkeys + 1)) +
-           al(rows_partials_bytes(nkeys)) + al(sizeof(int4) * ROW_LIST_CAP) +
-           al(sizeof(unsigned long long) * ROW_SLOTS * ROW_SLOT_WORDS) + al(2 * sizeof(int64_t));
+// its parts (bins_ws_bytes of workspace); partials: the scan's
+BinWork bin_work(void* ws, int64_t nkeys, int64_t cap, bool stats, int64_t*& partials) {
+    BinWork w{};
+    char* p = static_cast<char*>(ws);
+    w.cap = cap;
+    w.pairs = reinterpret_cast<int2*>(p);
+    p += al(sizeof(int2) * (size_t)cap);
+    w.rank = reinterpret_cast<int32_t*>(p);
+    p += al(sizeof(int32_t) * (size_t)cap);
+    w.cnt = reinterpret_cast<int32_t*>(p);
+    p += al(sizeof(int32_t) * ((size_t)nkeys + 1));
+    partials = reinterpret_cast<int64_t*>(p);
+    p += al(bin_partials_bytes(nkeys));
+    w.list = reinterpret_cast<int4*>(p);
+    p += al(sizeof(int4) * BIN_LIST_CAP);
+    w.slots = stats ? reinterpret_cast<unsigned long long*>(p) : nullptr;
+    p += al(sizeof(unsigned long long) * ROW_SLOTS * ROW_SLOT_WORDS);
+    w.ctl = reinterpret_cast<BinCtl*>(p);
+    return w;
 }
 
 bool check_level(const geo_level* lv) {
@@ -75,8 +89,8 @@ size_t geo_workspace_size(int32_t call, int64_t nkeys, int64_t cap) {
     if (nkeys < 0) return 0;
     switch (call) {
         case GEO_CALL_BINS_ROWS:
-        case GEO_CALL_BINS_ROWS_LEVELS: return rows_ws_bytes(nkeys, cap);
-        case GEO_CALL_BINS_LINKS: return bins_ws_bytes(nkeys, cap);
+        case GEO_CALL_BINS_LINKS:
+        case GEO_CALL_BINS_ROWS_LEVELS: return bins_ws_bytes(nkeys, cap);
         case GEO_CALL_REFINE: return geo_refine_ws_bytes(nkeys);
         case GEO_CALL_CUTLINKS: return geo_cutlinks_ws_bytes(nkeys, cap);
         case GEO_CALL_LINKS_DENSE: return geo_dense_ws_bytes(nkeys);
@@ -122,22 +136,17 @@ int geo_build_bins(const geo_mesh* mesh, const geo_level* lv, int32_t kind, int3
         return geo_build_row_bins_levels(mesh, lv->n0, lv->level, 1, precision, out, d_stats, ws, ws_bytes, stream);
     if (ws_bytes < bins_ws_bytes(nkeys, out->cap) || (!ws && ws_bytes)) return GEO_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    char* p = static_cast<char*>(ws);
-    int2* pairs = reinterpret_cast<int2*>(p);
-    p += al(sizeof(int2) * (size_t)out->cap);
-    int32_t* rank = reinterpret_cast<int32_t*>(p);
-    p += al(sizeof(int32_t) * (size_t)out->cap);
-    int32_t* cnt = reinterpret_cast<int32_t*>(p);
-    p += al(sizeof(int32_t) * ((size_t)nkeys + 1));
-    int64_t* partials = reinterpret_cast<int64_t*>(p);
+    int64_t* partials;
+    const BinWork w = bin_work(ws, nkeys, out->cap, false, partials);
     const DevMesh m = dev_mesh(mesh);
     const DevLevel d = dev_level(lv);
     int rc;
-    if ((rc = geo_zero_counts(reinterpret_cast<uint64_t*>(out->d_count), cnt, nkeys, s)) != GEO_OK) return rc;
+    if ((rc = launch_bins_zero(w, nkeys, s)) != GEO_OK) return rc;
     if ((rc = launch_check_mesh(m, d, d_stats, s)) != GEO_OK) return rc;
-    if ((rc = launch_links_pass1(m, d, cnt, pairs, rank, out->cap, out->d_count, s)) != GEO_OK) return rc;
-    if ((rc = geo_scan_exclusive(cnt, out->off, nkeys, partials, s)) != GEO_OK) return rc;
-    return launch_bins_scatter(pairs, rank, out->cap, out->d_count, out->off, out->val, s);
+    if ((rc = launch_links_pass1(m, d, w, s)) != GEO_OK) return rc;
+    // every key's count is complete whatever fits the pair array
+    if ((rc = geo_scan_exclusive(w.cnt, out->off, nkeys, partials, s, out->d_count)) != GEO_OK) return rc;
+    return launch_bins_scatter(w, out->off, out->val, s);
 }
 
 int geo_build_row_bins_levels(const geo_mesh* mesh, const int32_t n0[3], int32_t lmin, int32_t nlev,
@@ -169,30 +178,15 @@ int geo_build_row_bins_levels(const geo_mesh* mesh, const int32_t n0[3], int32_t
         cap += out[l].cap;
     }
     for (int l = nlev; l <= GEO_MAX_LEVELS; l++) rl.base[l] = (int)nkeys;
-    if (ws_bytes < rows_ws_bytes(nkeys, cap) || (!ws && ws_bytes)) return GEO_ERR_WORKSPACE;
+    if (ws_bytes < bins_ws_bytes(nkeys, cap) || (!ws && ws_bytes)) return GEO_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    RowWork w{};
-    char* p = static_cast<char*>(ws);
-    w.pairs = reinterpret_cast<int2*>(p);
-    p += al(sizeof(int2) * (size_t)cap);
-    w.rank = reinterpret_cast<int32_t*>(p);
-    p += al(sizeof(int32_t) * (size_t)cap);
-    w.cnt = reinterpret_cast<int32_t*>(p);
-    p += al(sizeof(int32_t) * ((size_t)nkeys + 1));
-    int64_t* partials = reinterpret_cast<int64_t*>(p);
-    p += al(rows_partials_bytes(nkeys));
-    w.list = reinterpret_cast<int4*>(p);
-    p += al(sizeof(int4) * ROW_LIST_CAP);
-    w.slots = d_stats ? reinterpret_cast<unsigned long long*>(p) : nullptr;
-    p += al(sizeof(unsigned long long) * ROW_SLOTS * ROW_SLOT_WORDS);
-    w.d_pairs = reinterpret_cast<int64_t*>(p);
-    w.list_n = reinterpret_cast<int*>(w.d_pairs + 1);
-    w.cap = cap;
+    int64_t* partials;
+    const BinWork w = bin_work(ws, nkeys, cap, d_stats != nullptr, partials);
     lv.level = lmin;
     const DevMesh m = dev_mesh(mesh);
     const DevLevel d = dev_level(&lv);
     int rc;
-    if ((rc = launch_rows_levels_zero(w, nkeys, s)) != GEO_OK) return rc;
+    if ((rc = launch_bins_zero(w, nkeys, s)) != GEO_OK) return rc;
     if ((rc = launch_check_mesh(m, d, d_stats, s)) != GEO_OK) return rc;
     if ((rc = launch_rows_levels(m, d, precision, rl, w, s)) != GEO_OK) return rc;
     // the counts of every key are complete whatever fits the pair array, so

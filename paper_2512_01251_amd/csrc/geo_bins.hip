@@ -19,6 +19,10 @@ namespace {
 // Append of (key, value) pairs.  Each workgroup is one wave; pairs are staged
 // in an LDS buffer and flushed with one global reservation per flush (a
 // global counter touched once per wave-iteration would serialise at L2).
+// Reservations on one counter complete one every 8.7 ns (64 spheres: 21,000
+// of them were 0.18 of the LINKS pass's 0.24 ms), so there are two: even
+// workgroups fill the pair array upwards from its start, odd ones downwards
+// from its end, and any split of the pairs between them fits.
 // The per-key counts are incremented at flush time, and the count a pair
 // finds is its rank among its key's pairs, kept beside it: the scatter then
 // places it without atomics.
@@ -32,17 +36,20 @@ template <bool Group>
 struct Appender {
     int2* buf;       // LDS [APP_BUF]
     int n;           // pairs staged (identical in every lane)
-    int2* pairs;
-    int32_t* rank;
-    int64_t cap;
-    int64_t* d_count;
-    int32_t* cnt;
+    const BinWork& w;
+
+    // array position of the i-th pair of a flush, or -1 past the capacity
+    __device__ __forceinline__ int64_t place(unsigned long long base, int i) const {
+        const unsigned long long k = base + (unsigned long long)i;
+        if (k >= (unsigned long long)w.cap) return -1;
+        return (blockIdx.x & 1) ? w.cap - 1 - (int64_t)k : (int64_t)k;
+    }
 
     __device__ __forceinline__ void flush() {
         if (n == 0) return;
         __syncthreads();
         unsigned long long base = 0;
-        if (threadIdx.x == 0) base = atomicAdd((unsigned long long*)d_count, (unsigned long long)n);
+        if (threadIdx.x == 0) base = atomicAdd((blockIdx.x & 1) ? &w.ctl->down : &w.ctl->up, (unsigned long long)n);
         base = __shfl(base, 0, 64);
         if constexpr (Group) {
             // Per chunk of 64 pairs, lanes holding the same key form a group;
@@ -77,14 +84,14 @@ struct Appender {
                 }
                 int r[4];
 #pragma unroll
-                for (int u = 0; u < 4; u++) r[u] = cntk[u] ? atomicAdd(&cnt[p[u].x], cntk[u]) : 0;
+                for (int u = 0; u < 4; u++) r[u] = cntk[u] ? atomicAdd(&w.cnt[p[u].x], cntk[u]) : 0;
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
                     const int base_k = __shfl(r[u], lead[u] < 0 ? lane : lead[u], 64);
-                    const unsigned long long pos = base + (unsigned long long)(i0 + 64 * u + lane);
-                    if (p[u].x >= 0 && pos < (unsigned long long)cap) {
-                        pairs[pos] = p[u];
-                        rank[pos] = base_k + off[u];
+                    const int64_t pos = place(base, i0 + 64 * u + lane);
+                    if (p[u].x >= 0 && pos >= 0) {
+                        w.pairs[pos] = p[u];
+                        w.rank[pos] = base_k + off[u];
                     }
                 }
             }
@@ -99,13 +106,13 @@ struct Appender {
                     p[u] = i < n ? buf[i] : make_int2(-1, 0);
                 }
 #pragma unroll
-                for (int u = 0; u < 4; u++) r[u] = p[u].x >= 0 ? atomicAdd(&cnt[p[u].x], 1) : 0;
+                for (int u = 0; u < 4; u++) r[u] = p[u].x >= 0 ? atomicAdd(&w.cnt[p[u].x], 1) : 0;
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
-                    const unsigned long long pos = base + (unsigned long long)(i0 + 64 * u);
-                    if (p[u].x >= 0 && pos < (unsigned long long)cap) {
-                        pairs[pos] = p[u];
-                        rank[pos] = r[u];
+                    const int64_t pos = place(base, i0 + 64 * u);
+                    if (p[u].x >= 0 && pos >= 0) {
+                        w.pairs[pos] = p[u];
+                        w.rank[pos] = r[u];
                     }
                 }
             }
@@ -127,6 +134,8 @@ struct Appender {
         return k;
     }
 };
+
+using RowAppender = Appender<false>;
 
 // ------------------------------------------------------------------------
 // per-triangle local frame for the row pass
@@ -472,7 +481,6 @@ __device__ void row_events(const DevMesh& m, const RowTri<R>& T, double s, int m
 // ------------------------------------------------------------------------
 constexpr int ROW_BIG = 128;          // lines of an item done by its own wave
 constexpr int ROW_PIECES = 64;        // most pieces of an item
-constexpr int ROW_LIST = ROW_LIST_CAP;
 
 template <typename R>
 struct RowItems {  // field-major: lane i writes item i, any lane reads any item
@@ -503,7 +511,7 @@ __device__ __forceinline__ void item_store(RowItems<R>& I, int i, const RowTri<R
 template <typename R>
 __device__ __forceinline__ void line_events(const DevMesh& m, const int n0[3], bool on, const RowTri<R>& T, int L,
                                             const RowMode& md, int jlo, int klo, int nj, int base, int line,
-                                            Appender<false>& app, Stats& st) {
+                                            RowAppender& app, Stats& st) {
     bool h0 = false, h1 = false;
     int32_t e0 = 0, e1 = 0;
     int key = 0;
@@ -519,7 +527,7 @@ __device__ __forceinline__ void line_events(const DevMesh& m, const int n0[3], b
 
 template <typename R>
 __device__ __forceinline__ void item_events(const DevMesh& m, const int n0[3], bool on, const RowItems<R>& I, int i,
-                                            int line, Appender<false>& app, Stats& st) {
+                                            int line, RowAppender& app, Stats& st) {
     RowTri<R> P;
     for (int k = 0; k < 9; k++) P.v[k / 3][k % 3] = I.v[k][i];
     P.delta = I.delta[i];
@@ -532,28 +540,27 @@ __device__ __forceinline__ void item_events(const DevMesh& m, const int n0[3], b
 
 // Pieces of an item with n lines: written to the list (triangle, level index,
 // first line, lines) by its lane.  Returns whether the list took them.
-__device__ __forceinline__ bool list_item(int4* list, int* list_n, bool big, int tri, int l, int n) {
+__device__ __forceinline__ bool list_item(const BinWork& w, bool big, int tri, int l, int n) {
     const int want = big ? ((n + ROW_PIECES - 1) / ROW_PIECES + 63) & ~63 : 1;
     const int piece = want < ROW_BIG ? ROW_BIG : want;
     const int k = big ? (n + piece - 1) / piece : 0;
     const int incl = wave_incl_scan(k), total = __shfl(incl, 63, 64);
     // a full list is not added to any more, so that its counter cannot wrap
-    int at = ROW_LIST;
-    if (threadIdx.x == 0 && __hip_atomic_load(list_n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < ROW_LIST)
-        at = atomicAdd(list_n, total);
+    int at = BIN_LIST_CAP;
+    if (threadIdx.x == 0 && __hip_atomic_load(&w.ctl->list_n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < BIN_LIST_CAP)
+        at = atomicAdd(&w.ctl->list_n, total);
     at = __shfl(at, 0, 64);
     at += incl - k;
-    const bool taken = big && at + k <= ROW_LIST;
+    const bool taken = big && at + k <= BIN_LIST_CAP;
     for (int i = 0; i < k; i++)  // a refused item leaves empty pieces
-        if (at + i < ROW_LIST)
-            list[at + i] = make_int4(tri, l, i * piece, !taken ? 0 : (n - i * piece < piece ? n - i * piece : piece));
+        if (at + i < BIN_LIST_CAP)
+            w.list[at + i] = make_int4(tri, l, i * piece, !taken ? 0 : (n - i * piece < piece ? n - i * piece : piece));
     return taken;
 }
 
 template <typename R>
 __device__ __forceinline__ void rows_levels_body(const DevMesh& m, const DevLevel& d, const RowLevels& rl, int tpw,
-                                                 int32_t* cnt, int2* pairs, int32_t* rank, int64_t cap,
-                                                 int64_t* d_pairs, int4* list, int* list_n, unsigned long long* slots) {
+                                                 const BinWork& w) {
     __shared__ int2 sbuf[APP_BUF];
     __shared__ RowItems<R> I;
     __shared__ uint16_t items[64 * GEO_MAX_LEVELS];  // lane | level index << 6
@@ -561,7 +568,7 @@ __device__ __forceinline__ void rows_levels_body(const DevMesh& m, const DevLeve
     __shared__ int sbase[GEO_MAX_LEVELS];
     const int lane = threadIdx.x;
     if (lane < GEO_MAX_LEVELS) sbase[lane] = rl.base[lane];
-    Appender<false> app{sbuf, 0, pairs, rank, cap, d_pairs, cnt};
+    RowAppender app{sbuf, 0, w};
     Stats st;
     const bool f32v = m.vdtype == GEO_F32;
     const int64_t stride = (int64_t)gridDim.x * tpw;
@@ -601,7 +608,7 @@ __device__ __forceinline__ void rows_levels_body(const DevMesh& m, const DevLeve
             }
             // large items: to the list, or (refused) below by the whole wave
             int nbig = n > ROW_BIG ? n : 0;
-            if (__any(nbig > 0) && list_item(list, list_n, nbig > 0, tri, l, nbig)) nbig = 0;
+            if (__any(nbig > 0) && list_item(w, nbig > 0, tri, l, nbig)) nbig = 0;
             if (n > ROW_BIG) n = 0;
             const int incl = wave_incl_scan(n), total = __shfl(incl, 63, 64);
             __syncthreads();
@@ -628,37 +635,32 @@ __device__ __forceinline__ void rows_levels_body(const DevMesh& m, const DevLeve
         }
     }
     app.flush();
-    row_stats<R>(slots, st);
+    row_stats<R>(w.slots, st);
 }
 
 // float32 form: 3 waves per SIMD; the float64 form keeps its registers (a cap
 // spills it heavily)
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 8)))
-k_rows_levels_f32(DevMesh m, DevLevel d, RowLevels rl, int tpw, int32_t* cnt, int2* pairs, int32_t* rank, int64_t cap,
-                  int64_t* d_pairs, int4* list, int* list_n, unsigned long long* slots) {
-    rows_levels_body<float>(m, d, rl, tpw, cnt, pairs, rank, cap, d_pairs, list, list_n, slots);
+k_rows_levels_f32(DevMesh m, DevLevel d, RowLevels rl, int tpw, BinWork w) {
+    rows_levels_body<float>(m, d, rl, tpw, w);
 }
 
-__global__ void __launch_bounds__(64) k_rows_levels_f64(DevMesh m, DevLevel d, RowLevels rl, int tpw, int32_t* cnt,
-                                                        int2* pairs, int32_t* rank, int64_t cap, int64_t* d_pairs,
-                                                        int4* list, int* list_n, unsigned long long* slots) {
-    rows_levels_body<double>(m, d, rl, tpw, cnt, pairs, rank, cap, d_pairs, list, list_n, slots);
+__global__ void __launch_bounds__(64) k_rows_levels_f64(DevMesh m, DevLevel d, RowLevels rl, int tpw, BinWork w) {
+    rows_levels_body<double>(m, d, rl, tpw, w);
 }
 
 // the listed pieces of large items, one wave per piece, lanes over its lines
 template <typename R>
-__global__ void __launch_bounds__(64) k_rows_pieces(DevMesh m, DevLevel d, RowLevels rl, int32_t* cnt, int2* pairs,
-                                                    int32_t* rank, int64_t cap, int64_t* d_pairs, const int4* list,
-                                                    const int* list_n, unsigned long long* slots) {
+__global__ void __launch_bounds__(64) k_rows_pieces(DevMesh m, DevLevel d, RowLevels rl, BinWork w) {
     __shared__ int2 sbuf[APP_BUF];
     const int lane = threadIdx.x;
-    int np = *list_n;
-    if (np < 0 || np > ROW_LIST) np = ROW_LIST;
+    int np = w.ctl->list_n;
+    if (np < 0 || np > BIN_LIST_CAP) np = BIN_LIST_CAP;
     if ((int)blockIdx.x >= np) return;
-    Appender<false> app{sbuf, 0, pairs, rank, cap, d_pairs, cnt};
+    RowAppender app{sbuf, 0, w};
     Stats st;
     for (int e = blockIdx.x; e < np; e += gridDim.x) {
-        const int4 p = list[e];
+        const int4 p = w.list[e];
         if (p.w <= 0) continue;  // uniform
         const int l = p.y, L = rl.lmin + l;
         const double s = ldexp(1.0, L);
@@ -674,27 +676,34 @@ __global__ void __launch_bounds__(64) k_rows_pieces(DevMesh m, DevLevel d, RowLe
                            p.z + i + lane, app, st);
     }
     app.flush();
-    row_stats<R>(slots, st);
+    row_stats<R>(w.slots, st);
 }
 
-// zero the shared pair counter, the list's counter, the statistics slots and
-// the key counts
-__global__ void k_rows_levels_zero(int64_t* d_pairs, int* list_n, unsigned long long* slots, int32_t* cnt,
-                                   int64_t nkeys) {
+// zero the counters, the statistics slots and the key counts
+__global__ void k_bins_zero(BinWork w, int64_t nkeys) {
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n = (int64_t)gridDim.x * blockDim.x;
     if (i0 == 0) {
-        *d_pairs = 0;
-        *list_n = 0;
+        w.ctl->up = w.ctl->down = 0;
+        w.ctl->list_n = 0;
     }
-    if (slots && blockIdx.x == 0)
-        for (int i = threadIdx.x; i < ROW_SLOTS * ROW_SLOT_WORDS; i += blockDim.x) slots[i] = 0ull;
-    for (int64_t i = i0; i < nkeys; i += n) cnt[i] = 0;
+    if (w.slots && blockIdx.x == 0)
+        for (int i = threadIdx.x; i < ROW_SLOTS * ROW_SLOT_WORDS; i += blockDim.x) w.slots[i] = 0ull;
+    for (int64_t i = i0; i < nkeys; i += n) w.cnt[i] = 0;
+}
+
+// staged pairs are the first `up` and the last `down` of the array
+struct BinPairs {
+    int64_t up, n;
+};
+__device__ __forceinline__ BinPairs staged_pairs(const BinWork& w) {
+    const unsigned long long c = (unsigned long long)w.cap, up = w.ctl->up, down = w.ctl->down;
+    const int64_t u = (int64_t)(up < c ? up : c);
+    return {u, u + (int64_t)(down < c ? down : c)};
 }
 
 // place the pairs of every level: the level of a pair is found from its key;
 // the statistics slots are added to the caller's counters
-__global__ void k_rows_levels_scatter(const int2* pairs, const int32_t* rank, int64_t cap, const int64_t* d_pairs,
-                                      RowLevels rl, const unsigned long long* slots, uint64_t* stats) {
+__global__ void k_rows_levels_scatter(BinWork w, RowLevels rl, uint64_t* stats) {
     __shared__ int sbase[GEO_MAX_LEVELS + 1];
     __shared__ const int32_t* soff[GEO_MAX_LEVELS];
     __shared__ int32_t* sval[GEO_MAX_LEVELS];
@@ -706,18 +715,19 @@ __global__ void k_rows_levels_scatter(const int2* pairs, const int32_t* rank, in
         scap[threadIdx.x] = rl.cap[threadIdx.x];
     }
     __syncthreads();
-    if (slots && blockIdx.x == 0 && threadIdx.x < ROW_SLOTS) {
-        const unsigned long long fb = slots[threadIdx.x * ROW_SLOT_WORDS], ex = slots[threadIdx.x * ROW_SLOT_WORDS + 1];
+    if (w.slots && blockIdx.x == 0 && threadIdx.x < ROW_SLOTS) {
+        const unsigned long long fb = w.slots[threadIdx.x * ROW_SLOT_WORDS],
+                                 ex = w.slots[threadIdx.x * ROW_SLOT_WORDS + 1];
         if (fb) atomicAdd((unsigned long long*)&stats[GEO_STAT_F32_TO_F64], fb);
         if (ex) atomicAdd((unsigned long long*)&stats[GEO_STAT_EXACT], ex);
     }
-    const int64_t n0 = *d_pairs;
-    const int64_t n = n0 < cap ? n0 : cap;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int2 p = pairs[i];
+    const BinPairs bp = staged_pairs(w);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < bp.n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t at = i < bp.up ? i : w.cap - 1 - (i - bp.up);
+        const int2 p = w.pairs[at];
         int l = 0;
         for (int q = 1; q < rl.nlev; q++) l += p.x >= sbase[q] ? 1 : 0;
-        const int64_t pos = (int64_t)soff[l][p.x - sbase[l]] + rank[i];
+        const int64_t pos = (int64_t)soff[l][p.x - sbase[l]] + w.rank[at];
         if (pos >= 0 && pos < scap[l]) sval[l][pos] = p.y;
     }
 }
@@ -727,39 +737,20 @@ __global__ void k_rows_levels_scatter(const int2* pairs, const int32_t* rank, in
 // margins so that rounding can only add candidates)
 // ------------------------------------------------------------------------
 
-// Per-triangle quantities of the separating-axis test.
-struct SatTri {
-    double v[3][3];
-    double e[3][3];  // edges v1-v0, v2-v1, v0-v2
-    double n[3];     // e0 x e1 (rounded; any vector is a valid separating axis)
-    double nvmin, nvmax;  // min / max over the vertices of n . v
-    double nvabs;    // max over the vertices of sum_a |n_a v_a|
-    double n1;       // |n|_1
-    float ef[3][3];  // e rounded to float, for the edge axes
+// Triangles of a wave's batch, with the quantities of the separating-axis test
+// (V: the vertices' own type).  Field-major in LDS: lane i writes triangle i,
+// any lane reads any triangle.
+template <typename V>
+struct LinkItems {
+    V v[9][64];
+    double n[3][64];                // e0 x e1 (rounded; any vector is a valid separating axis)
+    double nvmin[64], nvmax[64];    // min / max over the vertices of n . v
+    double nrad[64];                // radius of the block's reach along n, with its margins
+    int lo[3][64];                  // candidate blocks: lo + (0..sx-1, 0..sy-1, ..)
+    int sx[64], sy[64];
+    int ix[64], iy[64];             // ceil(65536 / sx), ceil(65536 / sy)
+    int pre[64];                    // number of the triangle's first pair
 };
-
-__device__ __forceinline__ void sat_setup(SatTri& T) {
-    for (int a = 0; a < 3; a++) {
-        T.e[0][a] = T.v[1][a] - T.v[0][a];
-        T.e[1][a] = T.v[2][a] - T.v[1][a];
-        T.e[2][a] = T.v[0][a] - T.v[2][a];
-    }
-    T.n[0] = T.e[0][1] * T.e[1][2] - T.e[0][2] * T.e[1][1];
-    T.n[1] = T.e[0][2] * T.e[1][0] - T.e[0][0] * T.e[1][2];
-    T.n[2] = T.e[0][0] * T.e[1][1] - T.e[0][1] * T.e[1][0];
-    T.nvmin = 1e300;
-    T.nvmax = -1e300;
-    T.nvabs = 0.0;
-    for (int i = 0; i < 3; i++) {
-        const double p = T.n[0] * T.v[i][0] + T.n[1] * T.v[i][1] + T.n[2] * T.v[i][2];
-        T.nvmin = fmin(T.nvmin, p);
-        T.nvmax = fmax(T.nvmax, p);
-        T.nvabs = fmax(T.nvabs, fabs(T.n[0] * T.v[i][0]) + fabs(T.n[1] * T.v[i][1]) + fabs(T.n[2] * T.v[i][2]));
-    }
-    T.n1 = fabs(T.n[0]) + fabs(T.n[1]) + fabs(T.n[2]);
-    for (int i = 0; i < 3; i++)
-        for (int a = 0; a < 3; a++) T.ef[i][a] = (float)T.e[i][a];
-}
 
 // Conservative triangle / cube overlap (centre c, half side hs): separating
 // axes are the box normals, the triangle normal and the nine edge crosses,
@@ -767,13 +758,14 @@ __device__ __forceinline__ void sat_setup(SatTri& T) {
 // are the candidate range itself (the caller enumerates exactly the blocks
 // whose widened box meets the triangle's bounding box); stage one takes the
 // triangle normal, stage two the edges.
-__device__ bool tri_box_stage1(const double c[3], double hs, const SatTri& T) {
+template <typename V>
+__device__ __forceinline__ bool tri_box_stage1(const double c[3], const LinkItems<V>& I, int i) {
     // the normal axis: projections n . v_i - n . c against the box radius; the
     // margin bounds the rounding of the dot products (4.5 u each side)
-    const double nc = T.n[0] * c[0] + T.n[1] * c[1] + T.n[2] * c[2];
-    const double err = 5e-16 * (T.nvabs + fabs(T.n[0] * c[0]) + fabs(T.n[1] * c[1]) + fabs(T.n[2] * c[2]));
-    const double rn = hs * T.n1 * (1.0 + 1e-9) + 1e-12 * T.n1 + err;
-    return !(T.nvmin - nc > rn || T.nvmax - nc < -rn);
+    const double p0 = I.n[0][i] * c[0], p1 = I.n[1][i] * c[1], p2 = I.n[2][i] * c[2];
+    const double nc = p0 + p1 + p2;
+    const double rn = I.nrad[i] + 5e-16 * (fabs(p0) + fabs(p1) + fabs(p2));
+    return !(I.nvmin[i] - nc > rn || I.nvmax[i] - nc < -rn);
 }
 
 // The nine edge axes in float.  The vertices relative to the centre,
@@ -785,136 +777,303 @@ __device__ bool tri_box_stage1(const double c[3], double hs, const SatTri& T) {
 // by a relative 1e-5 for its own rounding, so an axis is only taken as
 // separating where it separates the exact figures; the 1e-30 floor covers
 // products that underflow.
-__device__ bool tri_box_stage2(const double c[3], double hs, const SatTri& T) {
+template <typename V>
+__device__ __forceinline__ bool tri_box_stage2(const double c[3], double hs, const LinkItems<V>& I, int i) {
+    double v[3][3];
     float w[3][3];
     float wmax = 0.0f;
     for (int k = 0; k < 3; k++)
         for (int a = 0; a < 3; a++) {
-            w[k][a] = (float)(T.v[k][a] - c[a]);
+            v[k][a] = (double)I.v[3 * k + a][i];
+            w[k][a] = (float)(v[k][a] - c[a]);
             wmax = fmaxf(wmax, fabsf(w[k][a]));
         }
     const float hsf = (float)hs * (1.0f + 1e-5f) + 1e-6f * wmax + 1e-30f;
-    // axis = e_box(a) x e(i), nonzero in components b1 = a+1 and b2 = a+2
-    for (int i = 0; i < 3; i++) {
+    // axis = e_box(a) x e(k), nonzero in components b1 = a+1 and b2 = a+2
+    bool hit = true;
+    for (int k = 0; k < 3; k++) {
+        float e[3];
+        for (int a = 0; a < 3; a++) e[a] = (float)(v[(k + 1) % 3][a] - v[k][a]);
         for (int a = 0; a < 3; a++) {
             const int b1 = (a + 1) % 3, b2 = (a + 2) % 3;
-            const float x1 = -T.ef[i][b2], x2 = T.ef[i][b1];
+            const float x1 = -e[b2], x2 = e[b1];
             const float p0 = x1 * w[0][b1] + x2 * w[0][b2];
             const float p1 = x1 * w[1][b1] + x2 * w[1][b2];
             const float p2 = x1 * w[2][b1] + x2 * w[2][b2];
             const float r = hsf * (fabsf(x1) + fabsf(x2));
             const float mn = fminf(p0, fminf(p1, p2)), mx = fmaxf(p0, fmaxf(p1, p2));
-            if (mn > r || mx < -r) return false;
+            hit &= !(mn > r || mx < -r);
         }
     }
-    return true;
+    return hit;
 }
 
-// candidates of a triangle tested (and looked up) together
+// The LINKS pass.  A wave takes a batch of up to 64 triangles, one per lane for
+// the set-up (kept in LDS); their (triangle, candidate block) pairs are then
+// numbered through and every lane takes LINKS_U pairs at a time, whatever
+// triangle they are of, so that their forest descents overlap.  Bound by VALU
+// work and by the latency of the descents.  A triangle with more than LINK_BIG
+// candidates is cut into pieces for a second launch, as in the ROWS pass.
+// Before (one lane per triangle, its candidates in turn) and now: 0.82 and
+// 0.64 ms on 7.2M triangles (24.3M entries), 163 and 79 us on 112k, 103 and 17
+// us on 1,792, 3.3 and 0.02 ms on a 1,024-triangle cylinder.  Two counters
+// instead of one and buffers of 512 instead of 1,024 pairs are 0.15 ms of it.
 constexpr int LINKS_U = 4;
+constexpr int LINK_BIG = 128;      // (below 256: ix and iy divide exactly)
+constexpr int LINK_PIECES = 64;    // most pieces of a triangle
+constexpr int64_t LINK_PIECE_MAX = 1 << 30;
 
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) k_links_pass1(DevMesh m, DevLevel d, int32_t* cnt, int2* pairs, int32_t* rank,
-                                                    int64_t cap, int64_t* d_count) {
+using LinkAppender = Appender<true>;
+
+struct LinkGrid {  // block geometry of the level
+    int L, nb[3], nb0[3];
+    double h, bw, ibw, hs;
+};
+__device__ __forceinline__ LinkGrid link_grid(const DevLevel& d) {
+    LinkGrid g;
+    g.L = d.level;
+    g.h = ldexp(1.0, -g.L);
+    g.bw = 4.0 * g.h;
+    g.ibw = ldexp(1.0, g.L - 2);  // 1 / bw, exact
+    // half side of the box [4bh - h/2, 4(b+1)h + h/2] that the block's links reach
+    g.hs = (0.5 * g.bw + 0.5 * g.h) * (1.0 + 1e-9);
+    for (int a = 0; a < 3; a++) {
+        g.nb0[a] = d.n0[a] >> 2;
+        g.nb[a] = g.nb0[a] << g.L;
+    }
+    return g;
+}
+
+// Set-up of triangle t as item i: its candidate range and the data of the
+// tests.  Returns the number of candidates (0 for zero area).
+template <typename V>
+__device__ __forceinline__ int64_t link_setup(const DevMesh& m, int64_t t, const LinkGrid& g, LinkItems<V>& I, int i) {
+    double v[3][3];
+    for (int k = 0; k < 3; k++) {
+        const int vid = m.tris[3 * t + k];
+        for (int a = 0; a < 3; a++) {
+            const V x = static_cast<const V*>(m.verts)[3 * (int64_t)vid + a];
+            I.v[3 * k + a][i] = x;
+            v[k][a] = (double)x;
+        }
+    }
+    // zero-area triangles never meet a segment: exact test (all three
+    // coordinate-plane projections have zero area)
+    if (orient2d_filter<double>(v[0][1], v[0][2], v[1][1], v[1][2], v[2][1], v[2][2], 0.0) == 0 &&
+        orient2d_filter<double>(v[0][2], v[0][0], v[1][2], v[1][0], v[2][2], v[2][0], 0.0) == 0 &&
+        orient2d_filter<double>(v[0][0], v[0][1], v[1][0], v[1][1], v[2][0], v[2][1], 0.0) == 0 &&
+        orient2d_exact(v[0][1], v[0][2], v[1][1], v[1][2], v[2][1], v[2][2]) == 0 &&
+        orient2d_exact(v[0][2], v[0][0], v[1][2], v[1][0], v[2][2], v[2][0]) == 0 &&
+        orient2d_exact(v[0][0], v[0][1], v[1][0], v[1][1], v[2][0], v[2][1]) == 0)
+        return 0;
+    double e0[3], e1[3], n[3];
+    for (int a = 0; a < 3; a++) {
+        e0[a] = v[1][a] - v[0][a];
+        e1[a] = v[2][a] - v[1][a];
+    }
+    n[0] = e0[1] * e1[2] - e0[2] * e1[1];
+    n[1] = e0[2] * e1[0] - e0[0] * e1[2];
+    n[2] = e0[0] * e1[1] - e0[1] * e1[0];
+    double nvmin = 1e300, nvmax = -1e300, nvabs = 0.0;
+    for (int k = 0; k < 3; k++) {
+        const double p = n[0] * v[k][0] + n[1] * v[k][1] + n[2] * v[k][2];
+        nvmin = fmin(nvmin, p);
+        nvmax = fmax(nvmax, p);
+        nvabs = fmax(nvabs, fabs(n[0] * v[k][0]) + fabs(n[1] * v[k][1]) + fabs(n[2] * v[k][2]));
+    }
+    const double n1 = fabs(n[0]) + fabs(n[1]) + fabs(n[2]);
+    I.nvmin[i] = nvmin;
+    I.nvmax[i] = nvmax;
+    I.nrad[i] = g.hs * n1 * (1.0 + 1e-9) + 1e-12 * n1 + 5e-16 * nvabs;
+    int sz[3];
+    for (int a = 0; a < 3; a++) {
+        I.n[a][i] = n[a];
+        const double mn = fmin(v[0][a], fmin(v[1][a], v[2][a])), mx = fmax(v[0][a], fmax(v[1][a], v[2][a]));
+        // block b's links reach [4bh - h/2, 4bh + 4.5h]: it meets
+        // [mn, mx] iff (mn - 4.5h) / bw <= b <= (mx + h/2) / bw (the
+        // roundings are monotone and bw is a power of two; the 1e-7
+        // only widens the range)
+        int lo = (int)ceil((mn - 4.5 * g.h) * g.ibw - 1e-7);
+        int hi = (int)floor((mx + 0.5 * g.h) * g.ibw + 1e-7);
+        lo = lo < 0 ? 0 : lo;
+        hi = hi > g.nb[a] - 1 ? g.nb[a] - 1 : hi;
+        I.lo[a][i] = lo;
+        sz[a] = hi - lo + 1;
+    }
+    if (sz[0] <= 0 || sz[1] <= 0 || sz[2] <= 0) return 0;
+    I.sx[i] = sz[0];
+    I.sy[i] = sz[1];
+    I.ix[i] = (65535 + sz[0]) / sz[0];
+    I.iy[i] = (65535 + sz[1]) / sz[1];
+    return (int64_t)sz[0] * sz[1] * sz[2];
+}
+
+// LINKS_U pairs per lane (item i[u], candidate block b[u], on[u]) through both
+// tests and down the forest; the blocks found are appended
+template <typename V>
+__device__ __forceinline__ void link_pairs(const DevLevel& d, const LinkGrid& g, const LinkItems<V>& I,
+                                           const bool on[LINKS_U], const int i[LINKS_U], const int b[LINKS_U][3],
+                                           const int32_t tri[LINKS_U], LinkAppender& app) {
+    int idx[LINKS_U];
+#pragma unroll
+    for (int u = 0; u < LINKS_U; u++) {
+        idx[u] = -1;
+        if (on[u]) {
+            const double c[3] = {(b[u][0] + 0.5) * g.bw, (b[u][1] + 0.5) * g.bw, (b[u][2] + 0.5) * g.bw};
+            if (tri_box_stage1<V>(c, I, i[u]) && tri_box_stage2<V>(c, g.hs, I, i[u]))
+                idx[u] = (b[u][0] >> g.L) + g.nb0[0] * ((b[u][1] >> g.L) + g.nb0[1] * (b[u][2] >> g.L));
+        }
+    }
+    for (int l = 0; l < g.L; l++) {
+        int ch[LINKS_U];
+        const int sh = g.L - 1 - l;
+#pragma unroll
+        for (int u = 0; u < LINKS_U; u++) ch[u] = idx[u] >= 0 ? d.child[l][idx[u]] : -1;
+#pragma unroll
+        for (int u = 0; u < LINKS_U; u++)
+            idx[u] = ch[u] < 0 ? -1
+                               : ch[u] + (((b[u][0] >> sh) & 1) | (((b[u][1] >> sh) & 1) << 1) |
+                                          (((b[u][2] >> sh) & 1) << 2));
+    }
+#pragma unroll
+    for (int u = 0; u < LINKS_U; u++) app.add(idx[u] >= 0, idx[u], tri[u]);
+}
+
+// candidates first .. first + count - 1 of item i (its candidate box by
+// divisions), by the whole wave
+template <typename V>
+__device__ void link_range(const DevLevel& d, const LinkGrid& g, const LinkItems<V>& I, int i, int32_t t, int64_t first,
+                           int64_t count, LinkAppender& app) {
+    const int lane = threadIdx.x;
+    const int64_t sx = I.sx[i], sy = I.sy[i];
+    for (int64_t q0 = 0; q0 < count; q0 += 64 * LINKS_U) {  // uniform
+        bool on[LINKS_U];
+        int item[LINKS_U], b[LINKS_U][3];
+        int32_t tri[LINKS_U];
+#pragma unroll
+        for (int u = 0; u < LINKS_U; u++) {
+            const int64_t q = q0 + 64 * u + lane, c = first + q, r = c / sx;
+            on[u] = q < count;
+            item[u] = i;
+            tri[u] = t;
+            b[u][0] = I.lo[0][i] + (int)(c - r * sx);
+            b[u][1] = I.lo[1][i] + (int)(r % sy);
+            b[u][2] = I.lo[2][i] + (int)(r / sy);
+        }
+        link_pairs<V>(d, g, I, on, item, b, tri, app);
+    }
+}
+
+// pieces of a large triangle to the list (triangle, first candidate in 64
+// bits, count); returns whether the list took them
+__device__ __forceinline__ bool list_links(const BinWork& w, int64_t n, int32_t tri) {
+    const int64_t want = ((n + LINK_PIECES - 1) / LINK_PIECES + 127) & ~(int64_t)127;
+    const bool big = n > 0 && want <= LINK_PIECE_MAX;
+    const int k = big ? (int)((n + want - 1) / want) : 0;
+    const int incl = wave_incl_scan(k), total = __shfl(incl, 63, 64);
+    // a full list is not added to any more, so that its counter cannot wrap
+    int at = BIN_LIST_CAP;
+    if (threadIdx.x == 0 && __hip_atomic_load(&w.ctl->list_n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < BIN_LIST_CAP)
+        at = atomicAdd(&w.ctl->list_n, total);
+    at = __shfl(at, 0, 64) + incl - k;
+    const bool taken = big && at + k <= BIN_LIST_CAP;
+    for (int q = 0; q < k; q++) {  // a refused triangle leaves empty pieces
+        const int64_t first = q * want;
+        const int count = taken ? (int)(n - first < want ? n - first : want) : 0;
+        if (at + q < BIN_LIST_CAP) w.list[at + q] = make_int4(tri, (int)(uint32_t)first, (int)(first >> 32), count);
+    }
+    return taken;
+}
+
+template <typename V>
+__global__ void __launch_bounds__(64) k_links_pass1(DevMesh m, DevLevel d, int tpw, BinWork w) {
     __shared__ int2 sbuf[APP_BUF];
-    Appender<true> app{sbuf, 0, pairs, rank, cap, d_count, cnt};
-    const int L = d.level;
-    const double h = ldexp(1.0, -L), bw = 4.0 * h, ibw = ldexp(1.0, L - 2);  // 1 / bw, exact
-    const int nb0[3] = {d.n0[0] >> 2, d.n0[1] >> 2, d.n0[2] >> 2};
-    const int nbx = nb0[0] << L, nby = nb0[1] << L, nbz = nb0[2] << L;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < m.nt; base += stride) {
-        const int64_t t = base + threadIdx.x;
-        SatTri T;
-        double (&v)[3][3] = T.v;
-        int lo[3] = {0, 0, 0}, hi[3] = {-1, -1, -1};
-        bool live = t < m.nt;
-        if (live) {
-            for (int i = 0; i < 3; i++) {
-                const int vid = m.tris[3 * t + i];
-                for (int a = 0; a < 3; a++) v[i][a] = load_coord(m, vid, a);
-            }
-            sat_setup(T);
-            // zero-area triangles never meet a segment: exact test (all three
-            // coordinate-plane projections have zero area)
-            if (orient2d_filter<double>(v[0][1], v[0][2], v[1][1], v[1][2], v[2][1], v[2][2], 0.0) == 0 &&
-                orient2d_filter<double>(v[0][2], v[0][0], v[1][2], v[1][0], v[2][2], v[2][0], 0.0) == 0 &&
-                orient2d_filter<double>(v[0][0], v[0][1], v[1][0], v[1][1], v[2][0], v[2][1], 0.0) == 0 &&
-                orient2d_exact(v[0][1], v[0][2], v[1][1], v[1][2], v[2][1], v[2][2]) == 0 &&
-                orient2d_exact(v[0][2], v[0][0], v[1][2], v[1][0], v[2][2], v[2][0]) == 0 &&
-                orient2d_exact(v[0][0], v[0][1], v[1][0], v[1][1], v[2][0], v[2][1]) == 0)
-                live = false;
-        }
-        if (live) {
-            const int nb[3] = {nbx, nby, nbz};
-            for (int a = 0; a < 3; a++) {
-                const double mn = fmin(v[0][a], fmin(v[1][a], v[2][a])), mx = fmax(v[0][a], fmax(v[1][a], v[2][a]));
-                // block b's links reach [4bh - h/2, 4bh + 4.5h]: it meets
-                // [mn, mx] iff (mn - 4.5h) / bw <= b <= (mx + h/2) / bw (the
-                // roundings are monotone and bw is a power of two; the 1e-7
-                // only widens the range)
-                lo[a] = (int)ceil((mn - 4.5 * h) * ibw - 1e-7);
-                hi[a] = (int)floor((mx + 0.5 * h) * ibw + 1e-7);
-                lo[a] = lo[a] < 0 ? 0 : lo[a];
-                hi[a] = hi[a] > nb[a] - 1 ? nb[a] - 1 : hi[a];
-            }
-        }
-        const int sx = hi[0] - lo[0] + 1, sy = hi[1] - lo[1] + 1, sz = hi[2] - lo[2] + 1;
-        const int64_t n = (sx > 0 && sy > 0 && sz > 0) ? (int64_t)sx * sy * sz : 0;
-        const double hs = (0.5 * bw + 0.5 * h) * (1.0 + 1e-9);
-        // candidate block: box [4bh - h/2, 4(b+1)h + h/2] reached by the
-        // block's links, plus a relative margin.  The candidates through both
-        // stages, LINKS_U at a time (a triangle has a few: its widened box
-        // spans one or two blocks per axis), enumerated x fastest by a cursor;
-        // the forest lookups of the LINKS_U candidates descend together, so
-        // their dependent loads overlap.
-        int cur[3] = {lo[0], lo[1], lo[2]};
-        for (int64_t it0 = 0; __any(it0 < n); it0 += LINKS_U) {
-            int bb[LINKS_U][3], idx[LINKS_U];
+    __shared__ LinkItems<V> I;
+    __shared__ int mark[64 * LINKS_U];
+    const int lane = threadIdx.x;
+    LinkAppender app{sbuf, 0, w};
+    const LinkGrid g = link_grid(d);
+    const int64_t stride = (int64_t)gridDim.x * tpw;
+    for (int64_t base = (int64_t)blockIdx.x * tpw; base < m.nt; base += stride) {
+        const int64_t t = base + lane;
+        int64_t nall = 0;
+        __syncthreads();
+        if (lane < tpw && t < m.nt) nall = link_setup<V>(m, t, g, I, lane);
+        int64_t nbig = nall > LINK_BIG ? nall : 0;
+        if (__any(nbig > 0) && list_links(w, nbig, (int32_t)t)) nbig = 0;
+        const int n = nall > LINK_BIG ? 0 : (int)nall;
+        const int incl = wave_incl_scan(n), total = __shfl(incl, 63, 64);
+        I.pre[lane] = incl - n;
+        for (int done = 0; done < total; done += 64 * LINKS_U) {  // uniform
+            // triangle of each pair: its number where its pairs start (or the
+            // chunk does), carried on by a prefix maximum
+#pragma unroll
+            for (int u = 0; u < LINKS_U; u++) mark[64 * u + lane] = 0;
+            __syncthreads();
+            if (n > 0 && incl > done && incl - n < done + 64 * LINKS_U)
+                mark[incl - n > done ? incl - n - done : 0] = lane;
+            __syncthreads();
+            bool on[LINKS_U];
+            int item[LINKS_U], b[LINKS_U][3];
+            int32_t tri[LINKS_U];
+            int last = 0;
 #pragma unroll
             for (int u = 0; u < LINKS_U; u++) {
-                idx[u] = -1;
-                bb[u][0] = cur[0];
-                bb[u][1] = cur[1];
-                bb[u][2] = cur[2];
-                if (it0 + u < n) {
-                    const double c[3] = {(cur[0] + 0.5) * bw, (cur[1] + 0.5) * bw, (cur[2] + 0.5) * bw};
-                    if (tri_box_stage1(c, hs, T) && tri_box_stage2(c, hs, T))
-                        idx[u] = (cur[0] >> L) + nb0[0] * ((cur[1] >> L) + nb0[1] * (cur[2] >> L));
-                }
-                if (++cur[0] > hi[0]) {
-                    cur[0] = lo[0];
-                    if (++cur[1] > hi[1]) {
-                        cur[1] = lo[1];
-                        ++cur[2];
-                    }
-                }
+                const int own = wave_incl_max(mark[64 * u + lane]);
+                const int i = own > last ? own : last;
+                last = __shfl(i, 63, 64);
+                const int p = done + 64 * u + lane;
+                on[u] = p < total;
+                item[u] = i;
+                tri[u] = (int32_t)base + i;
+                // candidate c = x + sx (y + sy z), c < LINK_BIG
+                const int c = on[u] ? p - I.pre[i] : 0;
+                const int r = (c * I.ix[i]) >> 16, z = (r * I.iy[i]) >> 16;
+                b[u][0] = I.lo[0][i] + c - r * I.sx[i];
+                b[u][1] = I.lo[1][i] + r - z * I.sy[i];
+                b[u][2] = I.lo[2][i] + z;
             }
-            for (int l = 0; l < L; l++) {
-                int ch[LINKS_U];
-                const int sh = L - 1 - l;
-#pragma unroll
-                for (int u = 0; u < LINKS_U; u++) ch[u] = idx[u] >= 0 ? d.child[l][idx[u]] : -1;
-#pragma unroll
-                for (int u = 0; u < LINKS_U; u++)
-                    idx[u] = ch[u] < 0 ? -1
-                                       : ch[u] + (((bb[u][0] >> sh) & 1) | (((bb[u][1] >> sh) & 1) << 1) |
-                                                  (((bb[u][2] >> sh) & 1) << 2));
-            }
-#pragma unroll
-            for (int u = 0; u < LINKS_U; u++) app.add(idx[u] >= 0, idx[u], (int32_t)t);
+            link_pairs<V>(d, g, I, on, item, b, tri, app);
+        }
+        unsigned long long rest = __ballot(nbig > 0);  // refused by the list: by the whole wave
+        if (rest) __syncthreads();
+        while (rest) {  // uniform
+            const int i = __ffsll(rest) - 1;
+            rest &= rest - 1;
+            link_range<V>(d, g, I, i, (int32_t)base + i, 0, __shfl((long long)nbig, i, 64), app);
         }
     }
     app.flush();
 }
 
-__global__ void k_bins_scatter(const int2* pairs, const int32_t* rank, int64_t cap, const int64_t* d_count,
-                               const int32_t* off, int32_t* val) {
-    const int64_t n0 = *d_count;
-    const int64_t n = n0 < cap ? n0 : cap;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int2 p = pairs[i];
-        const int64_t pos = (int64_t)off[p.x] + rank[i];
-        if (pos >= 0 && pos < cap) val[pos] = p.y;
+// the listed pieces of large triangles, one wave per piece
+template <typename V>
+__global__ void __launch_bounds__(64) k_links_pieces(DevMesh m, DevLevel d, BinWork w) {
+    __shared__ int2 sbuf[APP_BUF];
+    __shared__ LinkItems<V> I;
+    int np = w.ctl->list_n;
+    if (np < 0 || np > BIN_LIST_CAP) np = BIN_LIST_CAP;
+    if ((int)blockIdx.x >= np) return;
+    LinkAppender app{sbuf, 0, w};
+    const LinkGrid g = link_grid(d);
+    for (int e = blockIdx.x; e < np; e += gridDim.x) {
+        const int4 p = w.list[e];
+        if (p.w <= 0) continue;  // uniform
+        __syncthreads();
+        if (threadIdx.x == 0) link_setup<V>(m, p.x, g, I, 0);
+        __syncthreads();
+        link_range<V>(d, g, I, 0, p.x, (int64_t)(((uint64_t)(uint32_t)p.z << 32) | (uint32_t)p.y), p.w, app);
+    }
+    app.flush();
+}
+
+__global__ void k_bins_scatter(BinWork w, const int32_t* off, int32_t* val) {
+    const BinPairs bp = staged_pairs(w);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < bp.n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t at = i < bp.up ? i : w.cap - 1 - (i - bp.up);
+        const int2 p = w.pairs[at];
+        const int64_t pos = (int64_t)off[p.x] + w.rank[at];
+        if (pos >= 0 && pos < w.cap) val[pos] = p.y;
     }
 }
 
@@ -941,12 +1100,12 @@ inline unsigned grid_for(int64_t n, int threads, int64_t maxg = 1 << 16) {
 
 }  // namespace
 
-int launch_rows_levels(const DevMesh& m, const DevLevel& d, int precision, const RowLevels& rl, const RowWork& w,
+int launch_rows_levels(const DevMesh& m, const DevLevel& d, int precision, const RowLevels& rl, const BinWork& w,
                        hipStream_t s) {
     if (m.nt == 0) return GEO_OK;
     const bool f32 = precision == GEO_PREC_F32_FALLBACK;
     // triangles per wave: 64, fewer where that would leave the chip idle (below
-    // 4,096 waves; 112k triangles: 98 us, 136 with 2,048 waves, 0.16 ms with 64
+    // 4,096 waves; 112k triangles: 86 us, 136 with 2,048 waves, 0.16 ms with 64
     // each), but 4 at least (1,792 triangles: 22 us, 29 with 2)
     const int64_t per = (m.nt + 4095) / 4096;
     const int tpw = per < 4 ? 4 : (per > 64 ? 64 : (int)per);
@@ -956,42 +1115,47 @@ int launch_rows_levels(const DevMesh& m, const DevLevel& d, int precision, const
     const unsigned g = grid_for(m.nt, tpw, f32 ? 16384 : 8192);
     kt_record(GEO_KT_ROWS, s, false);
     auto pass = f32 ? k_rows_levels_f32 : k_rows_levels_f64;
-    pass<<<g, 64, 0, s>>>(m, d, rl, tpw, w.cnt, w.pairs, w.rank, w.cap, w.d_pairs, w.list, w.list_n, w.slots);
+    pass<<<g, 64, 0, s>>>(m, d, rl, tpw, w);
     kt_record(GEO_KT_ROWS, s, true);
     auto pieces = f32 ? k_rows_pieces<float> : k_rows_pieces<double>;
-    pieces<<<2048, 64, 0, s>>>(m, d, rl, w.cnt, w.pairs, w.rank, w.cap, w.d_pairs, w.list, w.list_n, w.slots);
+    pieces<<<2048, 64, 0, s>>>(m, d, rl, w);
     GEO_LAUNCH_CHECK();
     return GEO_OK;
 }
 
-int launch_rows_levels_zero(const RowWork& w, int64_t nkeys, hipStream_t s) {
-    k_rows_levels_zero<<<grid_for(nkeys, 256, 16384), 256, 0, s>>>(w.d_pairs, w.list_n, w.slots, w.cnt, nkeys);
+int launch_bins_zero(const BinWork& w, int64_t nkeys, hipStream_t s) {
+    k_bins_zero<<<grid_for(nkeys, 256, 16384), 256, 0, s>>>(w, nkeys);
     GEO_LAUNCH_CHECK();
     return GEO_OK;
 }
 
-int launch_rows_levels_scatter(const RowLevels& rl, const RowWork& w, uint64_t* d_stats, hipStream_t s) {
-    if (w.cap <= 0 && !d_stats) return GEO_OK;
-    k_rows_levels_scatter<<<grid_for(w.cap, 256, 8192), 256, 0, s>>>(w.pairs, w.rank, w.cap, w.d_pairs, rl,
-                                                                     d_stats ? w.slots : nullptr, d_stats);
+int launch_rows_levels_scatter(const RowLevels& rl, const BinWork& w, uint64_t* d_stats, hipStream_t s) {
+    if (w.cap <= 0 && !w.slots) return GEO_OK;
+    k_rows_levels_scatter<<<grid_for(w.cap, 256, 8192), 256, 0, s>>>(w, rl, d_stats);
     GEO_LAUNCH_CHECK();
     return GEO_OK;
 }
 
-int launch_links_pass1(const DevMesh& m, const DevLevel& d, int32_t* cnt, int2* pairs, int32_t* rank,
-                       int64_t cap, int64_t* d_count, hipStream_t s) {
+int launch_links_pass1(const DevMesh& m, const DevLevel& d, const BinWork& w, hipStream_t s) {
     if (m.nt == 0) return GEO_OK;
+    // triangles per wave, as in the ROWS pass
+    const int64_t per = (m.nt + 4095) / 4096;
+    const int tpw = per < 4 ? 4 : (per > 64 ? 64 : (int)per);
+    const bool f32 = m.vdtype == GEO_F32;
     kt_record(GEO_KT_LINKS_BINS, s, false);
-    k_links_pass1<<<grid_for(m.nt, 64, 16384), 64, 0, s>>>(m, d, cnt, pairs, rank, cap, d_count);
+    auto pass = f32 ? k_links_pass1<float> : k_links_pass1<double>;
+    // (7.2M triangles: 0.64 ms; 0.68 with at most 8,192 workgroups)
+    pass<<<grid_for(m.nt, tpw, 16384), 64, 0, s>>>(m, d, tpw, w);
     kt_record(GEO_KT_LINKS_BINS, s, true);
+    auto pieces = f32 ? k_links_pieces<float> : k_links_pieces<double>;
+    pieces<<<2048, 64, 0, s>>>(m, d, w);
     GEO_LAUNCH_CHECK();
     return GEO_OK;
 }
 
-int launch_bins_scatter(const int2* pairs, const int32_t* rank, int64_t cap, const int64_t* d_count,
-                        const int32_t* off, int32_t* val, hipStream_t s) {
-    if (cap <= 0) return GEO_OK;
-    k_bins_scatter<<<grid_for(cap, 256, 8192), 256, 0, s>>>(pairs, rank, cap, d_count, off, val);
+int launch_bins_scatter(const BinWork& w, const int32_t* off, int32_t* val, hipStream_t s) {
+    if (w.cap <= 0) return GEO_OK;
+    k_bins_scatter<<<grid_for(w.cap, 256, 8192), 256, 0, s>>>(w, off, val);
     GEO_LAUNCH_CHECK();
     return GEO_OK;
 }

@@ -293,8 +293,6 @@ __device__ __forceinline__ void wave_count(uint64_t* ctr, unsigned n) {
 // kernel timer is on for that kernel (no-op otherwise)
 void kt_record(int kernel, hipStream_t s, bool stop);
 
-// zero *one and p[0..n-1] (one launch)
-int geo_zero_counts(uint64_t* one, int32_t* p, int64_t n, hipStream_t s);
 // exclusive scans of up to GEO_MAX_LEVELS arrays together: out[0..len-1] =
 // prefix sums of in, out[len] = total, *total (if given) = the total in 64
 // bits.  in and out must not overlap.  partials: geo_scan_partials_bytes of
@@ -330,28 +328,30 @@ struct RowLevels {
     int32_t* val[GEO_MAX_LEVELS];
     int64_t cap[GEO_MAX_LEVELS];
 };
-// scratch of a ROWS build: counts per key, staged pairs with their ranks and
-// their number, pieces of large items, statistics slots (NULL: no statistics)
-constexpr int ROW_LIST_CAP = 65536;
+// scratch of a bin build: counts per key, staged pairs with their ranks, the
+// counters, pieces of large triangles, statistics slots (NULL: no statistics)
+constexpr int BIN_LIST_CAP = 65536;
 constexpr int ROW_SLOTS = 64, ROW_SLOT_WORDS = 16;
-struct RowWork {
+struct BinCtl {  // a cache line each
+    alignas(128) unsigned long long up;    // pairs staged from the array's start
+    alignas(128) unsigned long long down;  // and from its end
+    alignas(128) int list_n;               // listed pieces
+};
+struct BinWork {
     int32_t* cnt;
     int2* pairs;
     int32_t* rank;
     int64_t cap;
-    int64_t* d_pairs;
+    BinCtl* ctl;
     int4* list;
-    int* list_n;
     unsigned long long* slots;
 };
-int launch_rows_levels(const DevMesh& m, const DevLevel& d, int precision, const RowLevels& rl, const RowWork& w,
+int launch_bins_zero(const BinWork& w, int64_t nkeys, hipStream_t s);
+int launch_rows_levels(const DevMesh& m, const DevLevel& d, int precision, const RowLevels& rl, const BinWork& w,
                        hipStream_t s);
-int launch_rows_levels_zero(const RowWork& w, int64_t nkeys, hipStream_t s);
-int launch_rows_levels_scatter(const RowLevels& rl, const RowWork& w, uint64_t* d_stats, hipStream_t s);
-int launch_links_pass1(const DevMesh& m, const DevLevel& d, int32_t* cnt, int2* pairs, int32_t* rank,
-                       int64_t cap, int64_t* d_count, hipStream_t s);
-int launch_bins_scatter(const int2* pairs, const int32_t* rank, int64_t cap, const int64_t* d_count,
-                        const int32_t* off, int32_t* val, hipStream_t s);
+int launch_rows_levels_scatter(const RowLevels& rl, const BinWork& w, uint64_t* d_stats, hipStream_t s);
+int launch_links_pass1(const DevMesh& m, const DevLevel& d, const BinWork& w, hipStream_t s);
+int launch_bins_scatter(const BinWork& w, const int32_t* off, int32_t* val, hipStream_t s);
 int launch_check_mesh(const DevMesh& m, const DevLevel& d, uint64_t* d_stats, hipStream_t s);
 size_t geo_dense_ws_bytes(int64_t nb);
 int launch_links_dense(int64_t nb, int64_t n_links, const int32_t* link_cell, const uint8_t* link_dir,
