@@ -45,6 +45,11 @@ namespace {
 
 constexpr int CL_CAND = 64;  // candidates staged per round
 constexpr int CL_MAXC = 8;   // pairs per link and flattening round
+// a wave's tasks: at least CL_RUN in a row, so that the candidates of several
+// small blocks are staged together, but fewer where that would leave fewer
+// than CL_WAVES waves (224k tasks: 459 us with 32,768 waves, 480 with 16,384,
+// 511 with 8,192; 511k tasks, float64 form: 1.31 ms with 16, 1.34 with 4)
+constexpr int CL_RUN = 16, CL_WAVES = 32768;
 
 __device__ __forceinline__ void dirvec(int k, int& cx, int& cy, int& cz) {
     cx = k % 3 - 1;
@@ -869,6 +874,70 @@ __device__ __forceinline__ int64_t advance_block(const int32_t* task_off, int64_
     }
 }
 
+// What the q kernel stages at once (staging takes the wave a thousand VALU
+// instructions, whether 6 or 64 lanes hold a candidate; block by block it was
+// over half of the kernel where triangles are as large as cells): chunk `chunk` of block b0's candidates when
+// the block has more than CL_CAND (chunk >= 0), else all candidates of n
+// consecutive blocks from b0 on that fit CL_CAND together.  Per block before,
+// and now: 575 and 459 us on a 112k-triangle star (6 candidates per block), 1.73
+// and 1.31 ms on 64 spheres (14, float64 form), 2.84 and 2.76 ms on the 7.2M
+// star (37).
+struct CandUnit {
+    int64_t b0;
+    int n, chunk;
+    int pack;      // lane i: first slot | count << 8 of block b0 + i (group)
+    int blk;       // lane i: block of candidate slot i, less b0
+    int tri;       // lane i: its triangle (-1: none)
+};
+
+// The unit that starts with `task` of block b, and its triangle ids; a group
+// takes blocks with tasks before t1 only.  By the whole wave; mark: 64 bytes
+// of LDS.
+__device__ __forceinline__ CandUnit plan_unit(int64_t nb, int64_t b, int task, int t1, const int32_t* task_off,
+                                              const int32_t* blk_off, const int32_t* loff, const int32_t* lval,
+                                              int64_t lcap, unsigned char* mark) {
+    const int lane = threadIdx.x;
+    CandUnit u;
+    u.b0 = b;
+    u.n = 1;
+    u.chunk = -1;
+    u.pack = u.blk = 0;
+    u.tri = -1;
+    const int64_t i = b + lane;
+    int nc = 0;
+    int64_t c0 = 0;
+    if (i < nb) {
+        const int s = task_off[i];
+        if (s < t1 && task_off[i + 1] > s) {
+            nc = candidates(loff, lcap, i);
+            c0 = loff[i] < 0 ? 0 : loff[i];
+        }
+    }
+    const int nfirst = __builtin_amdgcn_readfirstlane(nc);
+    if (nfirst > CL_CAND) {
+        const int n = blk_off[b + 1] - blk_off[b];
+        u.chunk = (task - task_off[b]) / ((n + 63) / 64);
+        const int64_t k = (int64_t)u.chunk * CL_CAND + lane;
+        if (k < nfirst) u.tri = lval[__shfl(c0, 0, 64) + k];
+        return u;
+    }
+    const int incl = wave_incl_scan(nc > CL_CAND ? CL_CAND + 1 : nc);
+    const bool in = incl <= CL_CAND;  // a prefix of the lanes
+    u.n = __popcll(__ballot(in));
+    const int start = incl - nc;
+    u.pack = in ? start | nc << 8 : 0;
+    const int total = __shfl(incl, u.n - 1, 64);
+    __syncthreads();
+    mark[lane] = 0;
+    __syncthreads();
+    if (in && nc > 0) mark[start] = (unsigned char)lane;
+    __syncthreads();
+    u.blk = wave_incl_max(mark[lane]);
+    const int64_t at = __shfl(c0, u.blk, 64) + (lane - __shfl(start, u.blk, 64));
+    if (lane < total) u.tri = lval[at];
+    return u;
+}
+
 // link queue of the exact pass: pos, with bit 31 set when the link must be
 // redone over all its candidates (an undecided pair did not fit the pair queue)
 constexpr int32_t FIX_FULL = (int32_t)0x80000000u;
@@ -899,6 +968,7 @@ __device__ __forceinline__ void cl_q_body(CL_Q_PARAMS) {
     __shared__ unsigned long long sstart;      // chunk positions where a cell's links start
     __shared__ uint16_t flat[64 * CL_MAXC];    // flattened pairs: owner lane | candidate slot << 6
     __shared__ float4 sxp[64];                 // each lane's link: centre-frame cell | direction (bytes)
+    __shared__ unsigned char gmark[64];        // plan_unit's
     __shared__ unsigned long long lbest[64];   // nearest hit of each lane's link (packed key)
     __shared__ unsigned long long lunc;        // links with an undecided pair (bit = lane)
     __shared__ unsigned long long lfull;       // ... one of which did not fit the pair queue
@@ -906,30 +976,29 @@ __device__ __forceinline__ void cl_q_body(CL_Q_PARAMS) {
     const int lane = threadIdx.x;
     const int ntasks = task_off[d.nblocks];
     // contiguous task range per workgroup, so that consecutive tasks share a block
-    const int per = (ntasks + (int)gridDim.x - 1) / (int)gridDim.x;
+    int per = (ntasks + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int few = ntasks / CL_WAVES < CL_RUN ? ntasks / CL_WAVES : CL_RUN;
+    per = per < few ? few : per;
     const int t0 = (int)blockIdx.x * per;
     const int t1 = t0 + per < ntasks ? t0 + per : ntasks;
     QStats st;
     if (t0 >= t1) return;
     int64_t b = task_block(task_off, d.nblocks, t0);
     int64_t b_prev = -1;
-    int64_t staged_b = -1;  // (block, candidate chunk) held in LDS
-    int staged_c = -1;
     uint32_t my_mask = 0;
     int my_pre = 0;
-    // prefetch of the next staging unit: candidate triangle (at staging) and
-    // its vertex ids (at the end of the task), so staging waits for one load
-    int pf_task = -1, pf_n = 0;
-    bool pf_vid_ok = false;
-    int pf_tri = 0, pf_v0 = 0, pf_v1 = 0, pf_v2 = 0;
+    // the unit held in LDS, and the one after it: its triangle ids are loaded
+    // when a unit is staged and their vertex ids at the end of that task, so
+    // staging waits for one load
+    int64_t u_b0 = -1;
+    int u_n = 0, u_chunk = -1, u_pack = 0;
+    CandUnit nx = plan_unit(d.nblocks, b, t0, t1, task_off, blk_off, loff, lval, lcap, gmark);
+    bool nx_vid = false;
+    int nx_v0 = 0, nx_v1 = 0, nx_v2 = 0;
     for (int task = t0; task < t1; task++) {
         if (task >= task_off[b + 1]) b = advance_block(task_off, d.nblocks, b + 1, task);  // uniform
         const int n = blk_off[b + 1] - blk_off[b];
-        int64_t c0 = loff[b], c1 = loff[b + 1];
-        if (c1 > lcap) c1 = lcap;
-        if (c0 < 0) c0 = 0;
-        if (c0 > c1) c0 = c1;
-        const int nc = (int)(c1 - c0);
+        const int nc = candidates(loff, lcap, b);
         const int ncc = nc > CL_CAND ? (nc + CL_CAND - 1) / CL_CAND : 1;
         // a block's tasks run candidate chunk by candidate chunk, so that
         // consecutive link chunks reuse the staged candidates
@@ -943,50 +1012,44 @@ __device__ __forceinline__ void cl_q_body(CL_Q_PARAMS) {
             my_pre = incl - c;
             b_prev = b;
         }
-        const int cb = cchunk * CL_CAND;
-        const int nstage = nc - cb < CL_CAND ? (nc - cb > 0 ? nc - cb : 0) : CL_CAND;
         __syncthreads();  // the previous task's readers of the LDS arrays are done
         if (lane == 0) {
             sstart = 0;
             lunc = 0;
             lfull = 0;
         }
-        if (b != staged_b || cchunk != staged_c) {  // uniform
-            staged_b = b;
-            staged_c = cchunk;
+        const bool held = ncc > 1 ? u_chunk == cchunk && u_b0 == b : u_chunk < 0 && b >= u_b0 && b < u_b0 + u_n;
+        if (!held) {  // uniform: stage the planned unit, which starts here
+            u_b0 = nx.b0;
+            u_n = nx.n;
+            u_chunk = nx.chunk;
+            u_pack = nx.pack;
             float blo[3] = {1e30f, 1e30f, 1e30f}, bhi[3] = {-1e30f, -1e30f, -1e30f};
-            const bool from_pf = pf_task == task;  // uniform
-            const int tri = lane < nstage ? (from_pf ? pf_tri : lval[c0 + cb + lane]) : -1;
             // entries of an overflowed bin are not triangle ids: left inert
-            if (lane < nstage && (unsigned)tri < (unsigned)m.nt) {
+            if ((unsigned)nx.tri < (unsigned)m.nt) {
                 int vid[3];
-                if (from_pf && pf_vid_ok) {
-                    vid[0] = pf_v0;
-                    vid[1] = pf_v1;
-                    vid[2] = pf_v2;
+                if (nx_vid) {
+                    vid[0] = nx_v0;
+                    vid[1] = nx_v1;
+                    vid[2] = nx_v2;
                 } else {
 #pragma unroll
-                    for (int i = 0; i < 3; i++) vid[i] = m.tris[3 * (int64_t)tri + i];
+                    for (int i = 0; i < 3; i++) vid[i] = m.tris[3 * (int64_t)nx.tri + i];
                 }
-                if constexpr (F32V) stage_cand_f32in(m, L, tri, vid, b0, cand, lane, blo, bhi, st);
-                else stage_cand<R>(m, L, tri, vid, b0, cand, lane, blo, bhi, st);
+                const int64_t cbk = u_b0 + nx.blk;
+                const int cb0[3] = {4 * d.bcoord[3 * cbk], 4 * d.bcoord[3 * cbk + 1], 4 * d.bcoord[3 * cbk + 2]};
+                if constexpr (F32V) stage_cand_f32in(m, L, nx.tri, vid, cb0, cand, lane, blo, bhi, st);
+                else stage_cand<R>(m, L, nx.tri, vid, cb0, cand, lane, blo, bhi, st);
             }
-            // first task of the next staging unit, and its candidates
-            pf_task = -1;
-            pf_vid_ok = false;
-            const int tn = task_off[b] + (cchunk + 1) * nlc;
+            // the next unit: after this chunk's tasks, or after the group's
+            nx.tri = -1;
+            nx_vid = false;
+            const int64_t be = u_b0 + u_n < d.nblocks ? u_b0 + u_n : d.nblocks;
+            const int tn = u_chunk >= 0 ? task_off[b] + (u_chunk + 1) * nlc : task_off[be];
             if (tn < t1) {
-                const int64_t bn = tn < task_off[b + 1] ? b : advance_block(task_off, d.nblocks, b + 1, tn);
-                const int nn = blk_off[bn + 1] - blk_off[bn];
-                int64_t d0 = loff[bn], d1 = loff[bn + 1];
-                if (d1 > lcap) d1 = lcap;
-                if (d0 < 0) d0 = 0;
-                if (d0 > d1) d0 = d1;
-                const int cbn = ((tn - task_off[bn]) / ((nn + 63) / 64)) * CL_CAND;
-                const int rem = (int)(d1 - d0) - cbn;
-                pf_n = rem < CL_CAND ? (rem > 0 ? rem : 0) : CL_CAND;
-                if (lane < pf_n) pf_tri = lval[d0 + cbn + lane];
-                pf_task = tn;
+                const int64_t bs = u_chunk >= 0 ? b : be;
+                const int64_t bn = tn < task_off[bs + 1] ? bs : advance_block(task_off, d.nblocks, bs + 1, tn);
+                nx = plan_unit(d.nblocks, bn, tn, t1, task_off, blk_off, loff, lval, lcap, gmark);
             }
             unsigned long long mine = 0;
 #pragma unroll
@@ -1001,6 +1064,12 @@ __device__ __forceinline__ void cl_q_body(CL_Q_PARAMS) {
                     if (lane == 12 * a + 6 + j) mine = B;
                 }
             if (lane < 36) bmask[lane] = mine;
+        }
+        // the block's slots among the unit's
+        unsigned long long own = ~0ull;
+        if (u_chunk < 0) {
+            const int pk = __builtin_amdgcn_readlane(u_pack, (int)(b - u_b0)), k = pk >> 8;
+            own = k >= 64 ? ~0ull : ((1ull << k) - 1ull) << (pk & 255);
         }
         // the links of this task: chunk positions base .. base + 63 of the
         // block's (t, k) order; the links of cell t start at its prefix (my_pre of lane t)
@@ -1039,7 +1108,7 @@ __device__ __forceinline__ void cl_q_body(CL_Q_PARAMS) {
         if (active) {
             const int slo[3] = {geo_min(tl[0], tl[0] + cx), geo_min(tl[1], tl[1] + cy), geo_min(tl[2], tl[2] + cz)};
             const int shi[3] = {geo_max(tl[0], tl[0] + cx), geo_max(tl[1], tl[1] + cy), geo_max(tl[2], tl[2] + cz)};
-            pm = bmask[1 + slo[0]] & bmask[7 + shi[0]] & bmask[13 + slo[1]] & bmask[19 + shi[1]] &
+            pm = own & bmask[1 + slo[0]] & bmask[7 + shi[0]] & bmask[13 + slo[1]] & bmask[19 + shi[1]] &
                  bmask[25 + slo[2]] & bmask[31 + shi[2]];
         }
         while (__any(pm != 0)) {  // uniform
@@ -1114,13 +1183,13 @@ __device__ __forceinline__ void cl_q_body(CL_Q_PARAMS) {
                 }
             }
         }
-        if (pf_task >= 0 && !pf_vid_ok) {  // uniform
-            if (lane < pf_n && (unsigned)pf_tri < (unsigned)m.nt) {
-                pf_v0 = m.tris[3 * (int64_t)pf_tri];
-                pf_v1 = m.tris[3 * (int64_t)pf_tri + 1];
-                pf_v2 = m.tris[3 * (int64_t)pf_tri + 2];
+        if (!nx_vid) {  // uniform
+            if ((unsigned)nx.tri < (unsigned)m.nt) {
+                nx_v0 = m.tris[3 * (int64_t)nx.tri];
+                nx_v1 = m.tris[3 * (int64_t)nx.tri + 1];
+                nx_v2 = m.tris[3 * (int64_t)nx.tri + 2];
             }
-            pf_vid_ok = true;
+            nx_vid = true;
         }
     }
     if (sl.p) {
@@ -1339,8 +1408,9 @@ int launch_cutlinks(const DevMesh& m, const DevLevel& d, const geo_bins* rows, c
     k_cl_multi<<<g, 64, 0, s>>>(nb, blk_off, links->off, links->cap, cap, 0, keys, mark, link_q, link_tri, sl);
     GEO_LAUNCH_CHECK();
     // tasks are split into one contiguous range per workgroup; finer ranges
-    // balance better; empty ranges exit at once
-    const unsigned gq = 65536;
+    // balance better; empty ranges exit at once (a level of few blocks is not
+    // given more workgroups than that)
+    const unsigned gq = (unsigned)(nb < 1024 ? 1024 : (nb < 65536 ? nb : 65536));
     kt_record(GEO_KT_CUTLINKS_Q, s, false);
     auto q_kernel = precision != GEO_PREC_F32_FALLBACK ? k_cl_q_f64 : m.vdtype == GEO_F32 ? k_cl_q_f32 : k_cl_q_f32_v64;
     q_kernel<<<gq, 64, 0, s>>>(m, d, wmask, links->off, links->val, links->cap, blk_off, task_off, cap, link_cell, link_dir,

@@ -66,3 +66,20 @@ def test_q_counters(name, precision):
         assert none[s] == one[s]
     q = call(None, k.n)[2]
     assert torch.equal(q, k.q)
+
+
+@pytest.mark.parametrize("precision", ["f32", "f64"])
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n_theta", [4, 12, 40, 160])
+def test_groups_of_blocks_and_chunks(n_theta, dtype, precision):
+    """Candidates staged for several blocks at once and for blocks with more
+    than 64 (the poles of the finer meshes), against the oracle: from a few
+    candidates per block, where a group spans 64 blocks, to hundreds."""
+    import oracle
+    from gpu_helpers import compare, gpu_embed
+    w = configs.star_small(n_theta=n_theta, n_phi=2 * n_theta, lf=1, lattice=27, dtype=dtype)
+    ref = oracle.embed(w.mesh, w.n0, w.lf, w.lattice, w.d_spec)
+    emb, _, _ = gpu_embed(w, precision)
+    compare(w, emb, ref)
+    nc = np.diff(emb.links.bins_off.cpu().numpy())
+    assert nc.max() > 64 if n_theta >= 40 else nc.max() < 64
