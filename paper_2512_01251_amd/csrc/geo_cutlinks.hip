@@ -72,7 +72,7 @@ __device__ __forceinline__ uint32_t lattice_dirs(int lattice) {
 // bins: parity of the crossings ahead, or'ed with the on-surface intervals
 
 // fold entries v[0..n-1] of a halo line (centres xm1 .. xm1+5) into par / surf
-__device__ __forceinline__ void fold_halo(const int32_t* v4, int64_t n, int xm1, unsigned& par, unsigned& surf) {
+__device__ __forceinline__ void fold_halo(const int32_t* v4, int n, int xm1, unsigned& par, unsigned& surf) {
 #pragma unroll
     for (int i = 0; i < 4; i++) {
         if (i >= n) break;
@@ -94,30 +94,22 @@ __device__ __forceinline__ void fold_halo(const int32_t* v4, int64_t n, int xm1,
 // both offset pairs, then the first four entries of both lines
 __device__ __forceinline__ void halo_bits2(const int32_t* off, const int32_t* val, int64_t cap, bool ha, int64_t la,
                                            int xa, bool hb, int64_t lb, int xb, int nx, unsigned& ra, unsigned& rb) {
-    int64_t a0 = 0, a1 = 0, b0 = 0, b1 = 0;
-    if (ha) { a0 = off[la]; a1 = off[la + 1]; }
-    if (hb) { b0 = off[lb]; b1 = off[lb + 1]; }
-    if (a1 > cap) a1 = cap;
-    if (a0 < 0) a0 = 0;
-    if (b1 > cap) b1 = cap;
-    if (b0 < 0) b0 = 0;
+    const int last = entry_limit(cap);
+    int a0 = 0, a1 = 0, b0 = 0, b1 = 0;
+    if (ha) line_range(off, la, last, a0, a1);
+    if (hb) line_range(off, lb, last, b0, b1);
     int32_t va[4], vb[4];
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        va[i] = a0 + i < a1 ? val[a0 + i] : 0;
-        vb[i] = b0 + i < b1 ? val[b0 + i] : 0;
-    }
+    line_entries(val, a0, a1, last, va);
+    line_entries(val, b0, b1, last, vb);
     unsigned pa = 0, sa = 0, pb = 0, sb = 0;
     fold_halo(va, a1 - a0, xa, pa, sa);
     fold_halo(vb, b1 - b0, xb, pb, sb);
-    for (int64_t e = a0 + 4; e < a1; e += 4) {  // lines with more than four entries
-#pragma unroll
-        for (int i = 0; i < 4; i++) va[i] = e + i < a1 ? val[e + i] : 0;
+    for (int e = a0 + 4; e < a1 && e > 0; e += 4) {  // lines with more than four entries
+        line_entries(val, e, a1, last, va);
         fold_halo(va, a1 - e, xa, pa, sa);
     }
-    for (int64_t e = b0 + 4; e < b1; e += 4) {
-#pragma unroll
-        for (int i = 0; i < 4; i++) vb[i] = e + i < b1 ? val[e + i] : 0;
+    for (int e = b0 + 4; e < b1 && e > 0; e += 4) {
+        line_entries(val, e, b1, last, vb);
         fold_halo(vb, b1 - e, xb, pb, sb);
     }
     ra = (pa | sa) & 0x3fu;
