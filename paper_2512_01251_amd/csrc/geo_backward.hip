@@ -71,10 +71,8 @@ struct BwTri {
     // (without contraction: n is exactly zero where two vertices coincide)
     __device__ __forceinline__ void load(const DevMesh& m, int tri) {
 #pragma clang fp contract(off)
-        for (int j = 0; j < 3; j++) {
-            v[j] = m.tris[3 * (int64_t)tri + j];
-            for (int a = 0; a < 3; a++) P[j][a] = load_coord(m, v[j], a);
-        }
+        load_tri(m, tri, v);
+        for (int j = 0; j < 3; j++) load_vert(m, v[j], P[j]);
         const double e1[3] = {P[1][0] - P[0][0], P[1][1] - P[0][1], P[1][2] - P[0][2]};
         const double e2[3] = {P[2][0] - P[0][0], P[2][1] - P[0][1], P[2][2] - P[0][2]};
         n[0] = e1[1] * e2[2] - e1[2] * e2[1];

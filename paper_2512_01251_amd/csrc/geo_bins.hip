@@ -275,9 +275,8 @@ struct TriLoad {
 };
 
 __device__ __forceinline__ void tri_load(const DevMesh& m, int64_t t, TriLoad& tl) {
-    for (int i = 0; i < 3; i++) tl.id[i] = m.tris[3 * t + i];
-    for (int i = 0; i < 3; i++)
-        for (int a = 0; a < 3; a++) tl.x[i][a] = load_coord(m, tl.id[i], a);
+    load_tri(m, t, tl.id);
+    for (int i = 0; i < 3; i++) load_vert(m, tl.id[i], tl.x[i]);
 }
 
 // Row lines of level L inside the triangle's yz box: [jlo, jhi] x [klo, khi]
@@ -849,12 +848,14 @@ __device__ __forceinline__ LinkGrid link_grid(const DevLevel& d) {
 template <typename V>
 __device__ __forceinline__ int64_t link_setup(const DevMesh& m, int64_t t, const LinkGrid& g, LinkItems<V>& I, int i) {
     double v[3][3];
+    int vid[3];
+    load_tri(m, t, vid);
     for (int k = 0; k < 3; k++) {
-        const int vid = m.tris[3 * t + k];
+        V x[3];
+        __builtin_memcpy(x, static_cast<const V*>(m.verts) + 3 * (int64_t)vid[k], sizeof(x));
         for (int a = 0; a < 3; a++) {
-            const V x = static_cast<const V*>(m.verts)[3 * (int64_t)vid + a];
-            I.v[3 * k + a][i] = x;
-            v[k][a] = (double)x;
+            I.v[3 * k + a][i] = x[a];
+            v[k][a] = (double)x[a];
         }
     }
     // zero-area triangles never meet a segment: exact test (all three
@@ -1082,8 +1083,10 @@ __global__ void k_check_mesh(DevMesh m, DevLevel d, uint64_t* stats) {
     unsigned bad = 0;
     const double top[3] = {(double)d.n0[0], (double)d.n0[1], (double)d.n0[2]};
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < m.nv; v += (int64_t)gridDim.x * blockDim.x) {
+        double xs[3];
+        load_vert(m, (int)v, xs);
         for (int a = 0; a < 3; a++) {
-            const double x = load_coord(m, (int)v, a);
+            const double x = xs[a];
             const bool ok = x == 0.0 || (x >= 0.25 && x <= top[a]);
             bad += ok ? 0u : 1u;
         }

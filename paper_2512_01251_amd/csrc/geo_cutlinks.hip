@@ -273,11 +273,6 @@ struct CandRef {
     __device__ __forceinline__ R& operator()(int k) const { return s.f[k][c]; }
 };
 
-// scaled vertex coordinate x 2^L (exact: a power-of-two scaling)
-__device__ __forceinline__ double vert_scaled2(const DevMesh& m, int vid, int a, double s) {
-    return load_coord(m, vid, a) * s;
-}
-
 __device__ __forceinline__ float down_f(double x) {
     float f = (float)x;
     return (double)f > x ? nextafterf(f, -1e30f) : f;
@@ -314,15 +309,18 @@ __device__ void stage_cand(const DevMesh& m, int L, int tri, const int vid[3], c
     double v[3][3];
     bool exact = true;
 #pragma unroll
-    for (int i = 0; i < 3; i++)
+    for (int i = 0; i < 3; i++) {
+        double x[3];
+        load_vert(m, vid[i], x);
 #pragma unroll
         for (int a = 0; a < 3; a++) {
             // centre frame: x 2^L - 1/2 - (b0 + 3/2) = x 2^L - (b0 + 2)
-            const double g = vert_scaled2(m, vid[i], a, s), o = (double)(b0[a] + 2);
+            const double g = x[a] * s, o = (double)(b0[a] + 2);
             const double d = g - o;
             if (!diff_exact(g, o, d)) exact = false;
             v[i][a] = d;
         }
+    }
     int flags = exact ? 0 : C_SLOW;
     const double e1[3] = {v[1][0] - v[0][0], v[1][1] - v[0][1], v[1][2] - v[0][2]};
     const double e2[3] = {v[2][0] - v[0][0], v[2][1] - v[0][1], v[2][2] - v[0][2]};
@@ -437,15 +435,18 @@ __device__ void stage_cand_f32in(const DevMesh& m, int L, int tri, const int vid
     float v[3][3];
     bool exact = true;
 #pragma unroll
-    for (int i = 0; i < 3; i++)
+    for (int i = 0; i < 3; i++) {
+        float x[3];
+        __builtin_memcpy(x, V + 3 * (int64_t)vid[i], 12);
 #pragma unroll
         for (int a = 0; a < 3; a++) {
-            const float g = V[3 * (int64_t)vid[i] + a] * sc;  // exact (power-of-two scaling)
+            const float g = x[a] * sc;  // exact (power-of-two scaling)
             const float o = (float)(b0[a] + 2);
             const float d = g - o;
             exact &= sum_exact_f(g, -o, d);
             v[i][a] = d;
         }
+    }
     float e1[3], e2[3];
 #pragma unroll
     for (int a = 0; a < 3; a++) {
@@ -665,7 +666,9 @@ __device__ __forceinline__ double o3_value(const double* a, const double* b, con
 
 // scaled global coordinate v 2^L - 1/2 (exact), the frame of the exact pass
 __device__ __forceinline__ void vert_scaled(const DevMesh& m, int vid, double s, double g[3]) {
-    for (int a = 0; a < 3; a++) g[a] = load_coord(m, vid, a) * s - 0.5;
+    double x[3];
+    load_vert(m, vid, x);
+    for (int a = 0; a < 3; a++) g[a] = x[a] * s - 0.5;
 }
 
 // hit parameter of X->Y on the plane of A, B, C, which its ends lie strictly on
@@ -1025,8 +1028,7 @@ __device__ __forceinline__ void cl_q_body(CL_Q_PARAMS) {
                     vid[1] = nx_v1;
                     vid[2] = nx_v2;
                 } else {
-#pragma unroll
-                    for (int i = 0; i < 3; i++) vid[i] = m.tris[3 * (int64_t)nx.tri + i];
+                    load_tri(m, nx.tri, vid);
                 }
                 const int64_t cbk = u_b0 + nx.blk;
                 const int cb0[3] = {4 * d.bcoord[3 * cbk], 4 * d.bcoord[3 * cbk + 1], 4 * d.bcoord[3 * cbk + 2]};
@@ -1177,9 +1179,11 @@ __device__ __forceinline__ void cl_q_body(CL_Q_PARAMS) {
         }
         if (!nx_vid) {  // uniform
             if ((unsigned)nx.tri < (unsigned)m.nt) {
-                nx_v0 = m.tris[3 * (int64_t)nx.tri];
-                nx_v1 = m.tris[3 * (int64_t)nx.tri + 1];
-                nx_v2 = m.tris[3 * (int64_t)nx.tri + 2];
+                int v[3];
+                load_tri(m, nx.tri, v);
+                nx_v0 = v[0];
+                nx_v1 = v[1];
+                nx_v2 = v[2];
             }
             nx_vid = true;
         }

@@ -70,6 +70,21 @@ __device__ __forceinline__ double load_coord(const DevMesh& m, int v, int a) {
                                : (double)static_cast<const float*>(m.verts)[3 * (int64_t)v + a];
 }
 
+// all three coordinates of a vertex, or ids of a triangle, by one load of 12
+// (float32, ids) or 24 bytes: gathers are bound by the L1's rate of accesses
+__device__ __forceinline__ void load_vert(const DevMesh& m, int v, double x[3]) {
+    if (m.vdtype == GEO_F64) {
+        __builtin_memcpy(x, static_cast<const double*>(m.verts) + 3 * (int64_t)v, 24);
+    } else {
+        float f[3];
+        __builtin_memcpy(f, static_cast<const float*>(m.verts) + 3 * (int64_t)v, 12);
+        for (int a = 0; a < 3; a++) x[a] = (double)f[a];
+    }
+}
+__device__ __forceinline__ void load_tri(const DevMesh& m, int64_t t, int v[3]) {
+    __builtin_memcpy(v, m.tris + 3 * t, 12);
+}
+
 // --------------------------------------------------------------------------
 // forest lookup: index of block (bx,by,bz) of level L, -1 if it does not
 // exist, -2 if it lies outside the domain.  Walks the child maps from the
