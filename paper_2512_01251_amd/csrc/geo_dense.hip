@@ -5,10 +5,11 @@
 // direction-major (structure of arrays: the 64 cells of one direction are
 // contiguous), -1 where a (cell, direction) has no link.
 //
-//   k_dn_flag    one thread per link: marks the block of each run of links
+//   k_dn_flag    one thread per link: the first link of a block's run (the table is
+//                sorted by block) marks the block and leaves its number there
 //   scan         boundary-block index of every block, and their count
-//   k_dn_map     block map (-1 for blocks without links)
-//   k_dn_starts  first link of every boundary block (the table is sorted by block)
+//   k_dn_map     block map (-1 for blocks without links), and the first link of
+//                every boundary block
 //   k_dn_write   one workgroup per boundary block: entries built in LDS, written once
 #include "geo_internal.h"
 
@@ -27,31 +28,27 @@ __device__ __forceinline__ int dir_slot(int k, int lattice) {
     return (k != 13 && k >= 0 && k < 27 && (lattice == 27 || n2 <= 2)) ? slot : -1;
 }
 
-__global__ void k_dn_flag(int64_t n_links, const int32_t* link_cell, int64_t nb, int32_t* flag) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_links; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t b = link_cell[i] >> 6;
-        if (b >= 0 && b < nb) flag[b] = 1;  // every writer stores the same value
-    }
-}
-
-__global__ void k_dn_map(int64_t nb, const int32_t* flag, const int32_t* pre, int32_t* block_map) {
-    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += (int64_t)gridDim.x * blockDim.x)
-        block_map[b] = flag[b] ? pre[b] : -1;
-}
-
-// first link of each boundary block (the table is sorted by block), and
-// start[nbnd] = n_links
-__global__ void k_dn_starts(int64_t n_links, const int32_t* link_cell, int64_t nb, const int32_t* block_map,
-                            const int64_t* d_nbnd, int32_t* start) {
+__global__ void k_dn_flag(int64_t n_links, const int32_t* link_cell, int64_t nb, int32_t* flag, int32_t* first) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_links; i += (int64_t)gridDim.x * blockDim.x) {
         const int64_t b = link_cell[i] >> 6;
         if (i > 0 && (link_cell[i - 1] >> 6) == b) continue;
         if (b >= 0 && b < nb) {
-            const int j = block_map[b];
-            if (j >= 0) start[j] = (int32_t)i;
+            flag[b] = 1;
+            first[b] = (int32_t)i;
         }
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) start[*d_nbnd] = (int32_t)n_links;
+}
+
+// start[j]: first link of the j-th boundary block, and start[their count] = n_links
+__global__ void k_dn_map(int64_t nb, const int32_t* flag, const int32_t* first, const int32_t* pre, int64_t n_links,
+                         int32_t* block_map, int32_t* start) {
+    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += (int64_t)gridDim.x * blockDim.x) {
+        const bool on = flag[b] != 0;
+        const int j = pre[b];
+        block_map[b] = on ? j : -1;
+        if (on) start[j] = first[b];
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) start[pre[nb]] = (int32_t)n_links;
 }
 
 // one workgroup per boundary block: its 64 x Q entries built in LDS (-1
@@ -69,23 +66,45 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_write(const int32_t* link_cel
     if (nbnd > cap) nbnd = cap;
     const int n = q_dirs * 64;
     if (threadIdx.x < 27) slot_of[threadIdx.x] = (int8_t)dir_slot(threadIdx.x, lattice);
-    for (int64_t j = blockIdx.x; j < nbnd; j += gridDim.x) {
-        for (int i = threadIdx.x; i < n; i += DN_THREADS) {
-            sq[i] = -1.0f;
-            st[i] = -1;
-        }
-        __syncthreads();
-        int64_t s0 = start[j], s1 = start[j + 1];
+    // a thread's first link of the block at hand, loaded while the block before
+    // was written
+    int64_t s0 = 0, s1 = 0;
+    int cell = 0, k = 27, tri = 0;
+    float q = 0;
+    auto fetch = [&](int64_t j) {
+        s0 = start[j];
+        s1 = start[j + 1];
         s0 = s0 < 0 ? 0 : s0;
         s1 = s1 > n_links ? n_links : s1;
-        for (int64_t i = s0 + threadIdx.x; i < s1; i += DN_THREADS) {
-            const int k = link_dir[i];
-            const int sl = k < 27 ? slot_of[k] : -1;
-            if (sl < 0) continue;
-            const int e = sl * 64 + (link_cell[i] & 63);
-            sq[e] = link_q[i];
-            st[e] = link_tri[i];
+        const int64_t i = s0 + threadIdx.x;
+        k = 27;
+        if (i < s1) {
+            k = link_dir[i];
+            cell = link_cell[i];
+            q = link_q[i];
+            tri = link_tri[i];
         }
+    };
+    auto put = [&](int k, int cell, float q, int tri) {
+        const int sl = k < 27 ? slot_of[k] : -1;
+        if (sl < 0) return;
+        const int e = sl * 64 + (cell & 63);
+        sq[e] = q;
+        st[e] = tri;
+    };
+    if ((int64_t)blockIdx.x < nbnd) fetch(blockIdx.x);
+    const uint4 none_q = make_uint4(0xbf800000u, 0xbf800000u, 0xbf800000u, 0xbf800000u);  // -1.0f
+    const uint4 none_t = make_uint4(~0u, ~0u, ~0u, ~0u);
+    for (int64_t j = blockIdx.x; j < nbnd; j += gridDim.x) {
+        for (int i = threadIdx.x; i < n / 4; i += DN_THREADS) {
+            reinterpret_cast<uint4*>(sq)[i] = none_q;
+            reinterpret_cast<uint4*>(st)[i] = none_t;
+        }
+        __syncthreads();
+        put(k, cell, q, tri);
+        for (int64_t i = s0 + threadIdx.x + DN_THREADS; i < s1; i += DN_THREADS)
+            put(link_dir[i], link_cell[i], link_q[i], link_tri[i]);
+        if (j + gridDim.x < nbnd) fetch(j + gridDim.x);
         __syncthreads();
         uint4* q4 = reinterpret_cast<uint4*>(dense_q + j * n);
         uint4* t4 = reinterpret_cast<uint4*>(dense_tri + j * n);
@@ -109,7 +128,7 @@ inline unsigned grid_for(int64_t n, int threads) {
 }  // namespace
 
 size_t geo_dense_ws_bytes(int64_t nb) {
-    return ((sizeof(int32_t) * (size_t)(nb + 1) + 255) & ~(size_t)255) * 3 + geo_scan_partials_bytes(nb);
+    return ((sizeof(int32_t) * (size_t)(nb + 1) + 255) & ~(size_t)255) * 4 + geo_scan_partials_bytes(nb);
 }
 
 int launch_links_dense(int64_t nb, int64_t n_links, const int32_t* link_cell, const uint8_t* link_dir,
@@ -122,24 +141,23 @@ int launch_links_dense(int64_t nb, int64_t n_links, const int32_t* link_cell, co
     int32_t* flag = reinterpret_cast<int32_t*>(p);
     int32_t* pre = reinterpret_cast<int32_t*>(p + a);
     int32_t* start = reinterpret_cast<int32_t*>(p + 2 * a);
-    int64_t* partials = reinterpret_cast<int64_t*>(p + 3 * a);
+    int32_t* first = reinterpret_cast<int32_t*>(p + 3 * a);
+    int64_t* partials = reinterpret_cast<int64_t*>(p + 4 * a);
     int rc;
     if (nb == 0) return geo_fill_u64(reinterpret_cast<uint64_t*>(d_nbnd), 0, 1, s);
     if ((rc = geo_fill_i32(flag, 0, nb, s)) != GEO_OK) return rc;
-    if ((rc = geo_fill_i32(start, 0, nb + 1, s)) != GEO_OK) return rc;
     if (n_links > 0) {
-        k_dn_flag<<<grid_for(n_links, 256), 256, 0, s>>>(n_links, link_cell, nb, flag);
+        k_dn_flag<<<grid_for(n_links, 256), 256, 0, s>>>(n_links, link_cell, nb, flag, first);
         GEO_LAUNCH_CHECK();
     }
     if ((rc = geo_scan_exclusive(flag, pre, nb, partials, s, d_nbnd)) != GEO_OK) return rc;
-    k_dn_map<<<grid_for(nb, 256), 256, 0, s>>>(nb, flag, pre, block_map);
+    k_dn_map<<<grid_for(nb, 256), 256, 0, s>>>(nb, flag, first, pre, n_links, block_map, start);
     GEO_LAUNCH_CHECK();
     // start[] has nb + 1 entries, enough for any count of boundary blocks
-    k_dn_starts<<<grid_for(n_links > 0 ? n_links : 1, 256), 256, 0, s>>>(n_links, link_cell, nb, block_map, d_nbnd,
-                                                                          start);
-    GEO_LAUNCH_CHECK();
     if (cap > 0) {
-        const int64_t g = cap < 16384 ? cap : 16384;
+        // 8 resident workgroups per CU: 72k boundary blocks (0.96 GB) 249 us per call
+        // against 260 with 16,384 (290 before the next links were fetched ahead)
+        const int64_t g = cap < 2048 ? cap : 2048;
         k_dn_write<<<(unsigned)g, DN_THREADS, 0, s>>>(link_cell, link_dir, link_q, link_tri, start, d_nbnd, cap,
                                                        n_links, lattice, q_dirs, dense_q, dense_tri);
         GEO_LAUNCH_CHECK();

@@ -40,7 +40,7 @@ struct LatTab {
     }
 };
 
-constexpr int IBB_GRID_MAX = 32768;
+constexpr int IBB_GRID_MAX = 131072;
 
 // Link slots [S0, S1) of one boundary block: load every population the links
 // among them need, then compute and store.  q: the block's q of every slot.
@@ -94,8 +94,9 @@ __device__ __forceinline__ void ibb_slots(const float* q, const T* __restrict__ 
     }
 }
 
-// One wave per boundary block at a time: the wave scans 64 entries of the
-// block map, then serves the boundary blocks among them; lanes are the cells.
+// One wave per boundary block at a time: the wave scans `chunk` entries (64 at
+// most) of the block map, then serves the boundary blocks among them; lanes are
+// the cells.
 // Per block, every q of the block is loaded first, then the populations of
 // the link slots, all at once for bounce-back and a third of the slots at a
 // time for the interpolated form (a bound on live registers), each group
@@ -104,7 +105,7 @@ __device__ __forceinline__ void ibb_slots(const float* q, const T* __restrict__ 
 template <typename T, int LAT, bool INTERP>
 __global__ void __launch_bounds__(64) k_ibb(DevLevel d, const uint64_t* __restrict__ solid,
                                             const int32_t* __restrict__ block_map, const float* __restrict__ dense_q,
-                                            int64_t nbnd, const int32_t* __restrict__ nbr_table,
+                                            int64_t nbnd, int chunk, const int32_t* __restrict__ nbr_table,
                                             const T* __restrict__ f_post, T* __restrict__ f_new,
                                             unsigned long long* d_fallback) {
     constexpr int QD = LAT == 27 ? 26 : 18, QF = QD + 1, C3 = (QD + 2) / 3;
@@ -123,9 +124,9 @@ __global__ void __launch_bounds__(64) k_ibb(DevLevel d, const uint64_t* __restri
         }
     }
     unsigned fallback = 0;
-    for (int64_t base = (int64_t)blockIdx.x * 64; base < d.nblocks; base += (int64_t)gridDim.x * 64) {
+    for (int64_t base = (int64_t)blockIdx.x * chunk; base < d.nblocks; base += (int64_t)gridDim.x * chunk) {
         const int64_t mb = base + lane;
-        const int32_t mj = mb < d.nblocks ? block_map[mb] : -1;
+        const int32_t mj = lane < chunk && mb < d.nblocks ? block_map[mb] : -1;
         uint64_t todo = __ballot(mj >= 0 && mj < nbnd);
         while (todo) {
             const int src = __builtin_ctzll(todo);
@@ -167,15 +168,15 @@ __global__ void __launch_bounds__(64) k_ibb(DevLevel d, const uint64_t* __restri
 }
 
 template <typename T, int LAT>
-void launch_ibb_t(unsigned g, const DevLevel& d, const uint64_t* solid, const int32_t* block_map,
+void launch_ibb_t(unsigned g, int chunk, const DevLevel& d, const uint64_t* solid, const int32_t* block_map,
                   const float* dense_q, int64_t nbnd, const int32_t* nbr, int interpolate, const void* f_post,
                   void* f_new, unsigned long long* d_fallback, hipStream_t s) {
     const T* fi = static_cast<const T*>(f_post);
     T* fo = static_cast<T*>(f_new);
     if (interpolate)
-        k_ibb<T, LAT, true><<<g, 64, 0, s>>>(d, solid, block_map, dense_q, nbnd, nbr, fi, fo, d_fallback);
+        k_ibb<T, LAT, true><<<g, 64, 0, s>>>(d, solid, block_map, dense_q, nbnd, chunk, nbr, fi, fo, d_fallback);
     else
-        k_ibb<T, LAT, false><<<g, 64, 0, s>>>(d, solid, block_map, dense_q, nbnd, nbr, fi, fo, d_fallback);
+        k_ibb<T, LAT, false><<<g, 64, 0, s>>>(d, solid, block_map, dense_q, nbnd, chunk, nbr, fi, fo, d_fallback);
 }
 
 // the 27 same-level neighbours of every block (offset 13 is the block itself)
@@ -205,20 +206,27 @@ int launch_ibb(const DevLevel& d, const uint64_t* solid, const int32_t* block_ma
                int64_t nbnd, const int32_t* nbr, int lattice, int interpolate, int dtype, const void* f_post,
                void* f_new, unsigned long long* d_fallback, hipStream_t s) {
     if (d.nblocks == 0 || nbnd == 0) return GEO_OK;
-    const int64_t chunks = ((int64_t)d.nblocks + 63) / 64;
+    // entries of the block map per wave: up to 64, fewer on levels where that
+    // would leave fewer than IBB_GRID_MAX waves, since a wave serves the boundary
+    // blocks among its entries one after the other (149k blocks, D3Q19, float32,
+    // interpolated: 343 us with 64 entries, 79 with 5 and 32,768 waves, 66 with
+    // 2 and 131,072; 4,096 blocks of one level of 64^3 cells: 71 and 17 us)
+    int64_t chunk = ((int64_t)d.nblocks + IBB_GRID_MAX - 1) / IBB_GRID_MAX;
+    chunk = chunk > 64 ? 64 : chunk;
+    const int64_t chunks = ((int64_t)d.nblocks + chunk - 1) / chunk;
     const int64_t g = chunks < IBB_GRID_MAX ? chunks : IBB_GRID_MAX;
     kt_record(GEO_KT_IBB, s, false);
     const unsigned gu = (unsigned)g;
     if (dtype == GEO_F64) {
         if (lattice == 27)
-            launch_ibb_t<double, 27>(gu, d, solid, block_map, dense_q, nbnd, nbr, interpolate, f_post, f_new, d_fallback, s);
+            launch_ibb_t<double, 27>(gu, (int)chunk, d, solid, block_map, dense_q, nbnd, nbr, interpolate, f_post, f_new, d_fallback, s);
         else
-            launch_ibb_t<double, 19>(gu, d, solid, block_map, dense_q, nbnd, nbr, interpolate, f_post, f_new, d_fallback, s);
+            launch_ibb_t<double, 19>(gu, (int)chunk, d, solid, block_map, dense_q, nbnd, nbr, interpolate, f_post, f_new, d_fallback, s);
     } else {
         if (lattice == 27)
-            launch_ibb_t<float, 27>(gu, d, solid, block_map, dense_q, nbnd, nbr, interpolate, f_post, f_new, d_fallback, s);
+            launch_ibb_t<float, 27>(gu, (int)chunk, d, solid, block_map, dense_q, nbnd, nbr, interpolate, f_post, f_new, d_fallback, s);
         else
-            launch_ibb_t<float, 19>(gu, d, solid, block_map, dense_q, nbnd, nbr, interpolate, f_post, f_new, d_fallback, s);
+            launch_ibb_t<float, 19>(gu, (int)chunk, d, solid, block_map, dense_q, nbnd, nbr, interpolate, f_post, f_new, d_fallback, s);
     }
     kt_record(GEO_KT_IBB, s, true);
     GEO_LAUNCH_CHECK();
