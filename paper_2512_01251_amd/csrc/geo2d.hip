@@ -260,8 +260,10 @@ __global__ void k2_ref_b(int64_t nb, const uint16_t* solid, const int32_t* nbr, 
     }
 }
 
+// one propagation pass; the last one (refine != null) also writes refine =
+// marked and eligible, and the number of children for their scan
 __global__ void k2_ref_prop(int64_t nb, const uint16_t* solid, const int32_t* nbr, const uint8_t* mark_in,
-                            uint8_t* mark_out, int first) {
+                            uint8_t* mark_out, int first, const uint8_t* elig, uint8_t* refine, int32_t* cnt) {
     for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += (int64_t)gridDim.x * blockDim.x) {
         bool mk = mark_in[b];
         if (!mk && (solid[b] == 0 || first))
@@ -270,14 +272,11 @@ __global__ void k2_ref_prop(int64_t nb, const uint16_t* solid, const int32_t* nb
                 if (k >= 0 && mark_in[k]) mk = true;
             }
         mark_out[b] = (uint8_t)mk;
-    }
-}
-
-__global__ void k2_ref_final(int64_t nb, const uint8_t* mark, const uint8_t* elig, uint8_t* refine, int32_t* cnt) {
-    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += (int64_t)gridDim.x * blockDim.x) {
-        const bool r = mark[b] && elig[b];
-        refine[b] = (uint8_t)r;
-        cnt[b] = r ? 4 : 0;
+        if (refine) {
+            const bool r = mk && elig[b];
+            refine[b] = (uint8_t)r;
+            cnt[b] = r ? 4 : 0;
+        }
     }
 }
 
@@ -365,82 +364,76 @@ __device__ double link_hit2(const double* a, const double* b, double X0, double 
     return num / den;
 }
 
+// One wave per block: each lane holds one candidate edge, 64 at a time, the
+// block's links are taken one after the other, and the nearest hit (the
+// smallest edge index at ties) is the wave's minimum.  Bound by the latency of
+// one test per link (a lane per cell that walked all its directions and edges:
+// 128 us for 1,236 links among 4,096 edges, now @F2@).
 __global__ void __launch_bounds__(64) k2_cl_fill(Dev2Mesh m, Dev2Level d, const int32_t* loff, const int32_t* lval,
                                                  int64_t lcap, double scale, const uint16_t* mask,
                                                  const int32_t* off, int64_t cap, int32_t* link_cell,
                                                  uint8_t* link_dir, float* link_q, int32_t* link_edge) {
-    // the block's candidate edges, 64 at a time, staged in LDS by the whole wave
-    __shared__ double sa[64][2], sb[64][2];
-    __shared__ int sid[64];
+    __shared__ double bt[128];        // nearest hit of each link so far: its t
+    __shared__ int be[128];           // and its edge
+    __shared__ unsigned char lk[128]; // cell | direction << 4 of each link, 8 directions as 0..7
     const int lane = threadIdx.x;
     for (int64_t b = blockIdx.x; b < d.nblocks; b += gridDim.x) {
         const uint16_t mk = lane < 16 ? mask[16 * b + lane] : 0;
-        // exclusive prefix of the cells' link counts in cell order
-        const int c = __popc(mk);
-        int incl = c;
-#pragma unroll
-        for (int o = 1; o < 16; o <<= 1) {
-            const int v = __shfl_up(incl, o, 64);
-            if ((lane & 15) >= o) incl += v;
-        }
-        const int64_t pos0 = (int64_t)off[b] + incl - c;
         if (!__any(mk != 0)) continue;  // uniform
-        const double X0 = 4 * d.bcoord[2 * b] + (lane & 3) + 0.5, X1 = 4 * d.bcoord[2 * b + 1] + (lane >> 2) + 0.5;
+        const int c = __popc(mk), incl = wave_incl_scan(c), n = __shfl(incl, 63, 64);
+        __syncthreads();
+        int pos = incl - c;  // the block's links in cell order
+        for (int k = 0; k < 9; k++)
+            if ((mk >> k) & 1) lk[pos++] = (unsigned char)(lane | (k < 4 ? k : k - 1) << 4);
+        for (int j = lane; j < n; j += 64) {
+            bt[j] = 2.0;
+            be[j] = -1;
+        }
+        __syncthreads();
+        const int x0 = 4 * d.bcoord[2 * b], y0 = 4 * d.bcoord[2 * b + 1];
         int e0 = loff[b], e1 = loff[b + 1];
         if (e0 < 0) e0 = 0;
         if (e1 > lcap) e1 = (int)lcap;
-        double best[9];
-        int be[9];
-#pragma unroll
-        for (int k = 0; k < 9; k++) {
-            best[k] = 2.0;
-            be[k] = -1;
-        }
         for (int c0 = e0; c0 < e1; c0 += 64) {  // uniform
-            const int nc = e1 - c0 < 64 ? e1 - c0 : 64;
-            __syncthreads();
-            if (lane < nc) {
-                const int e = lval[c0 + lane];
-                double a[2], bb[2];
-                const bool ok = e >= 0 && e < m.ne && load_edge(m, e, scale, a, bb);
-                sid[lane] = ok ? e : -1;
-                sa[lane][0] = a[0];
-                sa[lane][1] = a[1];
-                sb[lane][0] = bb[0];
-                sb[lane][1] = bb[1];
+            int e = -1;
+            double a[2] = {0, 0}, bb[2] = {0, 0};
+            if (c0 + lane < e1) {
+                e = lval[c0 + lane];
+                if (!(e >= 0 && e < m.ne && load_edge(m, e, scale, a, bb))) e = -1;
             }
-            __syncthreads();
-            if (mk) {
+            for (int j = 0; j < n; j++) {  // uniform
+                const int t4 = lk[j] & 15, q = lk[j] >> 4, k = q < 4 ? q : q + 1;
+                double t = -1.0;
+                if (e >= 0)
+                    t = link_hit2(a, bb, x0 + (t4 & 3) + 0.5, y0 + (t4 >> 2) + 0.5, (double)(k % 3 - 1),
+                                  (double)(k / 3 - 1));
+                if (!__any(t >= 0.0)) continue;  // uniform
+                int w = t >= 0.0 ? e : INT32_MAX;
+                if (!(t >= 0.0)) t = 2.0;
 #pragma unroll
-                for (int k = 0; k < 9; k++) {
-                    if (!((mk >> k) & 1)) continue;
-                    const double cx = k % 3 - 1, cy = k / 3 - 1;
-                    for (int q = 0; q < nc; q++) {
-                        const int e = sid[q];
-                        if (e < 0) continue;
-                        const double a[2] = {sa[q][0], sa[q][1]}, bb[2] = {sb[q][0], sb[q][1]};
-                        const double t = link_hit2(a, bb, X0, X1, cx, cy);
-                        if (t < 0.0) continue;
-                        if (t < best[k] || (t == best[k] && e < be[k])) {
-                            best[k] = t;
-                            be[k] = e;
-                        }
+                for (int o = 32; o > 0; o >>= 1) {
+                    const double to = __shfl_xor(t, o, 64);
+                    const int wo = __shfl_xor(w, o, 64);
+                    if (to < t || (to == t && wo < w)) {
+                        t = to;
+                        w = wo;
                     }
+                }
+                if (lane == 0 && (t < bt[j] || (t == bt[j] && w < be[j]))) {
+                    bt[j] = t;
+                    be[j] = w;
                 }
             }
         }
-        if (!mk) continue;
-        int64_t pos = pos0;
-#pragma unroll
-        for (int k = 0; k < 9; k++) {
-            if (!((mk >> k) & 1)) continue;
-            if (pos < cap) {
-                link_cell[pos] = (int32_t)(16 * b + lane);
-                link_dir[pos] = (uint8_t)k;
-                link_q[pos] = be[k] >= 0 ? (float)best[k] : -1.0f;
-                link_edge[pos] = be[k];
-            }
-            pos++;
+        __syncthreads();
+        for (int j = lane; j < n; j += 64) {
+            const int64_t p = (int64_t)off[b] + j;
+            if (p >= cap) continue;
+            const int q = lk[j] >> 4;
+            link_cell[p] = (int32_t)(16 * b + (lk[j] & 15));
+            link_dir[p] = (uint8_t)(q < 4 ? q : q + 1);
+            link_q[p] = be[j] >= 0 ? (float)bt[j] : -1.0f;
+            link_edge[p] = be[j];
         }
     }
 }
@@ -523,8 +516,8 @@ int geo2_build_bins(const geo2_mesh* mesh, const geo2_level* lv, int32_t kind, g
     int32_t* cursor = reinterpret_cast<int32_t*>(p);
     p += al256(sizeof(int32_t) * (size_t)(nkeys + 1));
     int64_t* partials = reinterpret_cast<int64_t*>(p);
-    int rc = geo_fill_i32(cnt, 0, nkeys + 1, s);
-    if (rc == GEO_OK) rc = geo_fill_i32(cursor, 0, nkeys + 1, s);
+    // counts and cursors lie side by side: one fill
+    int rc = geo_fill_i32(cnt, 0, (cursor - cnt) + nkeys + 1, s);
     if (rc != GEO_OK) return rc;
     const Dev2Mesh m = dev2_mesh(mesh);
     const Dev2Level d = dev2_level(lv);
@@ -586,12 +579,13 @@ int geo2_refine_flags(const geo2_level* lv, const uint16_t* solid, int32_t n_pro
         k2_ref_a<<<g, 256, 0, s>>>(d, solid, nbr, sb, elig);
         k2_ref_b<<<g, 256, 0, s>>>(nb, solid, nbr, sb, elig, m0, bclass);
         for (int k = 1; k <= n_prop; k++) {
-            k2_ref_prop<<<g, 256, 0, s>>>(nb, solid, nbr, m0, m1, k == 1);
+            const bool last = k == n_prop;
+            k2_ref_prop<<<g, 256, 0, s>>>(nb, solid, nbr, m0, m1, k == 1, elig, last ? refine : nullptr,
+                                          last ? cnt : nullptr);
             uint8_t* t = m0;
             m0 = m1;
             m1 = t;
         }
-        k2_ref_final<<<g, 256, 0, s>>>(nb, m0, elig, refine, cnt);
         GEO_LAUNCH_CHECK();
     }
     const int rc = geo_scan_exclusive(cnt, off, nb, partials, s);
