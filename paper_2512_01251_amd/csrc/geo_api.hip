@@ -11,20 +11,22 @@ namespace {
 
 inline size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// A bin build's workspace: staged pairs, ranks, key counts, scan partials (each
-// level's scan may end in a tile of its own), the list of large triangles'
-// pieces, the statistics slots, the counters.
-size_t bin_partials_bytes(int64_t nkeys) { return geo_scan_partials_bytes(nkeys) + sizeof(int64_t) * GEO_MAX_LEVELS; }
+// A bin build's workspace: staged pairs, ranks, key counts, scan partials (with
+// several levels each one's scan may end in a tile of its own), the list of
+// large triangles' pieces, the statistics slots, the counters.
+size_t bin_partials_bytes(int64_t nkeys, bool levels) {
+    return al(geo_scan_partials_bytes(nkeys)) + (levels ? al(sizeof(int64_t) * GEO_MAX_LEVELS) : 0);
+}
 
-size_t bins_ws_bytes(int64_t nkeys, int64_t cap) {
+size_t bins_ws_bytes(int64_t nkeys, int64_t cap, bool levels) {
     const size_t c = (size_t)(cap > 0 ? cap : 0);
     return al(sizeof(int2) * c) + al(sizeof(int32_t) * c) + al(sizeof(int32_t) * ((size_t)nkeys + 1)) +
-           al(bin_partials_bytes(nkeys)) + al(sizeof(int4) * BIN_LIST_CAP) +
+           bin_partials_bytes(nkeys, levels) + al(sizeof(int4) * BIN_LIST_CAP) +
            al(sizeof(unsigned long long) * ROW_SLOTS * ROW_SLOT_WORDS) + al(sizeof(BinCtl));
 }
 
 // its parts (bins_ws_bytes of workspace); partials: the scan's
-BinWork bin_work(void* ws, int64_t nkeys, int64_t cap, bool stats, int64_t*& partials) {
+BinWork bin_work(void* ws, int64_t nkeys, int64_t cap, bool levels, bool stats, int64_t*& partials) {
     BinWork w{};
     char* p = static_cast<char*>(ws);
     w.cap = cap;
@@ -35,7 +37,7 @@ BinWork bin_work(void* ws, int64_t nkeys, int64_t cap, bool stats, int64_t*& par
     w.cnt = reinterpret_cast<int32_t*>(p);
     p += al(sizeof(int32_t) * ((size_t)nkeys + 1));
     partials = reinterpret_cast<int64_t*>(p);
-    p += al(bin_partials_bytes(nkeys));
+    p += bin_partials_bytes(nkeys, levels);
     w.list = reinterpret_cast<int4*>(p);
     p += al(sizeof(int4) * BIN_LIST_CAP);
     w.slots = stats ? reinterpret_cast<unsigned long long*>(p) : nullptr;
@@ -81,6 +83,56 @@ int64_t row_keys(const geo_level* lv) {
     return ((int64_t)lv->n0[1] << lv->level) * ((int64_t)lv->n0[2] << lv->level);
 }
 
+// The row bins of one or more levels in one pass over the triangles. levels:
+// the workspace has room for several levels' scans, which one level's build
+// through geo_build_bins does without.
+int build_rows(const geo_mesh* mesh, const int32_t n0[3], int32_t lmin, int32_t nlev, bool levels, int32_t precision,
+               const geo_bins* out, uint64_t* d_stats, void* ws, size_t ws_bytes, geo_stream_t stream) {
+    if (!check_mesh(mesh) || !n0 || !out) return GEO_ERR_ARG;
+    if (lmin < 0 || nlev < 1 || lmin + nlev > GEO_MAX_LEVELS) return GEO_ERR_ARG;
+    if (precision != GEO_PREC_F64 && precision != GEO_PREC_F32_FALLBACK) return GEO_ERR_ARG;
+    geo_level lv{};
+    for (int a = 0; a < 3; a++) lv.n0[a] = n0[a];
+    lv.level = lmin + nlev - 1;  // the finest level bounds the resolution
+    if (!check_level(&lv)) return GEO_ERR_ARG;
+    RowLevels rl{};
+    rl.nlev = nlev;
+    rl.lmin = lmin;
+    int64_t nkeys = 0, cap = 0;
+    for (int l = 0; l < nlev; l++) {
+        lv.level = lmin + l;
+        const int64_t nk = row_keys(&lv);
+        if (!check_bins(&out[l], GEO_BINS_ROWS, nk)) return GEO_ERR_ARG;
+        for (int q = 0; q < l; q++)
+            if (out[q].d_count == out[l].d_count) return GEO_ERR_ARG;  // each level counts on its own
+        rl.base[l] = (int)nkeys;
+        nkeys += nk;
+        if (nkeys + 1 > INT32_MAX) return GEO_ERR_ARG;
+        rl.off[l] = out[l].off;
+        rl.val[l] = out[l].val;
+        rl.cap[l] = out[l].cap;
+        cap += out[l].cap;
+    }
+    for (int l = nlev; l <= GEO_MAX_LEVELS; l++) rl.base[l] = (int)nkeys;
+    if (ws_bytes < bins_ws_bytes(nkeys, cap, levels) || (!ws && ws_bytes)) return GEO_ERR_WORKSPACE;
+    hipStream_t s = (hipStream_t)stream;
+    int64_t* partials;
+    const BinWork w = bin_work(ws, nkeys, cap, levels, d_stats != nullptr, partials);
+    lv.level = lmin;
+    const DevMesh m = dev_mesh(mesh);
+    const DevLevel d = dev_level(&lv);
+    int rc;
+    if ((rc = launch_bins_zero(w, nkeys, s)) != GEO_OK) return rc;
+    if ((rc = launch_check_mesh(m, d, d_stats, s)) != GEO_OK) return rc;
+    if ((rc = launch_rows_levels(m, d, precision, rl, w, s)) != GEO_OK) return rc;
+    // the counts of every key are complete whatever fits the pair array, so
+    // the scans' totals are the entries needed
+    ScanJobs jobs{};
+    for (int l = 0; l < nlev; l++) jobs.add(w.cnt + rl.base[l], out[l].off, out[l].nkeys, out[l].d_count);
+    if ((rc = geo_scan_jobs(jobs, partials, s)) != GEO_OK) return rc;
+    return launch_rows_levels_scatter(rl, w, d_stats, s);
+}
+
 }  // namespace
 
 extern "C" {
@@ -89,8 +141,8 @@ size_t geo_workspace_size(int32_t call, int64_t nkeys, int64_t cap) {
     if (nkeys < 0) return 0;
     switch (call) {
         case GEO_CALL_BINS_ROWS:
-        case GEO_CALL_BINS_LINKS:
-        case GEO_CALL_BINS_ROWS_LEVELS: return bins_ws_bytes(nkeys, cap);
+        case GEO_CALL_BINS_LINKS: return bins_ws_bytes(nkeys, cap, false);
+        case GEO_CALL_BINS_ROWS_LEVELS: return bins_ws_bytes(nkeys, cap, true);
         case GEO_CALL_REFINE: return geo_refine_ws_bytes(nkeys);
         case GEO_CALL_CUTLINKS: return geo_cutlinks_ws_bytes(nkeys, cap);
         case GEO_CALL_LINKS_DENSE: return geo_dense_ws_bytes(nkeys);
@@ -133,11 +185,11 @@ int geo_build_bins(const geo_mesh* mesh, const geo_level* lv, int32_t kind, int3
     if (!check_bins(out, kind, nkeys)) return GEO_ERR_ARG;
     if (nkeys + 1 > INT32_MAX) return GEO_ERR_ARG;
     if (kind == GEO_BINS_ROWS)  // the joint build of one level
-        return geo_build_row_bins_levels(mesh, lv->n0, lv->level, 1, precision, out, d_stats, ws, ws_bytes, stream);
-    if (ws_bytes < bins_ws_bytes(nkeys, out->cap) || (!ws && ws_bytes)) return GEO_ERR_WORKSPACE;
+        return build_rows(mesh, lv->n0, lv->level, 1, false, precision, out, d_stats, ws, ws_bytes, stream);
+    if (ws_bytes < bins_ws_bytes(nkeys, out->cap, false) || (!ws && ws_bytes)) return GEO_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     int64_t* partials;
-    const BinWork w = bin_work(ws, nkeys, out->cap, false, partials);
+    const BinWork w = bin_work(ws, nkeys, out->cap, false, false, partials);
     const DevMesh m = dev_mesh(mesh);
     const DevLevel d = dev_level(lv);
     int rc;
@@ -152,49 +204,7 @@ int geo_build_bins(const geo_mesh* mesh, const geo_level* lv, int32_t kind, int3
 int geo_build_row_bins_levels(const geo_mesh* mesh, const int32_t n0[3], int32_t lmin, int32_t nlev,
                               int32_t precision, const geo_bins* out, uint64_t* d_stats, void* ws, size_t ws_bytes,
                               geo_stream_t stream) {
-    if (!check_mesh(mesh) || !n0 || !out) return GEO_ERR_ARG;
-    if (lmin < 0 || nlev < 1 || lmin + nlev > GEO_MAX_LEVELS) return GEO_ERR_ARG;
-    if (precision != GEO_PREC_F64 && precision != GEO_PREC_F32_FALLBACK) return GEO_ERR_ARG;
-    geo_level lv{};
-    for (int a = 0; a < 3; a++) lv.n0[a] = n0[a];
-    lv.level = lmin + nlev - 1;  // the finest level bounds the resolution
-    if (!check_level(&lv)) return GEO_ERR_ARG;
-    RowLevels rl{};
-    rl.nlev = nlev;
-    rl.lmin = lmin;
-    int64_t nkeys = 0, cap = 0;
-    for (int l = 0; l < nlev; l++) {
-        lv.level = lmin + l;
-        const int64_t nk = row_keys(&lv);
-        if (!check_bins(&out[l], GEO_BINS_ROWS, nk)) return GEO_ERR_ARG;
-        for (int q = 0; q < l; q++)
-            if (out[q].d_count == out[l].d_count) return GEO_ERR_ARG;  // each level counts on its own
-        rl.base[l] = (int)nkeys;
-        nkeys += nk;
-        if (nkeys + 1 > INT32_MAX) return GEO_ERR_ARG;
-        rl.off[l] = out[l].off;
-        rl.val[l] = out[l].val;
-        rl.cap[l] = out[l].cap;
-        cap += out[l].cap;
-    }
-    for (int l = nlev; l <= GEO_MAX_LEVELS; l++) rl.base[l] = (int)nkeys;
-    if (ws_bytes < bins_ws_bytes(nkeys, cap) || (!ws && ws_bytes)) return GEO_ERR_WORKSPACE;
-    hipStream_t s = (hipStream_t)stream;
-    int64_t* partials;
-    const BinWork w = bin_work(ws, nkeys, cap, d_stats != nullptr, partials);
-    lv.level = lmin;
-    const DevMesh m = dev_mesh(mesh);
-    const DevLevel d = dev_level(&lv);
-    int rc;
-    if ((rc = launch_bins_zero(w, nkeys, s)) != GEO_OK) return rc;
-    if ((rc = launch_check_mesh(m, d, d_stats, s)) != GEO_OK) return rc;
-    if ((rc = launch_rows_levels(m, d, precision, rl, w, s)) != GEO_OK) return rc;
-    // the counts of every key are complete whatever fits the pair array, so
-    // the scans' totals are the entries needed
-    ScanJobs jobs{};
-    for (int l = 0; l < nlev; l++) jobs.add(w.cnt + rl.base[l], out[l].off, out[l].nkeys, out[l].d_count);
-    if ((rc = geo_scan_jobs(jobs, partials, s)) != GEO_OK) return rc;
-    return launch_rows_levels_scatter(rl, w, d_stats, s);
+    return build_rows(mesh, n0, lmin, nlev, true, precision, out, d_stats, ws, ws_bytes, stream);
 }
 
 int geo_voxelize(const geo_level* lv, const geo_bins* rows, uint64_t* solid, geo_stream_t stream) {
