@@ -261,10 +261,15 @@ __global__ void k2_ref_b(int64_t nb, const uint16_t* solid, const int32_t* nbr, 
 }
 
 // one propagation pass; the last one (refine != null) also writes refine =
-// marked and eligible, and the number of children for their scan
-__global__ void k2_ref_prop(int64_t nb, const uint16_t* solid, const int32_t* nbr, const uint8_t* mark_in,
-                            uint8_t* mark_out, int first, const uint8_t* elig, uint8_t* refine, int32_t* cnt) {
-    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += (int64_t)gridDim.x * blockDim.x) {
+// marked and eligible, and its tile's refined blocks for the children's places
+__global__ void __launch_bounds__(256) k2_ref_prop(int64_t nb, int passes, const uint16_t* solid, const int32_t* nbr,
+                                                   const uint8_t* mark_in, uint8_t* mark_out, int first,
+                                                   const uint8_t* elig, uint8_t* refine, int32_t* counts) {
+    __shared__ int tmp[4];
+    int n_ref = 0;
+    for (int p = 0; p < passes; p++) {
+        const int64_t b = ((int64_t)blockIdx.x * passes + p) * 256 + threadIdx.x;
+        if (b >= nb) break;
         bool mk = mark_in[b];
         if (!mk && (solid[b] == 0 || first))
             for (int n = 0; n < NB8; n++) {
@@ -275,26 +280,19 @@ __global__ void k2_ref_prop(int64_t nb, const uint16_t* solid, const int32_t* nb
         if (refine) {
             const bool r = mk && elig[b];
             refine[b] = (uint8_t)r;
-            cnt[b] = r ? 4 : 0;
+            n_ref += r;
         }
     }
+    if (!refine) return;
+    n_ref = wg_sum256(n_ref, tmp);
+    if (threadIdx.x == 0) counts[blockIdx.x] = n_ref;
 }
 
-__global__ void k2_ref_emit(Dev2Level d, const uint8_t* refine, const int32_t* off, int32_t* child_map,
-                            int32_t* child_bcoord, int64_t* d_nchild) {
-    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < d.nblocks; b += (int64_t)gridDim.x * blockDim.x) {
-        if (!refine[b]) {
-            child_map[b] = -1;
-            continue;
-        }
-        const int c = off[b];
-        child_map[b] = c;
-        for (int o = 0; o < 4; o++) {
-            child_bcoord[2 * (int64_t)(c + o)] = 2 * d.bcoord[2 * b] + (o & 1);
-            child_bcoord[2 * (int64_t)(c + o) + 1] = 2 * d.bcoord[2 * b + 1] + (o >> 1);
-        }
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *d_nchild = off[d.nblocks];
+// the children, tile by tile
+__global__ void __launch_bounds__(256) k2_ref_emit(int64_t nb, const int32_t* bcoord, const uint8_t* refine,
+                                                   const int32_t* counts, int passes, int32_t* child_map,
+                                                   int32_t* child_bcoord, int64_t* d_nchild) {
+    emit_children<2>(nb, bcoord, refine, counts, passes, child_map, child_bcoord, d_nchild);
 }
 
 // --------------------------------------------------------------------------
@@ -368,7 +366,7 @@ __device__ double link_hit2(const double* a, const double* b, double X0, double 
 // block's links are taken one after the other, and the nearest hit (the
 // smallest edge index at ties) is the wave's minimum.  Bound by the latency of
 // one test per link (a lane per cell that walked all its directions and edges:
-// 128 us for 1,236 links among 4,096 edges, now @F2@).
+// 128 us for 1,236 links among 4,096 edges, now 26 us).
 __global__ void __launch_bounds__(64) k2_cl_fill(Dev2Mesh m, Dev2Level d, const int32_t* loff, const int32_t* lval,
                                                  int64_t lcap, double scale, const uint16_t* mask,
                                                  const int32_t* off, int64_t cap, int32_t* link_cell,
@@ -481,7 +479,7 @@ size_t geo2_bins_ws_bytes(int64_t nkeys) {
 
 size_t geo2_refine_ws_bytes(int64_t nb) {
     return al256(sizeof(int32_t) * NB8 * (size_t)nb) + 4 * al256((size_t)nb) +
-           2 * al256(sizeof(int32_t) * (size_t)(nb + 1)) + al256(geo_scan_partials_bytes(nb));
+           al256(sizeof(int32_t) * child_tiles(nb));
 }
 
 size_t geo2_cutlinks_ws_bytes(int64_t nb) {
@@ -568,29 +566,24 @@ int geo2_refine_flags(const geo2_level* lv, const uint16_t* solid, int32_t n_pro
     p += al256((size_t)nb);
     uint8_t* m1 = reinterpret_cast<uint8_t*>(p);
     p += al256((size_t)nb);
-    int32_t* cnt = reinterpret_cast<int32_t*>(p);
-    p += al256(sizeof(int32_t) * (size_t)(nb + 1));
-    int32_t* off = reinterpret_cast<int32_t*>(p);
-    p += al256(sizeof(int32_t) * (size_t)(nb + 1));
-    int64_t* partials = reinterpret_cast<int64_t*>(p);
+    int32_t* counts = reinterpret_cast<int32_t*>(p);
     const Dev2Level d = dev2_level(lv);
-    const unsigned g = grid1(nb, 256, 16384);
+    const unsigned g = grid1(nb, 256, 16384), tiles = child_tiles(nb);
+    const int passes = child_passes(nb);
     if (nb > 0) {
         k2_ref_a<<<g, 256, 0, s>>>(d, solid, nbr, sb, elig);
         k2_ref_b<<<g, 256, 0, s>>>(nb, solid, nbr, sb, elig, m0, bclass);
         for (int k = 1; k <= n_prop; k++) {
             const bool last = k == n_prop;
-            k2_ref_prop<<<g, 256, 0, s>>>(nb, solid, nbr, m0, m1, k == 1, elig, last ? refine : nullptr,
-                                          last ? cnt : nullptr);
+            k2_ref_prop<<<tiles, 256, 0, s>>>(nb, passes, solid, nbr, m0, m1, k == 1, elig,
+                                              last ? refine : nullptr, last ? counts : nullptr);
             uint8_t* t = m0;
             m0 = m1;
             m1 = t;
         }
         GEO_LAUNCH_CHECK();
     }
-    const int rc = geo_scan_exclusive(cnt, off, nb, partials, s);
-    if (rc != GEO_OK) return rc;
-    k2_ref_emit<<<g, 256, 0, s>>>(d, refine, off, child_map, child_bcoord, d_nchild);
+    k2_ref_emit<<<tiles, 256, 0, s>>>(nb, d.bcoord, refine, counts, passes, child_map, child_bcoord, d_nchild);
     GEO_LAUNCH_CHECK();
     return GEO_OK;
 }

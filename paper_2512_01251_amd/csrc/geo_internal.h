@@ -307,6 +307,84 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
     return v;
 }
 
+// The refined blocks of a level take their children's places without a scan of
+// their own: the pass that decides which blocks are refined counts them per
+// tile of 256 * child_passes(nb) consecutive blocks (one workgroup of 256
+// lanes), and the pass that emits the children starts each tile at the sum of
+// the counts before it.  At most CHILD_TILES tiles, which fill the chip once
+// (8 workgroups on each of 256 CUs), so that sum is at most 8 loads per lane.
+constexpr int CHILD_TILES = 2048;
+static inline int child_passes(int64_t nb) {
+    return nb > 0 ? (int)((nb + 256 * CHILD_TILES - 1) / (256 * CHILD_TILES)) : 1;
+}
+static inline unsigned child_tiles(int64_t nb) {
+    const int64_t t = 256 * (int64_t)child_passes(nb);
+    return nb > 0 ? (unsigned)((nb + t - 1) / t) : 1;
+}
+
+// the sum over a workgroup of 256 lanes; tmp: 4 words of LDS
+__device__ __forceinline__ int wg_sum256(int v, int* tmp) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) tmp[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return tmp[0] + tmp[1] + tmp[2] + tmp[3];
+}
+
+// One pass of a tile: the workgroup's refined blocks are numbered in block
+// order and twice their D coordinates kept in pc (256 * D words of LDS);
+// before: the number of this lane's block; returns their count.  tmp: 4 words.
+template <int D>
+__device__ __forceinline__ int child_pass(bool r, int64_t b, const int32_t* bcoord, int32_t* pc, int* tmp,
+                                          int& before) {
+    const int wv = threadIdx.x >> 6;
+    const unsigned long long m = __ballot(r);
+    if ((threadIdx.x & 63) == 0) tmp[wv] = __popcll(m);
+    __syncthreads();
+    before = __popcll(m & ((1ull << (threadIdx.x & 63)) - 1));
+    int tot = 0;
+#pragma unroll
+    for (int w = 0; w < 4; w++) {
+        if (w < wv) before += tmp[w];
+        tot += tmp[w];
+    }
+    if (r)
+#pragma unroll
+        for (int a = 0; a < D; a++) pc[D * before + a] = 2 * bcoord[D * b + a];
+    __syncthreads();
+    return tot;
+}
+
+// A tile's children: the child map of its blocks and its children's
+// coordinates, which are consecutive words, written lane by lane.
+template <int D>
+__device__ __forceinline__ void emit_children(int64_t nb, const int32_t* bcoord, const uint8_t* refine,
+                                              const int32_t* counts, int passes, int32_t* child_map,
+                                              int32_t* child_bcoord, int64_t* d_nchild) {
+    constexpr int NC = 1 << D;
+    __shared__ int32_t pc[256 * D];
+    __shared__ int tmp[4];
+    int n = 0;
+    for (unsigned i = threadIdx.x; i < blockIdx.x; i += 256) n += counts[i];
+    int64_t base = wg_sum256(n, tmp);
+    __syncthreads();
+    for (int p = 0; p < passes; p++) {
+        const int64_t b = ((int64_t)blockIdx.x * passes + p) * 256 + threadIdx.x;
+        const bool r = b < nb && refine[b];
+        int before;
+        const int tot = child_pass<D>(r, b, bcoord, pc, tmp, before);
+        if (b < nb) child_map[b] = r ? (int32_t)(NC * (base + before)) : -1;
+        int32_t* out = child_bcoord + NC * D * base;
+        for (int i = threadIdx.x; i < NC * D * tot; i += 256) {
+            const int c = i / D, a = i - D * c;
+            out[i] = pc[D * (c / NC) + a] + ((c >> a) & 1);
+        }
+        base += tot;
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *d_nchild = NC * base;
+}
+
 // inclusive prefix maximum of non-negative v over the wave, by the same steps
 __device__ __forceinline__ int wave_incl_max(int v) {
     auto mx = [](int a, int b) { return a > b ? a : b; };
