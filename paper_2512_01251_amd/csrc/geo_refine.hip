@@ -30,7 +30,11 @@ __device__ __forceinline__ void nbr_offset(int k, int& dx, int& dy, int& dz) {
 // parents, the 2x2x2 parents from (b-1) >> 1 to (b+1) >> 1 on each axis: the
 // first-child indices of those 8 are found by 8 descents of the forest run
 // side by side (their dependent loads overlap), and each neighbour is its
-// parent's first child plus its octant, with no further load.
+// parent's first child plus its octant, with no further load.  The parent of a
+// neighbour is a register, chosen by the block's parity; only a solid block
+// reads its neighbours' words, all at once.  Latency bound: 20.4 -> 14.3 us a
+// level for the 1.05M-triangle star on 192 x 200 x 176 cells (indexed parents
+// in scratch and 26 dependent words before).
 __global__ void k_ref_nbr(DevLevel d, const uint64_t* solid, int32_t* nbr, uint8_t* cls) {
     const int64_t nb = d.nblocks;
     const int L = d.level;
@@ -40,18 +44,18 @@ __global__ void k_ref_nbr(DevLevel d, const uint64_t* solid, int32_t* nbr, uint8
         // class bits from the neighbours' solid words: solid-boundary (solid
         // with a fully fluid neighbour) and eligible (every in-domain
         // neighbour exists)
-        bool fluid_nbr = false, elig = true;
-        auto note = [&](int n) {
-            if (n == -1) elig = false;
-            if (n >= 0 && solid[n] == 0ull) fluid_nbr = true;
-        };
+        int r[26];
         if (L == 0) {  // the dense root grid: no loads
+#pragma unroll
             for (int k = 0; k < 26; k++) {
                 int dx, dy, dz;
                 nbr_offset(k, dx, dy, dz);
-                const int n = forest_lookup(d, bc[0] + dx, bc[1] + dy, bc[2] + dz);
-                nbr[(int64_t)k * nb + b] = n;
-                note(n);
+                const int n[3] = {bc[0] + dx, bc[1] + dy, bc[2] + dz};
+                bool out = false;
+#pragma unroll
+                for (int a = 0; a < 3; a++)
+                    if (n[a] < 0 || n[a] >= nb0[a]) out = true;
+                r[k] = out ? -2 : n[0] + nb0[0] * (n[1] + nb0[1] * n[2]);
             }
         } else {
             int p0[3];  // lowest parent coordinate per axis (level L-1)
@@ -62,6 +66,7 @@ __global__ void k_ref_nbr(DevLevel d, const uint64_t* solid, int32_t* nbr, uint8
             for (int s = 0; s < 8; s++) {
                 const int p[3] = {p0[0] + (s & 1), p0[1] + ((s >> 1) & 1), p0[2] + (s >> 2)};
                 inside[s] = true;
+#pragma unroll
                 for (int a = 0; a < 3; a++)
                     if (p[a] < 0 || p[a] >= (nb0[a] << (L - 1))) inside[s] = false;
                 idx[s] = inside[s] ? (p[0] >> (L - 1)) + nb0[0] * ((p[1] >> (L - 1)) + nb0[1] * (p[2] >> (L - 1)))
@@ -83,41 +88,80 @@ __global__ void k_ref_nbr(DevLevel d, const uint64_t* solid, int32_t* nbr, uint8
                     }
                 }
             }
+            // the parents seen from the block: per axis the lower one at -1, the
+            // upper one at +1, and at 0 the block's own
+            int fc[27];
+#pragma unroll
+            for (int s = 0; s < 8; s++) fc[2 * (s & 1) + 6 * ((s >> 1) & 1) + 18 * (s >> 2)] = idx[s];
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const int z = 6 * (q & 1) + 18 * (q >> 1);
+                fc[z + 1] = (bc[0] & 1) ? fc[z] : fc[z + 2];
+            }
+#pragma unroll
+            for (int q = 0; q < 6; q++) {
+                const int z = q % 3 + 18 * (q / 3);
+                fc[z + 3] = (bc[1] & 1) ? fc[z] : fc[z + 6];
+            }
+#pragma unroll
+            for (int q = 0; q < 9; q++) fc[q + 9] = (bc[2] & 1) ? fc[q] : fc[q + 18];
+#pragma unroll
             for (int k = 0; k < 26; k++) {
                 int dv[3];
                 nbr_offset(k, dv[0], dv[1], dv[2]);
-                int n[3], s = 0;
+                int n[3];
                 bool out = false;
+#pragma unroll
                 for (int a = 0; a < 3; a++) {
                     n[a] = bc[a] + dv[a];
                     if (n[a] < 0 || n[a] >= (nb0[a] << L)) out = true;
-                    s |= ((n[a] >> 1) - p0[a]) << a;
                 }
-                int r = -2;
-                if (!out) {
-                    const int fc = idx[s];
-                    r = fc < 0 ? -1 : fc + ((n[0] & 1) | ((n[1] & 1) << 1) | ((n[2] & 1) << 2));
-                }
-                nbr[(int64_t)k * nb + b] = r;
-                note(r);
+                const int f = fc[k < 13 ? k : k + 1];
+                r[k] = out ? -2 : f < 0 ? -1 : f + ((n[0] & 1) | ((n[1] & 1) << 1) | ((n[2] & 1) << 2));
             }
         }
-        const bool is_solid = solid[b] != 0ull;
-        uint8_t g = is_solid ? F_S : 0;
-        if (is_solid && fluid_nbr) g |= F_SB;
-        if (elig) g |= F_EL;
+        bool elig = true;
+#pragma unroll
+        for (int k = 0; k < 26; k++) {
+            nbr[(int64_t)k * nb + b] = r[k];
+            if (r[k] == -1) elig = false;
+        }
+        uint8_t g = elig ? F_EL : 0;
+        if (solid[b] != 0ull) {  // a fluid block's class needs no neighbour
+            bool fluid_nbr = false;
+#pragma unroll
+            for (int k = 0; k < 26; k++) {
+                const uint64_t w = solid[r[k] >= 0 ? r[k] : b];  // its own word is not 0
+                if (w == 0ull) fluid_nbr = true;
+            }
+            g |= fluid_nbr ? F_S | F_SB : F_S;
+        }
         cls[b] = g;
     }
+}
+
+// Whether a neighbour of block b has a bit of a byte array.  Latency bound: all
+// 26 indices and then all 26 bytes are loaded at once.  One by one, each
+// waiting for the last, the marks of a level took 14.7 us and a propagation
+// pass 13.1 us on average (1.05M-triangle star, 192 x 200 x 176 cells), now 7.1
+// and 7.0; 10.5 and 7.4 us against 3.1 and 3.6 with 1,792 triangles.
+__device__ __forceinline__ bool near_bit(int64_t nb, const int32_t* nbr, int64_t b, const uint8_t* v, unsigned bit) {
+    int n[26];
+#pragma unroll
+    for (int k = 0; k < 26; k++) n[k] = nbr[(int64_t)k * nb + b];
+    unsigned any = 0;
+#pragma unroll
+    for (int k = 0; k < 26; k++) {
+        const unsigned x = v[n[k] >= 0 ? n[k] : b];
+        any |= n[k] >= 0 ? x : 0u;
+    }
+    return (any & bit) != 0;
 }
 
 __global__ void k_ref_m1(int64_t nb, const int32_t* nbr, const uint8_t* flags, uint8_t* M, uint8_t* bclass) {
     for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += (int64_t)gridDim.x * blockDim.x) {
         const uint8_t f = flags[b];
-        bool adj = false;
-        for (int k = 0; k < 26; k++) {
-            const int n = nbr[(int64_t)k * nb + b];
-            if (n >= 0 && (flags[n] & F_SB)) adj = true;
-        }
+        const bool adj = near_bit(nb, nbr, b, flags, F_SB);
         const bool m0 = (f & F_SB) && (f & F_EL);
         const bool m = m0 || adj;
         M[b] = m ? 1 : 0;
@@ -138,12 +182,7 @@ __global__ void __launch_bounds__(256) k_ref_prop(int64_t nb, int passes, const 
         if (b >= nb) break;
         uint8_t m = Min[b];
         const uint8_t f = flags[b];
-        if (!m && (!(f & F_S) || first)) {
-            for (int k = 0; k < 26; k++) {
-                const int n = nbr[(int64_t)k * nb + b];
-                if (n >= 0 && Min[n]) { m = 1; break; }
-            }
-        }
+        if (!m && (!(f & F_S) || first)) m = near_bit(nb, nbr, b, Min, 1);
         Mout[b] = m;
         if (refine) {
             const int r = (m && (f & F_EL)) ? 1 : 0;
@@ -173,9 +212,9 @@ __global__ void __launch_bounds__(256) k_ref_final(int64_t nb, int passes, const
 }
 
 // The children, tile by tile: 6.3 us a level where a star of 1.05M triangles on
-// 192 x 200 x 176 cells is refined, launch and latency bound (with a scan of its own, two
-// launches and 9.6 us more, and a lane per block writing its 24 words apart,
-// 7.0 us).
+// 192 x 200 x 176 cells is refined, launch and latency bound (with a scan of its
+// own, two launches and 9.6 us more, and a lane per block writing its 24 words
+// apart, 7.0 us).
 __global__ void __launch_bounds__(256) k_ref_emit(int64_t nb, const int32_t* bcoord, const uint8_t* refine,
                                                   const int32_t* counts, int passes, int32_t* child_map,
                                                   int32_t* child_bcoord, int64_t* d_nchild) {
