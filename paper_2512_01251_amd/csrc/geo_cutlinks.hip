@@ -179,7 +179,18 @@ __device__ __forceinline__ int block_tasks(int n, int nc) {
     return n > 0 ? ((n + 63) / 64) * (nc > CL_CAND ? (nc + CL_CAND - 1) / CL_CAND : 1) : 0;
 }
 
-__global__ void __launch_bounds__(64) k_cl_mask(DevLevel d, const int32_t* off, const int32_t* val, int64_t cap,
+// Blocks of a wave's chunk: 64, one coalesced read of their candidate counts,
+// where that leaves MASK_WAVES waves (about all that the chip holds at once);
+// fewer on smaller levels, where a wave's blocks are a chain of row-bin loads
+// and most of the chip would idle: 35.6 -> 8.0 us for a star of 1,792 triangles.
+constexpr int64_t MASK_WAVES = 8192;
+static inline int mask_chunk(int64_t nblocks) {
+    int c = 64;
+    while (c > 2 && nblocks < c * MASK_WAVES) c >>= 1;
+    return c;
+}
+
+__global__ void __launch_bounds__(64) k_cl_mask(DevLevel d, int chunk, const int32_t* off, const int32_t* val, int64_t cap,
                                                 const int32_t* loff, int64_t lcap, int lattice, uint32_t* wmask,
                                                 int zero_fill, int32_t* blk_cnt, int32_t* ntask, int32_t* fixn) {
     __shared__ unsigned halo[72];
@@ -187,13 +198,13 @@ __global__ void __launch_bounds__(64) k_cl_mask(DevLevel d, const int32_t* off, 
     if (blockIdx.x == 0 && threadIdx.x < 2) fixn[threadIdx.x] = 0;
     const uint32_t dirs = lattice_dirs(lattice);
     const int lane = threadIdx.x;
-    const int64_t nchunks = (d.nblocks + 63) / 64;
-    // chunks of 64 blocks: one coalesced read of their candidate counts, then
-    // only the blocks with candidates are classified, two per wave step
+    const int64_t nchunks = (d.nblocks + chunk - 1) / chunk;
+    // one coalesced read of a chunk's candidate counts, then only the blocks
+    // with candidates are classified, two per wave step
     for (int64_t ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
-        const int64_t b0 = ch * 64;
+        const int64_t b0 = ch * chunk;
         const int64_t bl = b0 + lane;
-        const bool inb = bl < d.nblocks;
+        const bool inb = lane < chunk && bl < d.nblocks;
         // a cut link crosses the surface inside the block's reach, so a block
         // without candidate triangles has none
         const bool has = inb && loff[bl] != loff[bl + 1];
@@ -1383,9 +1394,10 @@ int launch_cutlinks(const DevMesh& m, const DevLevel& d, const geo_bins* rows, c
     int2* pairq = reinterpret_cast<int2*>(p);
     if (nb == 0) return geo_fill_u64(reinterpret_cast<uint64_t*>(d_nlinks), 0, 1, s);
     uint32_t* wmask = link_mask ? link_mask : ws_mask;
-    const int64_t nchunk = (nb + 63) / 64;
+    const int chunk = mask_chunk(nb);
+    const int64_t nchunk = (nb + chunk - 1) / chunk;
     const unsigned g = (unsigned)(nchunk < 32768 ? nchunk : 32768);
-    k_cl_mask<<<g, 64, 0, s>>>(d, rows->off, rows->val, rows->cap, links->off, links->cap, lattice, wmask,
+    k_cl_mask<<<g, 64, 0, s>>>(d, chunk, rows->off, rows->val, rows->cap, links->off, links->cap, lattice, wmask,
                                link_mask ? 1 : 0, blk_cnt, ntask, fixn);
     GEO_LAUNCH_CHECK();
     // the link count is exact in 64 bits (the table's offsets are int32)
