@@ -825,6 +825,7 @@ __global__ void __launch_bounds__(64) k_cl_multi(int64_t nb, const int32_t* blk_
         if (b < nb && candidates(loff, lcap, b) > CL_CAND) {
             p0 = blk_off[b];
             p1 = blk_off[b + 1];
+            if (p0 < 0) p0 = 0;  // offsets past 2^31 - 1 links wrap
         }
         unsigned long long todo = __ballot(p1 > p0);
         while (todo) {  // uniform

@@ -1,0 +1,49 @@
+"""More entries than the int32 offsets of a table hold: the count stays exact
+in 64 bits, entries past the capacity are not written, and an offset that has
+wrapped to a negative value is never used as an index.  The solid is every
+second row of cells, given by hand-made ROWS bins, so the counts are closed
+forms."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+CAP = 4096
+
+
+def test_cut_links():
+    import paper_2512_01251_amd as geo
+    n0 = (1024, 512, 512)
+    nb = 256 * 128 * 128
+    dev = dict(device="cuda")
+    coord = torch.empty((nb, 3), dtype=torch.int32, **dev)
+    geo.geo_level0_blocks(n0, coord)
+    lv = geo.make_level(n0, 0, coord, [])
+    cnt = torch.zeros(3, dtype=torch.int64, **dev)
+    # rows with odd j: one surface interval over the whole line
+    nk = 512 * 512
+    odd = (torch.arange(nk, **dev) % 512) & 1
+    roff = torch.cat([torch.zeros(1, dtype=torch.int64, **dev), torch.cumsum(odd, 0)]).int()
+    rval = torch.full((nk // 2,), (1023 << 15) - 2 ** 31, dtype=torch.int32, **dev)
+    rows = geo.make_bins(geo.GEO_BINS_ROWS, nk, roff, rval, nk // 2, cnt[0:])
+    # every block has one candidate, the last 64 blocks 65 each (two chunks); none is a triangle
+    per = torch.ones(nb, dtype=torch.int64, **dev)
+    per[-64:] = 65
+    loff = torch.cat([torch.zeros(1, dtype=torch.int64, **dev), torch.cumsum(per, 0)]).int()
+    lval = torch.full((int(per.sum()),), -1, dtype=torch.int32, **dev)
+    links = geo.make_bins(geo.GEO_BINS_LINKS, nb, loff, lval, lval.numel(), cnt[1:])
+    V = torch.tensor([[1.0, 1.0, 1.0], [2.0, 1.0, 1.0], [1.0, 2.0, 1.0]], **dev)
+    T = torch.tensor([[0, 1, 2]], dtype=torch.int32, **dev)
+    cell = torch.full((CAP,), -7, dtype=torch.int32, **dev)
+    dr = torch.full((CAP,), 77, dtype=torch.uint8, **dev)
+    q, tri = torch.zeros(CAP, **dev), torch.zeros(CAP, dtype=torch.int32, **dev)
+    ws = torch.empty(geo.geo_workspace_size(geo.GEO_CALL_CUTLINKS, nb, CAP), dtype=torch.uint8, **dev)
+    geo.geo_cutlinks(geo.make_mesh(V, T), lv, rows, links, 27, geo.GEO_PREC_F32_FALLBACK, None, CAP, cnt[2:], cell,
+                     dr, q, tri, None, ws)
+    # cells (i, j even, k) and c = (cx, +-1, cz) inside the domain
+    n = (3 * 1024 - 2) * (2 * 256 - 1) * (3 * 512 - 2)
+    assert n > 2 ** 31 and int(cnt[2].item()) == n
+    # the first block's first cell, in the domain's corner: 4 links to the row above
+    assert cell[:4].tolist() == [0] * 4 and int(cell[4]) == 1
+    assert dr[:4].tolist() == [x + 9 * z + 3 * 2 for z in (1, 2) for x in (1, 2)]
+    assert int(cell.min()) == 0 and (q == -1).all() and (tri == -1).all()
