@@ -148,7 +148,7 @@ __global__ void __launch_bounds__(256) k2_bins(Dev2Mesh m, Dev2Level d, int kind
                 atomicAdd(&cnt[key], 1);
             } else {
                 const int64_t p = (int64_t)off[key] + atomicAdd(&cursor[key], 1);
-                if (p < cap) val[p] = (int32_t)e;
+                if (p >= 0 && p < cap) val[p] = (int32_t)e;  // (offsets past 2^31 - 1 entries wrap)
             }
         };
         if (kind == 0) {
@@ -426,7 +426,7 @@ __global__ void __launch_bounds__(64) k2_cl_fill(Dev2Mesh m, Dev2Level d, const 
         __syncthreads();
         for (int j = lane; j < n; j += 64) {
             const int64_t p = (int64_t)off[b] + j;
-            if (p >= cap) continue;
+            if (p < 0 || p >= cap) continue;  // (offsets past 2^31 - 1 links wrap)
             const int q = lk[j] >> 4;
             link_cell[p] = (int32_t)(16 * b + (lk[j] & 15));
             link_dir[p] = (uint8_t)(q < 4 ? q : q + 1);

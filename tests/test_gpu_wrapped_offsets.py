@@ -47,3 +47,52 @@ def test_cut_links():
     assert cell[:4].tolist() == [0] * 4 and int(cell[4]) == 1
     assert dr[:4].tolist() == [x + 9 * z + 3 * 2 for z in (1, 2) for x in (1, 2)]
     assert int(cell.min()) == 0 and (q == -1).all() and (tri == -1).all()
+
+
+def test_cut_links_2d():
+    import paper_2512_01251_amd as geo
+    n, nb = 32764, 8191 * 8191
+    dev = dict(device="cuda")
+    coord = torch.empty((nb, 2), dtype=torch.int32, **dev)
+    geo.geo2_level0_blocks((n, n), coord)
+    lv = geo.make_level2((n, n), 0, coord, [])
+    cnt = torch.zeros(3, dtype=torch.int64, **dev)
+    # one upward edge at the right end of the domain, ahead of every cell of the rows that list it: the odd ones
+    V = torch.tensor([[float(n), 0.25], [float(n), float(n)]], dtype=torch.float64, **dev)
+    E = torch.tensor([[0, 1]], dtype=torch.int32, **dev)
+    odd = torch.arange(n, **dev) & 1
+    roff = torch.cat([torch.zeros(1, dtype=torch.int64, **dev), torch.cumsum(odd, 0)]).int()
+    rval = torch.zeros(n // 2, dtype=torch.int32, **dev)
+    rows = geo.make_bins(geo.GEO_BINS_ROWS, n, roff, rval, n // 2, cnt[0:])
+    loff = torch.zeros(nb + 1, dtype=torch.int32, **dev)
+    lval = torch.zeros(1, dtype=torch.int32, **dev)
+    links = geo.make_bins(geo.GEO_BINS_LINKS, nb, loff, lval, 1, cnt[1:])
+    cell = torch.full((CAP,), -7, dtype=torch.int32, **dev)
+    dr = torch.full((CAP,), 77, dtype=torch.uint8, **dev)
+    q, edge = torch.zeros(CAP, **dev), torch.zeros(CAP, dtype=torch.int32, **dev)
+    ws = torch.empty(geo.geo_workspace_size(geo.GEO_CALL2_CUTLINKS, nb, 0), dtype=torch.uint8, **dev)
+    geo.geo2_cutlinks(geo.make_mesh2(V, E), lv, rows, links, CAP, cnt[2:], cell, dr, q, edge, ws)
+    total = (3 * n - 2) * (n - 1)  # (i, j even) and c = (cx, +-1) inside the domain
+    assert total > 2 ** 31 and int(cnt[2].item()) == total
+    assert cell[:3].tolist() == [0, 0, 1] and dr[:2].tolist() == [7, 8]
+    assert int(cell.min()) == 0 and (q == -1).all() and (edge == -1).all()
+
+
+def test_row_bins_2d():
+    import paper_2512_01251_amd as geo
+    ny, ne = 32764, 70000  # a comb of vertical edges, each on every row
+    dev = dict(device="cuda")
+    lv = geo.make_level2((64, ny), 0, torch.empty((0, 2), dtype=torch.int32, **dev), [])
+    x = 1.0 + torch.arange(ne, dtype=torch.float64, **dev) / 2048
+    V = torch.stack([torch.stack([x, torch.full_like(x, 0.25)], 1), torch.stack([x, torch.full_like(x, ny)], 1)], 1)
+    E = torch.arange(2 * ne, dtype=torch.int32, **dev).reshape(-1, 2)
+    off = torch.empty(ny + 1, dtype=torch.int32, **dev)
+    val = torch.full((CAP,), -7, dtype=torch.int32, **dev)
+    cnt = torch.zeros(1, dtype=torch.int64, **dev)
+    bins = geo.make_bins(geo.GEO_BINS_ROWS, ny, off, val, CAP, cnt)
+    ws = torch.empty(geo.geo_workspace_size(geo.GEO_CALL2_BINS, ny, 0), dtype=torch.uint8, **dev)
+    geo.geo2_build_bins(geo.make_mesh2(V.reshape(-1, 2).contiguous(), E), lv, geo.GEO_BINS_ROWS, bins, ws)
+    assert ne * ny > 2 ** 31 and int(cnt.item()) == ne * ny
+    assert int(off[1]) == ne
+    v = val.cpu()
+    assert len(torch.unique(v)) == CAP and int(v.min()) >= 0 and int(v.max()) < ne
