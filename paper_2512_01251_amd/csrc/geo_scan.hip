@@ -1,9 +1,11 @@
 // Device-wide exclusive scans of int32 counts and small fill kernels.
 //
 // Tiles of 4,096 values.  Two launches: the sums of all tiles, then the tiles
-// themselves, each adding up the sums of the tiles before it (at most a few
-// thousand words from L2) instead of waiting for a scan of the sums by one
-// workgroup.  Several arrays go through the same two launches, and where no
+// themselves, each adding up the sums of the tiles before it (up to SCAN_SUMS
+// words from L2) instead of waiting for a scan of the sums by one workgroup.
+// Those reads grow with the square of the tiles, so arrays of more than
+// SCAN_SUMS tiles take a launch in between that scans their sums.
+// Several arrays go through the same launches, and where no
 // array has more than SCAN_DIRECT tiles one launch does: a tile then reads the
 // values before it again (at most 48 loads per thread, less than a launch).
 // Bound by launches below about 10^6 values and by HBM above (4 bytes read
@@ -19,6 +21,10 @@ constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_ITEMS = 16;
 constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
 constexpr int SCAN_DIRECT = 4;
+// ROWS bins of 8,192^2 lines (16,384 tiles) without and with that launch: 236 and
+// 207 us; 16,384^2: 1.91 and 0.87 ms (1.13 with three launches of 2,048-value
+// tiles); 5,000^2 (6,104 tiles): 86 and 89 us
+constexpr int64_t SCAN_SUMS = 8192;
 
 // sum of v over the workgroup (every thread calls it)
 __device__ __forceinline__ int64_t block_sum(int64_t v) {
@@ -109,12 +115,52 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_tile_sums(ScanJobs jobs, int64
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
 }
 
+// The tile sums of each array (one workgroup) turned into the sums before each
+// tile.  A thread takes SUM_ITEMS tiles in a row.
+constexpr int SUM_ITEMS = 16;
+__global__ void __launch_bounds__(SCAN_THREADS) k_scan_sums(ScanJobs jobs, int64_t* partials) {
+    __shared__ int64_t wsum[SCAN_THREADS / 64];
+    const int q = blockIdx.x, t = threadIdx.x, w = t >> 6;
+    const int64_t n = (jobs.len[q] + SCAN_TILE - 1) / SCAN_TILE;
+    int64_t* p = partials + jobs.tile0[q];
+    int64_t carry = 0;
+    for (int64_t base = 0; base < n; base += SCAN_THREADS * SUM_ITEMS) {  // uniform
+        const int64_t i0 = base + (int64_t)t * SUM_ITEMS;
+        int64_t v[SUM_ITEMS], s = 0;
+#pragma unroll
+        for (int k = 0; k < SUM_ITEMS; k++) v[k] = i0 + k < n ? p[i0 + k] : 0;
+#pragma unroll
+        for (int k = 0; k < SUM_ITEMS; k++) s += v[k];
+        int64_t incl = s;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t u = __shfl_up(incl, o, 64);
+            if ((t & 63) >= o) incl += u;
+        }
+        if ((t & 63) == 63) wsum[w] = incl;
+        __syncthreads();
+        int64_t ex = carry + incl - s;
+#pragma unroll
+        for (int i = 0; i < SCAN_THREADS / 64; i++) {
+            if (i < w) ex += wsum[i];
+            carry += wsum[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < SUM_ITEMS; k++) {
+            if (i0 + k < n) p[i0 + k] = ex;
+            ex += v[k];
+        }
+    }
+}
+
 // The tile passes through LDS so that global reads and writes are coalesced
 // (lane-consecutive), while each thread scans SCAN_ITEMS consecutive values.
 // The LDS rows are padded by one word per SCAN_ITEMS, so a thread's
 // consecutive items fall in distinct banks.  partials == nullptr: the values
-// of the tiles before are read themselves.
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_tiles(ScanJobs jobs, const int64_t* partials) {
+// of the tiles before are read themselves; scanned: partials holds the sums
+// before each tile.
+__global__ void __launch_bounds__(SCAN_THREADS) k_scan_tiles(ScanJobs jobs, const int64_t* partials, int scanned) {
     __shared__ int tile[SCAN_TILE + SCAN_TILE / SCAN_ITEMS];
     const int q = tile_job(jobs, blockIdx.x);
     const int first = jobs.tile0[q], ti = (int)blockIdx.x - first;
@@ -128,7 +174,9 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_tiles(ScanJobs jobs, cons
 #pragma unroll
     for (int k = 0; k < SCAN_ITEMS; k++) tile[slot(1024 * (k / 4) + 4 * t + (k & 3))] = v[k];
     int64_t before = 0;
-    if (partials)
+    if (scanned)
+        before = t == 0 ? partials[first + ti] : 0;
+    else if (partials)
         for (int i = t; i < ti; i += SCAN_THREADS) before += partials[first + i];
     else
         for (int i = 0; i < ti; i++) before += tile_share(in + (int64_t)i * SCAN_TILE, SCAN_TILE);
@@ -207,9 +255,10 @@ int geo_scan_jobs(ScanJobs& j, int64_t* partials, hipStream_t s) {
         most = nt > most ? nt : most;
     }
     if (tiles == 0) return GEO_OK;
-    const bool direct = most <= SCAN_DIRECT;
+    const bool direct = most <= SCAN_DIRECT, scanned = most > SCAN_SUMS;
     if (!direct) k_tile_sums<<<(unsigned)tiles, SCAN_THREADS, 0, s>>>(j, partials);
-    k_scan_tiles<<<(unsigned)tiles, SCAN_THREADS, 0, s>>>(j, direct ? nullptr : partials);
+    if (scanned) k_scan_sums<<<(unsigned)j.n, SCAN_THREADS, 0, s>>>(j, partials);
+    k_scan_tiles<<<(unsigned)tiles, SCAN_THREADS, 0, s>>>(j, direct ? nullptr : partials, scanned ? 1 : 0);
     GEO_LAUNCH_CHECK();
     return GEO_OK;
 }
