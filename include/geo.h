@@ -452,7 +452,9 @@ int geo_cutlinks_backward(const geo_mesh* mesh, const geo_level* lv, int64_t n_l
  * outputs, GEO_ERR_DEVICE if an event wait fails.
  */
 enum {
-    GEO_KT_ROWS = 0,       /* ROWS bins, triangle pass (count / append)          */
+    GEO_KT_ROWS = 0,       /* ROWS bins, triangle pass (count / append), the
+                              launch for the pieces of large triangles included,
+                              as one bracket; so for GEO_KT_LINKS_BINS          */
     GEO_KT_VOXELIZE = 1,   /* solid voxelization of one level                   */
     GEO_KT_LINKS_BINS = 2, /* LINKS bins, triangle pass (block overlap tests)    */
     GEO_KT_CUTLINKS_Q = 3, /* cut-link q kernel (nearest hit per link)          */

@@ -1119,9 +1119,9 @@ int launch_rows_levels(const DevMesh& m, const DevLevel& d, int precision, const
     kt_record(GEO_KT_ROWS, s, false);
     auto pass = f32 ? k_rows_levels_f32 : k_rows_levels_f64;
     pass<<<g, 64, 0, s>>>(m, d, rl, tpw, w);
-    kt_record(GEO_KT_ROWS, s, true);
     auto pieces = f32 ? k_rows_pieces<float> : k_rows_pieces<double>;
     pieces<<<2048, 64, 0, s>>>(m, d, rl, w);
+    kt_record(GEO_KT_ROWS, s, true);
     GEO_LAUNCH_CHECK();
     return GEO_OK;
 }
@@ -1149,9 +1149,9 @@ int launch_links_pass1(const DevMesh& m, const DevLevel& d, const BinWork& w, hi
     auto pass = f32 ? k_links_pass1<float> : k_links_pass1<double>;
     // (7.2M triangles: 0.64 ms; 0.68 with at most 8,192 workgroups)
     pass<<<grid_for(m.nt, tpw, 16384), 64, 0, s>>>(m, d, tpw, w);
-    kt_record(GEO_KT_LINKS_BINS, s, true);
     auto pieces = f32 ? k_links_pieces<float> : k_links_pieces<double>;
     pieces<<<2048, 64, 0, s>>>(m, d, w);
+    kt_record(GEO_KT_LINKS_BINS, s, true);
     GEO_LAUNCH_CHECK();
     return GEO_OK;
 }
