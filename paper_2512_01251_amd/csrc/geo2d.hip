@@ -362,11 +362,16 @@ __device__ double link_hit2(const double* a, const double* b, double X0, double 
     return num / den;
 }
 
-// One wave per block: each lane holds one candidate edge, 64 at a time, the
-// block's links are taken one after the other, and the nearest hit (the
-// smallest edge index at ties) is the wave's minimum.  Bound by the latency of
-// one test per link (a lane per cell that walked all its directions and edges:
-// 128 us for 1,236 links among 4,096 edges, now 26 us).
+// One wave per block, its candidate edges 64 at a time (a chunk).  A lane per
+// link walks the chunk's edges in LDS, or, where that would take more tests in a
+// row, each lane holds one edge, the block's links are taken one after the
+// other, and the nearest hit (the smallest edge index at ties) is the wave's
+// minimum.  Bound by the latency of one test, and of that minimum.  The calls
+// with a lane per cell that walked all its directions and edges, with a lane per
+// edge always, and now: 53, 79 and 39 us for 34,000 links of a rectangle, 20, 29
+// and 14 us for 1,232 of a 16-gon, 135, 33 and 30 us for 1,244 of a 4,096-gon,
+// 1,190, 100 and 96 us for as many of a 40,000-gon; a lane per link up to three
+// times as many tests: 30 and 102 us for the last two.
 __global__ void __launch_bounds__(64) k2_cl_fill(Dev2Mesh m, Dev2Level d, const int32_t* loff, const int32_t* lval,
                                                  int64_t lcap, double scale, const uint16_t* mask,
                                                  const int32_t* off, int64_t cap, int32_t* link_cell,
@@ -374,6 +379,8 @@ __global__ void __launch_bounds__(64) k2_cl_fill(Dev2Mesh m, Dev2Level d, const 
     __shared__ double bt[128];        // nearest hit of each link so far: its t
     __shared__ int be[128];           // and its edge
     __shared__ unsigned char lk[128]; // cell | direction << 4 of each link, 8 directions as 0..7
+    __shared__ double se[4][64];      // a chunk's edges, and their indices
+    __shared__ int sid[64];
     const int lane = threadIdx.x;
     for (int64_t b = blockIdx.x; b < d.nblocks; b += gridDim.x) {
         const uint16_t mk = lane < 16 ? mask[16 * b + lane] : 0;
@@ -398,6 +405,36 @@ __global__ void __launch_bounds__(64) k2_cl_fill(Dev2Mesh m, Dev2Level d, const 
             if (c0 + lane < e1) {
                 e = lval[c0 + lane];
                 if (!(e >= 0 && e < m.ne && load_edge(m, e, scale, a, bb))) e = -1;
+            }
+            const int nc = e1 - c0 < 64 ? e1 - c0 : 64;
+            if ((n + 63) / 64 * nc <= n) {  // uniform
+                __syncthreads();
+                se[0][lane] = a[0];
+                se[1][lane] = a[1];
+                se[2][lane] = bb[0];
+                se[3][lane] = bb[1];
+                sid[lane] = e;
+                __syncthreads();
+                for (int j = lane; j < n; j += 64) {
+                    const int t4 = lk[j] & 15, q = lk[j] >> 4, k = q < 4 ? q : q + 1;
+                    double best = bt[j];
+                    int w = be[j];
+                    for (int i = 0; i < nc; i++) {
+                        const int ei = sid[i];
+                        if (ei < 0) continue;
+                        const double A[2] = {se[0][i], se[1][i]}, B[2] = {se[2][i], se[3][i]};
+                        const double t = link_hit2(A, B, x0 + (t4 & 3) + 0.5, y0 + (t4 >> 2) + 0.5,
+                                                   (double)(k % 3 - 1), (double)(k / 3 - 1));
+                        if (t >= 0.0 && (t < best || (t == best && ei < w))) {
+                            best = t;
+                            w = ei;
+                        }
+                    }
+                    bt[j] = best;
+                    be[j] = w;
+                }
+                __syncthreads();
+                continue;
             }
             for (int j = 0; j < n; j++) {  // uniform
                 const int t4 = lk[j] & 15, q = lk[j] >> 4, k = q < 4 ? q : q + 1;
