@@ -29,10 +29,10 @@ namespace {
 // ------------------------------------------------------------------------
 constexpr int APP_BUF = 512;
 
-// Group: pairs whose keys repeat within a flush (link bins: neighbouring
-// triangles share blocks) take their ranks with one atomic per key; else one
-// atomic per pair (row bins: keys mostly distinct).
-template <bool Group>
+// Rows: pairs whose keys repeat within a flush (link bins: neighbouring
+// triangles share blocks) take their ranks with one atomic per key and Rows
+// rows of 64 pairs; 0: one atomic per pair (row bins: keys mostly distinct).
+template <int Rows>
 struct Appender {
     int2* buf;       // LDS [APP_BUF]
     int n;           // pairs staged (identical in every lane)
@@ -51,43 +51,55 @@ struct Appender {
         unsigned long long base = 0;
         if (threadIdx.x == 0) base = atomicAdd((blockIdx.x & 1) ? &w.ctl->down : &w.ctl->up, (unsigned long long)n);
         base = __shfl(base, 0, 64);
-        if constexpr (Group) {
-            // Per chunk of 64 pairs, lanes holding the same key form a group;
-            // its lowest lane takes the group's ranks with one atomic (atomics
-            // on one address serialise).  The atomics of four chunks are in
-            // flight together.
+        if constexpr (Rows > 0) {
+            // Four rows of 64 pairs at a time, their atomics in flight together.
+            // Pairs with the same key form a group, whose first pair takes the
+            // group's ranks with one atomic (atomics on one address serialise).
             const int lane = threadIdx.x;
             const unsigned long long lt = (1ull << lane) - 1ull;
             for (int i0 = 0; i0 < n; i0 += 256) {
                 int2 p[4];
-                int lead[4], off[4], cntk[4];
+                int lead[4], off[4], cntk[4];  // lead: the group's first lane | its row << 6
+                unsigned long long rem[4];
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
                     const int i = i0 + 64 * u + lane;
                     const bool valid = i < n;
                     p[u] = valid ? buf[i] : make_int2(-1, 0);
-                    lead[u] = -1;
+                    lead[u] = lane;
                     off[u] = 0;
                     cntk[u] = 0;
-                    unsigned long long rem = __ballot(valid);
-                    while (rem) {  // uniform
-                        const int l = __ffsll(rem) - 1;
-                        const int k = __shfl(p[u].x, l, 64);
-                        const unsigned long long same = __ballot(valid && p[u].x == k) & rem;
-                        if ((same >> lane) & 1ull) {
-                            lead[u] = l;
-                            off[u] = __popcll(same & lt);
-                        }
-                        if (lane == l) cntk[u] = __popcll(same);
-                        rem &= ~same;
-                    }
+                    rem[u] = __ballot(valid);
                 }
+#pragma unroll
+                for (int u = 0; u < 4; u++)
+                    while (rem[u]) {  // uniform
+                        const int l = __ffsll(rem[u]) - 1;
+                        const int k = __builtin_amdgcn_readlane(p[u].x, l);
+                        int c = 0;
+#pragma unroll
+                        for (int v = u; v < u + Rows && v < 4; v++) {
+                            const unsigned long long same = __ballot(p[v].x == k) & rem[v];
+                            if (p[v].x == k) {
+                                lead[v] = l | u << 6;
+                                off[v] = c + __popcll(same & lt);
+                            }
+                            c += __popcll(same);
+                            rem[v] &= ~same;
+                        }
+                        if (lane == l) cntk[u] = c;
+                    }
                 int r[4];
 #pragma unroll
                 for (int u = 0; u < 4; u++) r[u] = cntk[u] ? atomicAdd(&w.cnt[p[u].x], cntk[u]) : 0;
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
-                    const int base_k = __shfl(r[u], lead[u] < 0 ? lane : lead[u], 64);
+                    int base_k = __shfl(r[u], lead[u] & 63, 64);
+#pragma unroll
+                    for (int v = u - 1; v >= 0 && v > u - Rows; v--) {
+                        const int b = __shfl(r[v], lead[u] & 63, 64);
+                        if (lead[u] >> 6 == v) base_k = b;
+                    }
                     const int64_t pos = place(base, i0 + 64 * u + lane);
                     if (p[u].x >= 0 && pos >= 0) {
                         w.pairs[pos] = p[u];
@@ -135,7 +147,7 @@ struct Appender {
     }
 };
 
-using RowAppender = Appender<false>;
+using RowAppender = Appender<0>;
 
 // ------------------------------------------------------------------------
 // per-triangle local frame for the row pass
@@ -822,7 +834,6 @@ constexpr int LINK_BIG = 128;      // (below 256: ix and iy divide exactly)
 constexpr int LINK_PIECES = 64;    // most pieces of a triangle
 constexpr int64_t LINK_PIECE_MAX = 1 << 30;
 
-using LinkAppender = Appender<true>;
 
 struct LinkGrid {  // block geometry of the level
     int L, nb[3], nb0[3];
@@ -911,10 +922,10 @@ __device__ __forceinline__ int64_t link_setup(const DevMesh& m, int64_t t, const
 
 // LINKS_U pairs per lane (item i[u], candidate block b[u], on[u]) through both
 // tests and down the forest; the blocks found are appended
-template <typename V>
+template <typename V, int Rows>
 __device__ __forceinline__ void link_pairs(const DevLevel& d, const LinkGrid& g, const LinkItems<V>& I,
                                            const bool on[LINKS_U], const int i[LINKS_U], const int b[LINKS_U][3],
-                                           const int32_t tri[LINKS_U], LinkAppender& app) {
+                                           const int32_t tri[LINKS_U], Appender<Rows>& app) {
     int idx[LINKS_U];
 #pragma unroll
     for (int u = 0; u < LINKS_U; u++) {
@@ -942,9 +953,9 @@ __device__ __forceinline__ void link_pairs(const DevLevel& d, const LinkGrid& g,
 
 // candidates first .. first + count - 1 of item i (its candidate box by
 // divisions), by the whole wave
-template <typename V>
+template <typename V, int Rows>
 __device__ void link_range(const DevLevel& d, const LinkGrid& g, const LinkItems<V>& I, int i, int32_t t, int64_t first,
-                           int64_t count, LinkAppender& app) {
+                           int64_t count, Appender<Rows>& app) {
     const int lane = threadIdx.x;
     const int64_t sx = I.sx[i], sy = I.sy[i];
     for (int64_t q0 = 0; q0 < count; q0 += 64 * LINKS_U) {  // uniform
@@ -961,7 +972,7 @@ __device__ void link_range(const DevLevel& d, const LinkGrid& g, const LinkItems
             b[u][1] = I.lo[1][i] + (int)(r % sy);
             b[u][2] = I.lo[2][i] + (int)(r / sy);
         }
-        link_pairs<V>(d, g, I, on, item, b, tri, app);
+        link_pairs<V, Rows>(d, g, I, on, item, b, tri, app);
     }
 }
 
@@ -986,13 +997,13 @@ __device__ __forceinline__ bool list_links(const BinWork& w, int64_t n, int32_t 
     return taken;
 }
 
-template <typename V>
+template <typename V, int Rows>
 __global__ void __launch_bounds__(64) k_links_pass1(DevMesh m, DevLevel d, int tpw, BinWork w) {
     __shared__ int2 sbuf[APP_BUF];
     __shared__ LinkItems<V> I;
     __shared__ int mark[64 * LINKS_U];
     const int lane = threadIdx.x;
-    LinkAppender app{sbuf, 0, w};
+    Appender<Rows> app{sbuf, 0, w};
     const LinkGrid g = link_grid(d);
     const int64_t stride = (int64_t)gridDim.x * tpw;
     for (int64_t base = (int64_t)blockIdx.x * tpw; base < m.nt; base += stride) {
@@ -1034,14 +1045,14 @@ __global__ void __launch_bounds__(64) k_links_pass1(DevMesh m, DevLevel d, int t
                 b[u][1] = I.lo[1][i] + r - z * I.sy[i];
                 b[u][2] = I.lo[2][i] + z;
             }
-            link_pairs<V>(d, g, I, on, item, b, tri, app);
+            link_pairs<V, Rows>(d, g, I, on, item, b, tri, app);
         }
         unsigned long long rest = __ballot(nbig > 0);  // refused by the list: by the whole wave
         if (rest) __syncthreads();
         while (rest) {  // uniform
             const int i = __ffsll(rest) - 1;
             rest &= rest - 1;
-            link_range<V>(d, g, I, i, (int32_t)base + i, 0, __shfl((long long)nbig, i, 64), app);
+            link_range<V, Rows>(d, g, I, i, (int32_t)base + i, 0, __shfl((long long)nbig, i, 64), app);
         }
     }
     app.flush();
@@ -1055,7 +1066,7 @@ __global__ void __launch_bounds__(64) k_links_pieces(DevMesh m, DevLevel d, BinW
     int np = w.ctl->list_n;
     if (np < 0 || np > BIN_LIST_CAP) np = BIN_LIST_CAP;
     if ((int)blockIdx.x >= np) return;
-    LinkAppender app{sbuf, 0, w};
+    Appender<1> app{sbuf, 0, w};
     const LinkGrid g = link_grid(d);
     for (int e = blockIdx.x; e < np; e += gridDim.x) {
         const int4 p = w.list[e];
@@ -1063,7 +1074,7 @@ __global__ void __launch_bounds__(64) k_links_pieces(DevMesh m, DevLevel d, BinW
         __syncthreads();
         if (threadIdx.x == 0) link_setup<V>(m, p.x, g, I, 0);
         __syncthreads();
-        link_range<V>(d, g, I, 0, p.x, (int64_t)(((uint64_t)(uint32_t)p.z << 32) | (uint32_t)p.y), p.w, app);
+        link_range<V, 1>(d, g, I, 0, p.x, (int64_t)(((uint64_t)(uint32_t)p.z << 32) | (uint32_t)p.y), p.w, app);
     }
     app.flush();
 }
@@ -1141,12 +1152,24 @@ int launch_rows_levels_scatter(const RowLevels& rl, const BinWork& w, uint64_t* 
 
 int launch_links_pass1(const DevMesh& m, const DevLevel& d, const BinWork& w, hipStream_t s) {
     if (m.nt == 0) return GEO_OK;
-    // triangles per wave, as in the ROWS pass
-    const int64_t per = (m.nt + 4095) / 4096;
+    // triangles per wave, as in the ROWS pass; but half as many waves where the
+    // blocks are few, so that a triangle has few candidates and the waves'
+    // reservations would take most of the time (the call with 20k triangles of 8
+    // spheres over 40k blocks 52 -> 34 us; 112k of a star over 1.48M blocks 94 us
+    // with 4,096 waves, 118 with half)
+    const int64_t waves = d.nblocks < 4 * (int64_t)m.nt ? 2048 : 4096;
+    const int64_t per = (m.nt + waves - 1) / waves;
     const int tpw = per < 4 ? 4 : (per > 64 ? 64 : (int)per);
     const bool f32 = m.vdtype == GEO_F32;
     kt_record(GEO_KT_LINKS_BINS, s, false);
-    auto pass = f32 ? k_links_pass1<float> : k_links_pass1<double>;
+    // Fewer blocks than triangles: these are small and repeat a key many times, so
+    // that its atomics serialise, and four rows of pairs share one (2M triangles
+    // over 512 blocks: 376 -> 185 us, 7.2M over 5.8M 820 -> 802).  Otherwise the
+    // search over four rows costs more than the atomics (20k triangles of an
+    // icosphere over 0.97M blocks: 65 us, 76 with four rows).
+    const bool share = d.nblocks < m.nt;
+    auto pass = f32 ? (share ? k_links_pass1<float, 4> : k_links_pass1<float, 1>)
+                    : (share ? k_links_pass1<double, 4> : k_links_pass1<double, 1>);
     // (7.2M triangles: 0.64 ms; 0.68 with at most 8,192 workgroups)
     pass<<<grid_for(m.nt, tpw, 16384), 64, 0, s>>>(m, d, tpw, w);
     auto pieces = f32 ? k_links_pieces<float> : k_links_pieces<double>;
