@@ -15,7 +15,7 @@
 // two 64-bit block masks are assembled (bit t = I + 4 J + 16 K).  Bound by the
 // L1's rate of accesses and the latency of offsets and entries, which serve two
 // blocks this way and come by loads of 8 and 16 bytes.  On level 0, and where
-// 8 blocks are not such a family, a wave takes 4 blocks, 16 lanes each.  All
+// 8 blocks are not such a family, 16 lanes take a block.  All
 // levels of a step before (4 blocks per wave, loads of 4 bytes), with families,
 // and with wider loads too: 514, 358 and 283 us on the 7.2M-triangle star, 405,
 // 266 and 188 us on 64 spheres, 150, 122 and 96 us on a 1M-triangle star over
@@ -110,6 +110,15 @@ __device__ __forceinline__ void voxelize4(const DevLevel& d, const int32_t* off,
     if (l == 15 && b < d.nblocks) solid[b] = m;
 }
 
+// Level 0, whose blocks are no families: 4 blocks to a wave, four times the waves
+// of the families' kernel (512^3 cells: 78 us, 89 with that; 256^3: 10.5 and 13.7).
+__global__ void __launch_bounds__(256) k_voxelize0(DevLevel d, const int32_t* off, const int32_t* val, int64_t cap,
+                                                   uint64_t* solid) {
+    const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    for (int64_t wb = wave * 4; wb < d.nblocks; wb += nwaves * 4) voxelize4(d, off, val, cap, wb, solid);
+}
+
 constexpr int FAM = 2;  // families of a wave, their loads in flight together
 __global__ void __launch_bounds__(256) k_voxelize(DevLevel d, const int32_t* off, const int32_t* val,
                                                   int64_t cap, uint64_t* solid) {
@@ -129,7 +138,7 @@ __global__ void __launch_bounds__(256) k_voxelize(DevLevel d, const int32_t* off
             int c[3];
 #pragma unroll
             for (int a = 0; a < 3; a++) c[a] = in ? d.bcoord[3 * bo + a] : 0;
-            bool ok = d.level > 0 && in;
+            bool ok = in;
 #pragma unroll
             for (int a = 0; a < 3; a++) {
                 p[u][a] = __builtin_amdgcn_readfirstlane(c[a]);
@@ -180,11 +189,13 @@ __global__ void k_level0(int nbx, int nby, int nbz, int32_t* bcoord) {
 int launch_voxelize(const DevLevel& d, const int32_t* off, const int32_t* val, int64_t cap, uint64_t* solid,
                     hipStream_t s) {
     if (d.nblocks == 0) return GEO_OK;
-    int64_t waves = ((int64_t)d.nblocks + 8 * FAM - 1) / (8 * FAM);
+    const int per_wave = d.level > 0 ? 8 * FAM : 4;
+    int64_t waves = ((int64_t)d.nblocks + per_wave - 1) / per_wave;
     int64_t g = (waves * 64 + 255) / 256;
     if (g > 65536) g = 65536;
     kt_record(GEO_KT_VOXELIZE, s, false);
-    k_voxelize<<<(unsigned)g, 256, 0, s>>>(d, off, val, cap, solid);
+    auto kernel = d.level > 0 ? k_voxelize : k_voxelize0;
+    kernel<<<(unsigned)g, 256, 0, s>>>(d, off, val, cap, solid);
     kt_record(GEO_KT_VOXELIZE, s, true);
     GEO_LAUNCH_CHECK();
     return GEO_OK;
