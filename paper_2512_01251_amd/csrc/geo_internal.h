@@ -21,11 +21,13 @@ GEO_HD __forceinline__ float geo_max(float a, float b) { return __builtin_fmaxf(
 GEO_HD __forceinline__ float geo_min(float a, float b) { return __builtin_fminf(a, b); }
 GEO_HD __forceinline__ double geo_max(double a, double b) { return __builtin_fmax(a, b); }
 GEO_HD __forceinline__ double geo_min(double a, double b) { return __builtin_fmin(a, b); }
-// element k of (a0, a1, a2) as a value select, so that arrays stay in registers
-// (a select over loads from one array would be folded into a dynamic index)
+// element k of (a0, a1, a2), or a where `first`, else b, as a value select, so that
+// arrays stay in registers (a select over loads from one array would be folded
+// into a dynamic index)
 template <typename R> GEO_HD __forceinline__ R pick3(R a0, R a1, R a2, int k) {
     return k == 0 ? a0 : (k == 1 ? a1 : a2);
 }
+template <typename R> GEO_HD __forceinline__ R pick2(R a, R b, int first) { return first ? a : b; }
 #define SEL3(a, k) pick3((a)[0], (a)[1], (a)[2], (k))
 
 // --------------------------------------------------------------------------

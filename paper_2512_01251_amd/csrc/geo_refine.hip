@@ -31,10 +31,11 @@ __device__ __forceinline__ void nbr_offset(int k, int& dx, int& dy, int& dz) {
 // first-child indices of those 8 are found by 8 descents of the forest run
 // side by side (their dependent loads overlap), and each neighbour is its
 // parent's first child plus its octant, with no further load.  The parent of a
-// neighbour is a register, chosen by the block's parity; only a solid block
-// reads its neighbours' words, all at once.  Latency bound: 20.4 -> 14.3 us a
-// level for the 1.05M-triangle star on 192 x 200 x 176 cells (indexed parents
-// in scratch and 26 dependent words before).
+// neighbour is a register, chosen by value by the block's parity (an element of
+// an array chosen that way would be indexed in scratch); only a solid block reads
+// its neighbours' words, all at once.  Latency bound, a level of the
+// 1.05M-triangle star on 192 x 200 x 176 cells: 20.4 us with 26 dependent words,
+// 14.2 with the parents in 112 bytes of scratch, 12.6 now.
 __global__ void k_ref_nbr(DevLevel d, const uint64_t* solid, int32_t* nbr, uint8_t* cls) {
     const int64_t nb = d.nblocks;
     const int L = d.level;
@@ -96,15 +97,15 @@ __global__ void k_ref_nbr(DevLevel d, const uint64_t* solid, int32_t* nbr, uint8
 #pragma unroll
             for (int q = 0; q < 4; q++) {
                 const int z = 6 * (q & 1) + 18 * (q >> 1);
-                fc[z + 1] = (bc[0] & 1) ? fc[z] : fc[z + 2];
+                fc[z + 1] = pick2(fc[z], fc[z + 2], bc[0] & 1);
             }
 #pragma unroll
             for (int q = 0; q < 6; q++) {
                 const int z = q % 3 + 18 * (q / 3);
-                fc[z + 3] = (bc[1] & 1) ? fc[z] : fc[z + 6];
+                fc[z + 3] = pick2(fc[z], fc[z + 6], bc[1] & 1);
             }
 #pragma unroll
-            for (int q = 0; q < 9; q++) fc[q + 9] = (bc[2] & 1) ? fc[q] : fc[q + 18];
+            for (int q = 0; q < 9; q++) fc[q + 9] = pick2(fc[q], fc[q + 18], bc[2] & 1);
 #pragma unroll
             for (int k = 0; k < 26; k++) {
                 int dv[3];
