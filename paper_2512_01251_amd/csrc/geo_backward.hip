@@ -28,6 +28,10 @@ constexpr int BW_RUN = 2048;           // links per workgroup, at most
 // fill the table after a round or two, so a longer run merges nothing more: runs
 // of two rounds
 constexpr int BW_FINE = 8, BW_RUN_FINE = 2 * BW_THREADS;
+// from BW_DENSE links per triangle on all workgroups add to few vertices, whose
+// atomics in HBM serialise: half as many workgroups (0.79M links on 300
+// triangles: 35 us, 49 with 2,048)
+constexpr int BW_DENSE = 64;
 // places that a vertex is looked for in the table (4, 8, 16, 48: 179, 178, 181
 // and 211 us for 0.85M links on 2M triangles; 69, 68, 68 and 117 on 448k)
 constexpr int BW_PROBES = 8;
@@ -204,9 +208,10 @@ int launch_backward(const DevMesh& m, const DevLevel& d, int64_t n_links, const 
     if (n_links <= 0) return GEO_OK;
     // runs of BW_RUN links, shorter ones where that would leave the chip idle
     // (below 2,048 workgroups, 8 on each CU: 0.85M links on 112k triangles 36 us,
-    // 50 with 1,024) and on fine meshes (13.4M links on 7.2M triangles: 0.87 ms,
+    // 50 with the 1,024 of meshes of few vertices) and on fine meshes (13.4M links on 7.2M triangles: 0.87 ms,
     // 0.90 with BW_RUN, 0.99 with 256)
-    int64_t run = (n_links / 2048 + BW_THREADS - 1) / BW_THREADS * BW_THREADS;
+    const int64_t fill = n_links < BW_DENSE * (int64_t)m.nt ? 2048 : 1024;
+    int64_t run = (n_links / fill + BW_THREADS - 1) / BW_THREADS * BW_THREADS;
     const int64_t most = n_links < BW_FINE * (int64_t)m.nt ? BW_RUN_FINE : BW_RUN;
     run = run < BW_THREADS ? BW_THREADS : (run > most ? most : run);
     const int64_t g = (n_links + run - 1) / run;
