@@ -28,15 +28,18 @@ namespace {
 // places it without atomics.
 // ------------------------------------------------------------------------
 constexpr int APP_BUF = 512;
+constexpr int APP_TAB_BITS = 9, APP_TAB = 1 << APP_TAB_BITS;
 
-// Rows: pairs whose keys repeat within a flush (link bins: neighbouring
-// triangles share blocks) take their ranks with one atomic per key and Rows
-// rows of 64 pairs; 0: one atomic per pair (row bins: keys mostly distinct).
-template <int Rows>
+// Group: pairs whose keys repeat within a flush (link bins: neighbouring
+// triangles share blocks) take their ranks with one atomic per key and 256
+// pairs (atomics on one address serialise); else one atomic per pair (row bins:
+// keys mostly distinct).
+template <bool Group>
 struct Appender {
     int2* buf;       // LDS [APP_BUF]
     int n;           // pairs staged (identical in every lane)
     const BinWork& w;
+    unsigned* tab;   // LDS [APP_TAB] (Group)
 
     // array position of the i-th pair of a flush, or -1 past the capacity
     __device__ __forceinline__ int64_t place(unsigned long long base, int i) const {
@@ -51,61 +54,68 @@ struct Appender {
         unsigned long long base = 0;
         if (threadIdx.x == 0) base = atomicAdd((blockIdx.x & 1) ? &w.ctl->down : &w.ctl->up, (unsigned long long)n);
         base = __shfl(base, 0, 64);
-        if constexpr (Rows > 0) {
-            // Four rows of 64 pairs at a time, their atomics in flight together.
-            // Pairs with the same key form a group, whose first pair takes the
-            // group's ranks with one atomic (atomics on one address serialise).
+        if constexpr (Group) {
+            // 256 pairs at a time, four of a lane.  Pairs with the same key meet in
+            // a slot of an LDS table (open addressing, never more than half full),
+            // which counts them and holds the number of the first, whose key it is
+            // and whose lane then takes the slot's ranks with one atomic.  The
+            // whole LINKS call with groups found by ballots within rows of 64
+            // pairs, and with the table: 803 and 724 us on the 7.2M-triangle star,
+            // 200 and 186 us on 64 spheres, 313 and 124 us on a 40,000-triangle
+            // cylinder, 82 and 70 us on the 112k star.
             const int lane = threadIdx.x;
-            const unsigned long long lt = (1ull << lane) - 1ull;
+            constexpr unsigned EMPTY = ~0u;
             for (int i0 = 0; i0 < n; i0 += 256) {
+#pragma unroll
+                for (int k = 0; k < APP_TAB / 64; k++) tab[64 * k + lane] = EMPTY;
+                __syncthreads();
                 int2 p[4];
-                int lead[4], off[4], cntk[4];  // lead: the group's first lane | its row << 6
-                unsigned long long rem[4];
+                unsigned at[4];  // slot | rank in it << 16
+                bool head[4];    // the slot's first
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
-                    const int i = i0 + 64 * u + lane;
-                    const bool valid = i < n;
-                    p[u] = valid ? buf[i] : make_int2(-1, 0);
-                    lead[u] = lane;
-                    off[u] = 0;
-                    cntk[u] = 0;
-                    rem[u] = __ballot(valid);
+                    const int i = 64 * u + lane;
+                    p[u] = i0 + i < n ? buf[i0 + i] : make_int2(-1, 0);
+                    at[u] = 0;
+                    head[u] = false;
                 }
 #pragma unroll
-                for (int u = 0; u < 4; u++)
-                    while (rem[u]) {  // uniform
-                        const int l = __ffsll(rem[u]) - 1;
-                        const int k = __builtin_amdgcn_readlane(p[u].x, l);
-                        int c = 0;
-#pragma unroll
-                        for (int v = u; v < u + Rows && v < 4; v++) {
-                            const unsigned long long same = __ballot(p[v].x == k) & rem[v];
-                            if (p[v].x == k) {
-                                lead[v] = l | u << 6;
-                                off[v] = c + __popcll(same & lt);
-                            }
-                            c += __popcll(same);
-                            rem[v] &= ~same;
+                for (int u = 0; u < 4; u++) {
+                    if (p[u].x < 0) continue;
+                    unsigned s = ((unsigned)p[u].x * 2654435761u) >> (32 - APP_TAB_BITS);
+                    while (true) {
+                        unsigned e = __hip_atomic_load(&tab[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        if (e == EMPTY) e = atomicCAS(&tab[s], EMPTY, (unsigned)(64 * u + lane) << 16 | 1u);
+                        if (e == EMPTY) {
+                            at[u] = s;
+                            head[u] = true;
+                            break;
                         }
-                        if (lane == l) cntk[u] = c;
+                        if (buf[i0 + (e >> 16)].x == p[u].x) {
+                            at[u] = s | (atomicAdd(&tab[s], 1u) & 0xffffu) << 16;
+                            break;
+                        }
+                        s = (s + 1) & (APP_TAB - 1);
                     }
+                }
+                __syncthreads();
                 int r[4];
 #pragma unroll
-                for (int u = 0; u < 4; u++) r[u] = cntk[u] ? atomicAdd(&w.cnt[p[u].x], cntk[u]) : 0;
+                for (int u = 0; u < 4; u++) r[u] = head[u] ? atomicAdd(&w.cnt[p[u].x], (int)(tab[at[u]] & 0xffffu)) : 0;
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < 4; u++)
+                    if (head[u]) tab[at[u]] = (unsigned)r[u];
+                __syncthreads();
 #pragma unroll
                 for (int u = 0; u < 4; u++) {
-                    int base_k = __shfl(r[u], lead[u] & 63, 64);
-#pragma unroll
-                    for (int v = u - 1; v >= 0 && v > u - Rows; v--) {
-                        const int b = __shfl(r[v], lead[u] & 63, 64);
-                        if (lead[u] >> 6 == v) base_k = b;
-                    }
                     const int64_t pos = place(base, i0 + 64 * u + lane);
                     if (p[u].x >= 0 && pos >= 0) {
                         w.pairs[pos] = p[u];
-                        w.rank[pos] = base_k + off[u];
+                        w.rank[pos] = (int)tab[at[u] & (APP_TAB - 1)] + (int)(at[u] >> 16);
                     }
                 }
+                __syncthreads();
             }
         } else {
             // four returning atomics in flight per lane before their results are used
@@ -147,7 +157,7 @@ struct Appender {
     }
 };
 
-using RowAppender = Appender<0>;
+using RowAppender = Appender<false>;
 
 // ------------------------------------------------------------------------
 // per-triangle local frame for the row pass
@@ -579,7 +589,7 @@ __device__ __forceinline__ void rows_levels_body(const DevMesh& m, const DevLeve
     __shared__ int sbase[GEO_MAX_LEVELS];
     const int lane = threadIdx.x;
     if (lane < GEO_MAX_LEVELS) sbase[lane] = rl.base[lane];
-    RowAppender app{sbuf, 0, w};
+    RowAppender app{sbuf, 0, w, nullptr};
     Stats st;
     const bool f32v = m.vdtype == GEO_F32;
     const int64_t stride = (int64_t)gridDim.x * tpw;
@@ -668,7 +678,7 @@ __global__ void __launch_bounds__(64) k_rows_pieces(DevMesh m, DevLevel d, RowLe
     int np = w.ctl->list_n;
     if (np < 0 || np > BIN_LIST_CAP) np = BIN_LIST_CAP;
     if ((int)blockIdx.x >= np) return;
-    RowAppender app{sbuf, 0, w};
+    RowAppender app{sbuf, 0, w, nullptr};
     Stats st;
     for (int e = blockIdx.x; e < np; e += gridDim.x) {
         const int4 p = w.list[e];
@@ -759,7 +769,7 @@ struct LinkItems {
     double nrad[64];                // radius of the block's reach along n, with its margins
     int lo[3][64];                  // candidate blocks: lo + (0..sx-1, 0..sy-1, ..)
     int sx[64], sy[64];
-    int ix[64], iy[64];             // ceil(65536 / sx), ceil(65536 / sy)
+    int ix[64], iy[64];             // ceil(2^20 / sx), ceil(2^20 / sy)
     int pre[64];                    // number of the triangle's first pair
 };
 
@@ -825,15 +835,20 @@ __device__ __forceinline__ bool tri_box_stage2(const double c[3], double hs, con
 // triangle they are of, so that their forest descents overlap.  Bound by VALU
 // work and by the latency of the descents.  A triangle with more than LINK_BIG
 // candidates is cut into pieces for a second launch, as in the ROWS pass.
-// Before (one lane per triangle, its candidates in turn) and now: 0.82 and
-// 0.64 ms on 7.2M triangles (24.3M entries), 163 and 79 us on 112k, 103 and 17
-// us on 1,792, 3.3 and 0.02 ms on a 1,024-triangle cylinder.  Two counters
-// instead of one and buffers of 512 instead of 1,024 pairs are 0.15 ms of it.
+// Before (one lane per triangle, its candidates in turn) and now, both launches:
+// 0.81 and 0.54 ms on 7.2M triangles (24.3M entries), 160 and 50 us on 112k, 100
+// and 19 us on 1,792, 3.31 and 0.065 ms on a 1,024-triangle cylinder.  Two
+// counters instead of one and buffers of 512 instead of 1,024 pairs are 0.15 ms
+// of the first.
 constexpr int LINKS_U = 4;
-constexpr int LINK_BIG = 128;      // (below 256: ix and iy divide exactly)
+// (at most 1,024: ix and iy divide exactly.  The call with 128, 256 and 512: 95,
+// 48 and 48 us on an icosphere of 5,120 triangles over 0.97M blocks, 263, 139 and
+// 139 us on a cylinder of 40,000, 68, 85 and 123 us on one of 1,024)
+constexpr int LINK_BIG = 256;
 constexpr int LINK_PIECES = 64;    // most pieces of a triangle
 constexpr int64_t LINK_PIECE_MAX = 1 << 30;
 
+using LinkAppender = Appender<true>;
 
 struct LinkGrid {  // block geometry of the level
     int L, nb[3], nb0[3];
@@ -915,17 +930,17 @@ __device__ __forceinline__ int64_t link_setup(const DevMesh& m, int64_t t, const
     if (sz[0] <= 0 || sz[1] <= 0 || sz[2] <= 0) return 0;
     I.sx[i] = sz[0];
     I.sy[i] = sz[1];
-    I.ix[i] = (65535 + sz[0]) / sz[0];
-    I.iy[i] = (65535 + sz[1]) / sz[1];
+    I.ix[i] = (1048575 + sz[0]) / sz[0];
+    I.iy[i] = (1048575 + sz[1]) / sz[1];
     return (int64_t)sz[0] * sz[1] * sz[2];
 }
 
 // LINKS_U pairs per lane (item i[u], candidate block b[u], on[u]) through both
 // tests and down the forest; the blocks found are appended
-template <typename V, int Rows>
+template <typename V>
 __device__ __forceinline__ void link_pairs(const DevLevel& d, const LinkGrid& g, const LinkItems<V>& I,
                                            const bool on[LINKS_U], const int i[LINKS_U], const int b[LINKS_U][3],
-                                           const int32_t tri[LINKS_U], Appender<Rows>& app) {
+                                           const int32_t tri[LINKS_U], LinkAppender& app) {
     int idx[LINKS_U];
 #pragma unroll
     for (int u = 0; u < LINKS_U; u++) {
@@ -953,33 +968,57 @@ __device__ __forceinline__ void link_pairs(const DevLevel& d, const LinkGrid& g,
 
 // candidates first .. first + count - 1 of item i (its candidate box by
 // divisions), by the whole wave
-template <typename V, int Rows>
+template <typename V>
 __device__ void link_range(const DevLevel& d, const LinkGrid& g, const LinkItems<V>& I, int i, int32_t t, int64_t first,
-                           int64_t count, Appender<Rows>& app) {
+                           int64_t count, LinkAppender& app) {
+    // a lane's candidate by division once, then 64 further on each time by carries
     const int lane = threadIdx.x;
-    const int64_t sx = I.sx[i], sy = I.sy[i];
+    const int sx = I.sx[i], sy = I.sy[i], dx = 64 % sx, dy = 64 / sx % sy, dz = 64 / sx / sy;
+    int x, y, z;
+    if (first + lane <= UINT32_MAX) {
+        const unsigned c = (unsigned)(first + lane), r = c / (unsigned)sx;
+        x = (int)(c - r * (unsigned)sx);
+        z = (int)(r / (unsigned)sy);
+        y = (int)(r - (unsigned)z * (unsigned)sy);
+    } else {
+        const int64_t c = first + lane, r = c / sx;
+        x = (int)(c - r * sx);
+        y = (int)(r % sy);
+        z = (int)(r / sy);
+    }
     for (int64_t q0 = 0; q0 < count; q0 += 64 * LINKS_U) {  // uniform
         bool on[LINKS_U];
         int item[LINKS_U], b[LINKS_U][3];
         int32_t tri[LINKS_U];
 #pragma unroll
         for (int u = 0; u < LINKS_U; u++) {
-            const int64_t q = q0 + 64 * u + lane, c = first + q, r = c / sx;
-            on[u] = q < count;
+            on[u] = q0 + 64 * u + lane < count;
             item[u] = i;
             tri[u] = t;
-            b[u][0] = I.lo[0][i] + (int)(c - r * sx);
-            b[u][1] = I.lo[1][i] + (int)(r % sy);
-            b[u][2] = I.lo[2][i] + (int)(r / sy);
+            b[u][0] = I.lo[0][i] + x;
+            b[u][1] = I.lo[1][i] + y;
+            b[u][2] = I.lo[2][i] + z;
+            x += dx;
+            y += dy;
+            z += dz;
+            if (x >= sx) {
+                x -= sx;
+                y++;
+            }
+            if (y >= sy) {
+                y -= sy;
+                z++;
+            }
         }
-        link_pairs<V, Rows>(d, g, I, on, item, b, tri, app);
+        link_pairs<V>(d, g, I, on, item, b, tri, app);
     }
 }
 
 // pieces of a large triangle to the list (triangle, first candidate in 64
 // bits, count); returns whether the list took them
 __device__ __forceinline__ bool list_links(const BinWork& w, int64_t n, int32_t tri) {
-    const int64_t want = ((n + LINK_PIECES - 1) / LINK_PIECES + 127) & ~(int64_t)127;
+    constexpr int64_t step = 64 * LINKS_U;  // what a wave takes at a time
+    const int64_t want = ((n + LINK_PIECES - 1) / LINK_PIECES + step - 1) & ~(step - 1);
     const bool big = n > 0 && want <= LINK_PIECE_MAX;
     const int k = big ? (int)((n + want - 1) / want) : 0;
     const int incl = wave_incl_scan(k), total = __shfl(incl, 63, 64);
@@ -997,13 +1036,14 @@ __device__ __forceinline__ bool list_links(const BinWork& w, int64_t n, int32_t 
     return taken;
 }
 
-template <typename V, int Rows>
+template <typename V>
 __global__ void __launch_bounds__(64) k_links_pass1(DevMesh m, DevLevel d, int tpw, BinWork w) {
     __shared__ int2 sbuf[APP_BUF];
     __shared__ LinkItems<V> I;
     __shared__ int mark[64 * LINKS_U];
+    __shared__ unsigned stab[APP_TAB];
     const int lane = threadIdx.x;
-    Appender<Rows> app{sbuf, 0, w};
+    LinkAppender app{sbuf, 0, w, stab};
     const LinkGrid g = link_grid(d);
     const int64_t stride = (int64_t)gridDim.x * tpw;
     for (int64_t base = (int64_t)blockIdx.x * tpw; base < m.nt; base += stride) {
@@ -1040,19 +1080,19 @@ __global__ void __launch_bounds__(64) k_links_pass1(DevMesh m, DevLevel d, int t
                 tri[u] = (int32_t)base + i;
                 // candidate c = x + sx (y + sy z), c < LINK_BIG
                 const int c = on[u] ? p - I.pre[i] : 0;
-                const int r = (c * I.ix[i]) >> 16, z = (r * I.iy[i]) >> 16;
+                const int r = (c * I.ix[i]) >> 20, z = (r * I.iy[i]) >> 20;
                 b[u][0] = I.lo[0][i] + c - r * I.sx[i];
                 b[u][1] = I.lo[1][i] + r - z * I.sy[i];
                 b[u][2] = I.lo[2][i] + z;
             }
-            link_pairs<V, Rows>(d, g, I, on, item, b, tri, app);
+            link_pairs<V>(d, g, I, on, item, b, tri, app);
         }
         unsigned long long rest = __ballot(nbig > 0);  // refused by the list: by the whole wave
         if (rest) __syncthreads();
         while (rest) {  // uniform
             const int i = __ffsll(rest) - 1;
             rest &= rest - 1;
-            link_range<V, Rows>(d, g, I, i, (int32_t)base + i, 0, __shfl((long long)nbig, i, 64), app);
+            link_range<V>(d, g, I, i, (int32_t)base + i, 0, __shfl((long long)nbig, i, 64), app);
         }
     }
     app.flush();
@@ -1063,10 +1103,11 @@ template <typename V>
 __global__ void __launch_bounds__(64) k_links_pieces(DevMesh m, DevLevel d, BinWork w) {
     __shared__ int2 sbuf[APP_BUF];
     __shared__ LinkItems<V> I;
+    __shared__ unsigned stab[APP_TAB];
     int np = w.ctl->list_n;
     if (np < 0 || np > BIN_LIST_CAP) np = BIN_LIST_CAP;
     if ((int)blockIdx.x >= np) return;
-    Appender<1> app{sbuf, 0, w};
+    LinkAppender app{sbuf, 0, w, stab};
     const LinkGrid g = link_grid(d);
     for (int e = blockIdx.x; e < np; e += gridDim.x) {
         const int4 p = w.list[e];
@@ -1074,7 +1115,7 @@ __global__ void __launch_bounds__(64) k_links_pieces(DevMesh m, DevLevel d, BinW
         __syncthreads();
         if (threadIdx.x == 0) link_setup<V>(m, p.x, g, I, 0);
         __syncthreads();
-        link_range<V, 1>(d, g, I, 0, p.x, (int64_t)(((uint64_t)(uint32_t)p.z << 32) | (uint32_t)p.y), p.w, app);
+        link_range<V>(d, g, I, 0, p.x, (int64_t)(((uint64_t)(uint32_t)p.z << 32) | (uint32_t)p.y), p.w, app);
     }
     app.flush();
 }
@@ -1155,21 +1196,14 @@ int launch_links_pass1(const DevMesh& m, const DevLevel& d, const BinWork& w, hi
     // triangles per wave, as in the ROWS pass; but half as many waves where the
     // blocks are few, so that a triangle has few candidates and the waves'
     // reservations would take most of the time (the call with 20k triangles of 8
-    // spheres over 40k blocks 52 -> 34 us; 112k of a star over 1.48M blocks 94 us
-    // with 4,096 waves, 118 with half)
+    // spheres over 40k blocks 52 us with 4,096 waves, 34 with half; 112k of a star
+    // over 1.48M blocks 94 and 118 us)
     const int64_t waves = d.nblocks < 4 * (int64_t)m.nt ? 2048 : 4096;
     const int64_t per = (m.nt + waves - 1) / waves;
     const int tpw = per < 4 ? 4 : (per > 64 ? 64 : (int)per);
     const bool f32 = m.vdtype == GEO_F32;
     kt_record(GEO_KT_LINKS_BINS, s, false);
-    // Fewer blocks than triangles: these are small and repeat a key many times, so
-    // that its atomics serialise, and four rows of pairs share one (2M triangles
-    // over 512 blocks: 376 -> 185 us, 7.2M over 5.8M 820 -> 802).  Otherwise the
-    // search over four rows costs more than the atomics (20k triangles of an
-    // icosphere over 0.97M blocks: 65 us, 76 with four rows).
-    const bool share = d.nblocks < m.nt;
-    auto pass = f32 ? (share ? k_links_pass1<float, 4> : k_links_pass1<float, 1>)
-                    : (share ? k_links_pass1<double, 4> : k_links_pass1<double, 1>);
+    auto pass = f32 ? k_links_pass1<float> : k_links_pass1<double>;
     // (7.2M triangles: 0.64 ms; 0.68 with at most 8,192 workgroups)
     pass<<<grid_for(m.nt, tpw, 16384), 64, 0, s>>>(m, d, tpw, w);
     auto pieces = f32 ? k_links_pieces<float> : k_links_pieces<double>;

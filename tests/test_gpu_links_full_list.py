@@ -11,22 +11,22 @@ from test_gpu_links_pieces import _met
 
 pytestmark = pytest.mark.gpu
 
-LIST_CAP, BIG, PIECES = 65536, 128, 64  # the list's entries; candidates that a wave does itself; most pieces
+LIST_CAP, STEP, PIECES = 65536, 256, 64  # the list's entries; candidates that a wave does itself; most pieces
 
 
 def _pieces(P, nb):
-    """Pieces of triangles P [t, 3, 3]: the blocks whose widened box meets the bounding box, cut in multiples of 128."""
+    """Pieces of triangles P [t, 3, 3]: the blocks whose widened box meets the bounding box, cut in multiples of 256."""
     lo = np.maximum(np.ceil((P.min(1) - 4.5) / 4 - 1e-7), 0)
     hi = np.minimum(np.floor((P.max(1) + 0.5) / 4 + 1e-7), nb - 1)
     n = (hi - lo + 1).prod(1).astype(np.int64)
-    piece = ((n + PIECES - 1) // PIECES + 127) // 128 * 128
-    return np.where(n > BIG, (n + piece - 1) // piece, 0)
+    piece = ((n + PIECES - 1) // PIECES + STEP - 1) // STEP * STEP
+    return np.where(n > STEP, (n + piece - 1) // piece, 0)
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 def test_more_pieces_than_the_list_holds(dtype):
     import paper_2512_01251_amd as geo
-    n, n0, nb, boxes = 256, (256, 256, 256), 64, 320
+    n, n0, nb, boxes = 256, (256, 256, 256), 64, 400
     k = np.arange(boxes)
     lo = np.stack([4.03 + 0.0131 * k, 4.07 + 0.0137 * k, 4.11 + 0.0139 * k], 1)
     m = meshes.merge([meshes.box(a, n - a) for a in lo])
