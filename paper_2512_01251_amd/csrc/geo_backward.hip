@@ -14,9 +14,10 @@
 // gathers and the LDS atomics, so the table is small (14 KB), and the atomics
 // in HBM (19 per ns), so it is kept over a run of up to BW_RUN links.  Before (nine
 // sums per link, by segmented prefix sums over the wave and an LDS table of
-// vertices per 256 links) and now: 547 and 300 us for 14.5M links on a
-// 448k-triangle star, 2.66 and 1.53 ms for 58M on the 7.2M star; two tables in
-// 28 KB took 360 us, two replicas of the sums 435, runs of 1,024 330, 4,096 315.
+// vertices per 256 links) and now: 543 and 244 us for 14.5M links on a
+// 448k-triangle star, 2.66 and 1.28 ms for 58M on the 7.2M star.  Measured on the
+// first beside this form at 300 us (its gathers by single words): two tables in
+// 28 KB 360 us, two replicas of the sums 435, runs of 1,024 330, 4,096 315.
 #include "geo_internal.h"
 
 namespace {

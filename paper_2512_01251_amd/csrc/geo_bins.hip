@@ -3,8 +3,9 @@
 // ROWS bins hold, per x-row line of a level, the exact surface events along
 // the line (parity crossings and on-surface intervals); they are built from
 // the triangles: for each row line inside a triangle's yz bounding box it is
-// decided exactly whether the line meets it, and where along the line.  LINKS bins hold, per block, the triangles overlapping the block
-// box widened by one cell (the widened bin cover of Algorithm 2).
+// decided exactly whether the line meets it, and where along the line.  LINKS
+// bins hold, per block, the triangles overlapping the block box widened by half
+// a cell on every side, the reach of its links (Algorithm 2 widens by a cell).
 //
 // Both are counting sorts without a global sort: pass 1 appends (key, value)
 // pairs with one atomic per wave and counts per key, an exclusive scan turns
